@@ -6,21 +6,19 @@
 // explicit 7-point FD and added, times c(s), into the output), organised for
 // a 256-thread workgroup of four waves, one per SIMD, that runs one source
 // line (r = 7, 8), two (r = 5, 6) or four (r = 4) side by side:
-//   * the W^3 window cells are numbered flat, i = (cy W + cx) W + z (z
-//     fastest), and thread t of a line's SG threads owns the RUN consecutive
-//     cells [RUN t, RUN t + RUN) in registers (RUN = 20 at r = 8: 246 of 256
-//     lanes busy; RUN / 4 odd, so the exchange accesses of 16 consecutive
-//     lanes meet no LDS bank twice);
+//   * the W^3 window cells are numbered flat, i = cy PY + cx W + z (z fastest;
+//     PY is W^2 rounded up to a multiple of 4, the cells between are unused),
+//     and thread t of a line's SG threads owns the RUN consecutive cells
+//     [RUN t, RUN t + RUN) in registers (RUN = 20 at r = 8: 249 of 256 lanes
+//     busy; RUN / 4 odd, so the exchange accesses of 16 consecutive lanes
+//     meet no LDS bank twice);
 //   * the z neighbours of a cell are its run neighbours (registers), except
 //     at the two run ends (from LDS); a run crossing a column boundary meets
 //     a window wall there (coefficient 0);
-//   * the x and y neighbours are the runs at offsets +-W and +-W^2, read from
-//     the LDS copy of the window as 128-bit loads of the aligned span that
-//     covers them (the offsets are odd, so a run of RUN cells is covered by
-//     RUN / 4 + 1 aligned 16-byte chunks; the misalignment is the same for
-//     every thread and is resolved at compile time).  Where RUN > W (every
-//     radius 4..8) the runs at +-W overlap the own run: only the W cells
-//     before and after it are read (aligned, ceil(W / 4) chunks each, which
+//   * the y neighbours are the runs at offsets +-PY, read from the LDS copy of
+//     the window as aligned 128-bit loads (RUN / 4 each).  The runs at +-W (x)
+//     overlap the own run where RUN > W (every radius 4..8): only the W cells
+//     before and after it are read (aligned, ceil(W / 4) loads each, which
 //     also hold the two run-end z neighbours), the rest come from registers;
 //   * double-buffered exchange, one barrier per sub-step;
 //   * the superposition ring is a shift register of RUN FP64 accumulators
@@ -28,165 +26,24 @@
 //     window plane z = 0 hold the finished plane sz - R, which is added to
 //     c_out with one atomic per window column; then every accumulator moves
 //     down one cell (cell i takes cell i + 1, the run's top cell takes the
-//     next thread's bottom cell through LDS), which is the window of source
-//     sz + 1.  LDS holds only the exchange buffers (<= 50 KB), so two
-//     workgroups share a CU and overlap each other's barriers.
+//     next thread's bottom cell), which is the window of source sz + 1.
+// What bounds a sub-step is the LDS pipe: a 128-bit write of a wave takes 13.6
+// clocks of it and a read 5.2 (measured alone), 5 + 20 of them per wave at r =
+// 8, i.e. 690 clocks per window and sub-step against 560 of FP32 FMAs.  The
+// pitch PY saves two reads per wave and sub-step (the offset W^2 is odd, and a
+// misaligned run spans RUN / 4 + 1 loads).  LDS (<= 53 KB) and 168 registers
+// let three workgroups share a CU and fill each other's barrier and LDS waits;
+// at that budget the compiler keeps the ring in private memory across the
+// sub-step loop, which itself holds no spills.  96^3 steps, 3 workgroups of
+// pitch PY against 2 of pitch W^2: r = 4 (50 sub-steps) 12.3 -> 8.9 ms, r = 5
+// (78) 31.1 -> 24.8 ms, r = 6 (113) 68.6 -> 63.0 ms, r = 7 (153) 174 -> 163 ms,
+// r = 8 (200) 233 -> 222 ms.
 // Per cell and sub-step the arithmetic is that of one_substep (same terms,
 // same order), so the kernels equal line_kernel's bit for bit.
-#include "fdirw_device.h"
+#include "fdirw_flat.h"
 #include "fdirw_launch.h"
 
 namespace fdirw {
-
-namespace {
-
-// Cells per thread when sg threads share a window of w3 cells: a multiple of
-// 4 whose quarter is odd, so that the 16-byte run starts of 16 consecutive
-// lanes fall on 16 distinct groups of four LDS banks (a quarter of 2 or 4
-// would put two or four lanes on one group: 2- or 4-way conflicts on every
-// exchange access).
-constexpr int odd_run(int need)
-{
-    int q = (need + 3) / 4;
-    if (q % 2 == 0) ++q;
-    return 4 * q;
-}
-constexpr int run_for(int w3, int sg) { return odd_run((w3 + sg - 1) / sg); }
-
-// Threads per source line of the fused step at radius R: 64, 128 or 256,
-// whichever leaves the fewest of a 256-thread workgroup's lanes idle with at
-// most 20 cells per thread (the register budget of two waves per SIMD); the
-// workgroup runs 256 / that many lines side by side.  r = 4: 4 lines of 64
-// threads x 12 cells (61 busy); r = 5, 6: 2 lines of 128 x 12 / 20 (111 /
-// 110 busy); r = 7, 8: one line of 256 x 20 (169 / 246 busy).
-constexpr int line_threads(int R)
-{
-    const int w3 = (2 * R + 1) * (2 * R + 1) * (2 * R + 1);
-    int best = 256, best_busy = -1;
-    for (int sg = 256; sg >= 64; sg /= 2) {
-        const int run = run_for(w3, sg);
-        if (run > 20) continue;
-        const int busy = (w3 + run - 1) / run * (256 / sg);
-        if (busy > best_busy) { best_busy = busy; best = sg; }
-    }
-    return best;
-}
-
-template <int R, int SG_ = line_threads(R)> struct Flat {
-    static constexpr int W = 2 * R + 1;
-    static constexpr int W2 = W * W;
-    static constexpr int W3 = W2 * W;
-    static constexpr int NT = 256;                             // threads per workgroup
-    static constexpr int SG = SG_;                             // threads per window
-    static constexpr int LPW = NT / SG;                        // windows per workgroup
-    static constexpr int RUN = run_for(W3, SG);                // cells per thread
-    static constexpr int NACT = (W3 + RUN - 1) / RUN;          // threads of a window that own cells
-    static constexpr int PAD = ru(W2 + 4, 4);                  // zero cells before and after
-    // one exchange buffer of one window: its threads past the window (index
-    // >= NACT) run the sub-steps too, on zero values and coefficients,
-    // writing zeros after it
-    static constexpr int XLEN = ru(PAD + SG * RUN + W2 + 8 + PAD, 4);
-    static_assert(NT % SG == 0 && NACT <= SG, "window does not fit its threads");
-};
-
-// LDS of the fused kernels sized for every radius 0..8: exchange floats
-// (two buffers per window) and output-plane doubles (one per parity).
-constexpr int flat_xb_max()
-{
-    int m = 0;
-    for (int r = 0; r <= 8; ++r) {
-        const int w = 2 * r + 1, w2 = w * w, sg = line_threads(r), run = run_for(w2 * w, sg);
-        const int pad = ru(w2 + 4, 4), xlen = ru(pad + sg * run + w2 + 8 + pad, 4);
-        m = m > 2 * (256 / sg) * xlen ? m : 2 * (256 / sg) * xlen;
-    }
-    return m;
-}
-constexpr int flat_plane_max()
-{
-    int m = 0;
-    for (int r = 0; r <= 8; ++r) {
-        const int w2 = (2 * r + 1) * (2 * r + 1), v = 256 / line_threads(r) * w2;
-        m = m > v ? m : v;
-    }
-    return m;
-}
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-
-// Misalignment m in [0, 4) of a neighbour run at offset d from an aligned start.
-constexpr int mis(int d) { return ((d % 4) + 4) % 4; }
-
-// Reads the RUN values at buf[base + d .. + RUN) (base 4-aligned) as aligned
-// 128-bit loads into v[0 .. RUN).
-template <int RUN, int D>
-__device__ __forceinline__ void read_run(const float *__restrict__ buf, int base, float (&v)[RUN])
-{
-    constexpr int M = mis(D);
-    constexpr int NC = (RUN + M + 3) / 4;
-    const v4f *p = (const v4f *)(buf + base + D - M);
-    float t[4 * NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        v4f q = p[c];
-        // keep the whole 16-byte load (otherwise the unused lanes of the
-        // first / last chunk let the compiler split it into 32-bit loads)
-        asm("" : "+v"(q));
-        t[4 * c] = q.x; t[4 * c + 1] = q.y; t[4 * c + 2] = q.z; t[4 * c + 3] = q.w;
-    }
-#pragma unroll
-    for (int k = 0; k < RUN; ++k) v[k] = t[k + M];
-}
-
-// Reads the 4 NC values at buf[base + OFF .. + 4 NC) (base + OFF 4-aligned) as
-// aligned 128-bit loads into t.
-template <int NC, int OFF>
-__device__ __forceinline__ void read_chunks(const float *__restrict__ buf, int base, float (&t)[4 * NC])
-{
-    const v4f *p = (const v4f *)(buf + base + OFF);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        v4f q = p[c];
-        asm("" : "+v"(q));
-        t[4 * c] = q.x; t[4 * c + 1] = q.y; t[4 * c + 2] = q.z; t[4 * c + 3] = q.w;
-    }
-}
-
-// The runs at -W and +W (v0, v1) and the cells next to the run's ends (zlo,
-// zhi) for the run of g at buf[base .. + RUN).  Where RUN > W they are the W
-// cells before the run (previous thread) and after it (next thread) plus
-// RUN - W cells of the own run (registers); else the aligned spans of read_run.
-template <int RUN, int W>
-__device__ __forceinline__ void read_x_runs(const float *__restrict__ buf, int base, const float (&g)[RUN],
-                                            float (&v0)[RUN], float (&v1)[RUN], float &zlo, float &zhi)
-{
-    if constexpr (RUN > W) {
-        constexpr int NC = (W + 3) / 4;
-        float tp[4 * NC], tn[4 * NC];
-        read_chunks<NC, -4 * NC>(buf, base, tp);
-        read_chunks<NC, RUN>(buf, base, tn);
-#pragma unroll
-        for (int k = 0; k < RUN; ++k) {
-            v0[k] = k < W ? tp[4 * NC - W + k] : g[k < W ? 0 : k - W];
-            v1[k] = k < RUN - W ? g[k < RUN - W ? k + W : 0] : tn[k + W - RUN];
-        }
-        zlo = tp[4 * NC - 1];
-        zhi = tn[0];
-    } else {
-        zlo = buf[base - 1];
-        zhi = buf[base + RUN];
-        read_run<RUN, -W>(buf, base, v0);
-        read_run<RUN, W>(buf, base, v1);
-    }
-}
-
-template <int R> struct FlatSeg {
-    static constexpr int RUN = Flat<R>::RUN;
-    float xm[RUN], xp[RUN], ym[RUN], yp[RUN];
-    float zf[RUN + 1];        // zf[k]: face between run cells k - 1 and k
-    float diag[RUN];
-};
-
-}  // namespace
 
 // One source line of one domain for the flat layout; the face coefficients
 // come from the accessor f (FaceArrays<float> over [3][n] FP32 owned-face
@@ -204,8 +61,6 @@ template <typename Faces> struct FlatLine {
     double *part;
     int part_z0, part_planes;
 };
-
-constexpr int FLAT_NT = 256;
 
 // Adds plane Z (when inside the domain) of the window of line (sx, sy) to
 // c_out: column col of the window, held at pl[col], goes to cell (Z,
@@ -231,29 +86,42 @@ __device__ __forceinline__ void flush_plane(const Line &a, const double *pl, int
     }
 }
 
-constexpr int FLAT_XB = flat_xb_max();
-constexpr int FLAT_PLANE = flat_plane_max();
+// LDS of one workgroup at radius R: exchange floats (two buffers per line) and
+// output-plane doubles (one per line and parity); _MAX over the radii 0..8.
+template <int R> constexpr int FLAT_XB = 2 * Flat<R>::LPW * Flat<R>::XLEN;
+template <int R> constexpr int FLAT_PLANE = 2 * Flat<R>::LPW * Flat<R>::W2;
+constexpr int flat_max(int a, int b) { return a > b ? a : b; }
+template <int R> constexpr int flat_xb_max()
+{
+    if constexpr (R == 0) return FLAT_XB<0>;
+    else return flat_max(FLAT_XB<R>, flat_xb_max<R - 1>());
+}
+template <int R> constexpr int flat_plane_max()
+{
+    if constexpr (R == 0) return FLAT_PLANE<0>;
+    else return flat_max(FLAT_PLANE<R>, flat_plane_max<R - 1>());
+}
+constexpr int FLAT_EDGE = 2 * (FLAT_NT / 64 + 1);            // one value per wave and parity, and a 0
 
 // The sources (sx, sy, z0 .. z1 - 1) of the lines line0 .. line0 + nlines - 1
 // (line = sy nx + sx; 1 <= nlines <= Flat<R>::LPW) by a workgroup of FLAT_NT
 // threads, Flat<R>::SG threads per line, the lines side by side in lockstep
 // (their sub-steps share the barriers): kernels generated and superposed into
-// a.c_out (FP64 atomics).  xb: 2 LPW XLEN floats of LDS (16-byte aligned),
-// red: 4 doubles, shbuf: 2 x (FLAT_NT + 1) doubles, plane: 2 x FLAT_PLANE
-// doubles.  Every thread of the block calls it; kmin, kmax and used come back
-// per line (the same in every thread of the line's group).  A window group
-// past nlines runs on the first line with its sources taken as zero and
-// writes nothing.  DET:
+// a.c_out (FP64 atomics).  xb: FLAT_XB<R> floats of LDS (16-byte aligned),
+// red: 4 doubles, edge: FLAT_EDGE doubles, plane: FLAT_PLANE<R> doubles.  Every thread of the block calls it; the
+// first thread of line g leaves the line's smallest and largest kernel mass
+// and its number of kernels in fig[3 g .. 3 g + 2] (LDS; kept there and not in
+// registers, which the sub-step loop needs all).  A window group
+// past nlines runs on zero coefficients and writes nothing.  DET:
 // the deterministic form (partial slots, a.part).
 template <int R, bool DET, typename Faces>
 __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, int nlines, int z0, int z1, float *xb,
-                                          double *red, double (*shbuf)[FLAT_NT + 1], double (*plane)[FLAT_PLANE],
-                                          double &kmin, double &kmax, int &used)
+                                          double *red, double *edge, double *plane, double *fig)
 {
     using F = Flat<R>;
-    constexpr int W = F::W, W2 = F::W2, W3 = F::W3, RUN = F::RUN, PAD = F::PAD, XLEN = F::XLEN;
+    constexpr int W = F::W, W2 = F::W2, RUN = F::RUN, PAD = F::PAD, XLEN = F::XLEN;
     constexpr int SG = F::SG, LPW = F::LPW;
-    static_assert(F::NT == FLAT_NT && 2 * LPW * XLEN <= FLAT_XB && LPW * W2 <= FLAT_PLANE, "LDS sizes");
+    static_assert(F::NT == FLAT_NT, "workgroup size");
 
     const int t = threadIdx.x;
     const int g = LPW == 1 ? 0 : t / SG;                      // the thread's line in the workgroup
@@ -271,17 +139,11 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     float *const xg = xb + g * XLEN;                         // the line's first exchange buffer
     __syncthreads();                                        // LDS of a previous line is no longer read
     for (int i = t; i < 2 * LPW * XLEN; i += F::NT) xb[i] = 0.0f;
-    if (t == 0) { shbuf[0][F::NT] = 0.0; shbuf[1][F::NT] = 0.0; }
+    if (t < FLAT_EDGE) edge[t] = 0.0;
+    if (tg == 0) { fig[3 * g] = INFINITY; fig[3 * g + 1] = -INFINITY; fig[3 * g + 2] = 0.0; }
     __syncthreads();
     const int64_t nxy = (int64_t)a.nx * a.ny;
 
-    // window position of run cell k: flat index s0 + k = (cy W + cx) W + z
-#define FDIRW_POS(k, cx, cy, zz, ok)                                   \
-    const int i_##k = s0v + (k);                                       \
-    const int col_##k = i_##k / W;                                     \
-    const int zz = i_##k - col_##k * W;                               \
-    const int cx = col_##k % W, cy = col_##k / W;                      \
-    const bool ok = i_##k < F::NACT * RUN && i_##k < W3
     // s0v: the run start laundered per source, so that the cell positions are
     // recomputed where they are used instead of being kept in registers
     // across the sub-step loop (idle threads get a start past the window)
@@ -293,7 +155,7 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     int par = 0;
 
     for (int sz = z0; sz < z1; ++sz) {
-        int s0v = act ? s0 : W3;
+        int s0v = act ? s0 : F::NCELL;
         asm volatile("" : "+v"(s0v));
         // the sources of the workgroup's lines: a kernel is generated for
         // every line when one of them is nonzero (uniform per block)
@@ -308,144 +170,59 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
             }
         }
         if (any) {
-            if (cs != 0.0) ++used;                          // uniform per line
             FlatSeg<R> c;
-            // coefficients of the run's cells for the window of (sx, sy, sz)
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) {
-                FDIRW_POS(k, cx, cy, zw, ok);
-                const int X = sx - R + cx, Y = sy - R + cy, Z = sz - R + zw;
-                const bool in = ok && X >= 0 && X < a.nx && Y >= 0 && Y < a.ny && Z >= 0 && Z < a.nz;
-                float xm = 0.f, xp = 0.f, ym = 0.f, yp = 0.f, zf = 0.f;
-                if (in) {
-                    const int64_t i = (int64_t)Z * nxy + (int64_t)Y * a.nx + X;
-                    if (cx < W - 1) xp = a.f.x(i, X);
-                    if (cx > 0 && X > 0) xm = a.f.x(i - 1, X - 1);
-                    if (cy < W - 1) yp = a.f.y(i, Y);
-                    if (cy > 0 && Y > 0) ym = a.f.y(i - a.nx, Y - 1);
-                    if (zw > 0 && Z > 0) zf = a.f.z(i - nxy, Z - 1);
-                }
-                c.xm[k] = xm; c.xp[k] = xp; c.ym[k] = ym; c.yp[k] = yp; c.zf[k] = zf;
-            }
-            {
-                // face above the run's top cell: the face below cell s0 + RUN
-                const int i = s0 + RUN;
-                const int col = i / W, z = i - col * W;
-                const int X = sx - R + col % W, Y = sy - R + col / W, Z = sz - R + z;
-                float zf = 0.f;
-                if (act && i < W3 && z > 0 && X >= 0 && X < a.nx && Y >= 0 && Y < a.ny && Z > 0 && Z < a.nz)
-                    zf = a.f.z((int64_t)(Z - 1) * nxy + (int64_t)Y * a.nx + X, Z - 1);
-                c.zf[RUN] = zf;
-            }
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) {
-                float s = c.xm[k] + c.xp[k];
-                s = s + c.ym[k];
-                s = s + c.yp[k];
-                s = s + c.zf[k];
-                s = s + c.zf[k + 1];
-                c.diag[k] = 1.0f - s;
-            }
+            flat_load<R>(c, a.f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
             float Gs[RUN];
-#define G(k) Gs[k]
 #pragma unroll
             for (int k = 0; k < RUN; ++k) {
-                FDIRW_POS(k, cx, cy, zw, ok);
-                G(k) = (ok && cx == R && cy == R && zw == R) ? 1.0f : 0.0f;
+                const FlatCell<R> p(s0v + k);
+                Gs[k] = (p.ok && p.cx == R && p.cy == R && p.z == R) ? 1.0f : 0.0f;
             }
-
-            // n_sub explicit sub-steps, exchange buffers alternating.  Every
-            // thread runs them without a branch (an idle thread's run is
-            // zeros: its writes land in the zero band after the window), so
-            // that the new values need not be merged with the old ones of
-            // idle threads; two sub-steps per trip let the registers of G and
-            // of the new values alternate instead of being copied back.
-            auto substep = [&](float *buf) {
-                // a wave that has passed the barrier issues ahead of the
-                // other workgroup's wave on its SIMD until its next write
-                __builtin_amdgcn_s_setprio(0);
-                {
-#pragma unroll
-                    for (int q = 0; q < RUN / 4; ++q)
-                        *(float4 *)(buf + own + 4 * q) = make_float4(G(4 * q), G(4 * q + 1), G(4 * q + 2), G(4 * q + 3));
-                }
-                __syncthreads();
-                __builtin_amdgcn_s_setprio(1);
-                {
-                    // the neighbour runs are requested two directions ahead
-                    // of their use (two buffers), so their LDS latency
-                    // overlaps the FMAs of the previous direction
-                    float zlo, zhi;
-                    float v0[RUN], v1[RUN];
-                    read_x_runs<RUN, W>(buf, own, Gs, v0, v1, zlo, zhi);
-                    float acc2[RUN];
-#pragma unroll
-                    for (int k = 0; k < RUN; ++k) {
-                        float a2 = c.diag[k] * G(k);
-                        a2 = __builtin_fmaf(c.zf[k], k > 0 ? G(k - 1) : zlo, a2);
-                        acc2[k] = __builtin_fmaf(c.zf[k + 1], k < RUN - 1 ? G(k + 1) : zhi, a2);
-                    }
-#pragma unroll
-                    for (int k = 0; k < RUN; ++k) acc2[k] = __builtin_fmaf(c.xm[k], v0[k], acc2[k]);
-                    read_run<RUN, -W2>(buf, own, v0);
-#pragma unroll
-                    for (int k = 0; k < RUN; ++k) acc2[k] = __builtin_fmaf(c.xp[k], v1[k], acc2[k]);
-                    read_run<RUN, W2>(buf, own, v1);
-#pragma unroll
-                    for (int k = 0; k < RUN; ++k) acc2[k] = __builtin_fmaf(c.ym[k], v0[k], acc2[k]);
-#pragma unroll
-                    for (int k = 0; k < RUN; ++k) G(k) = __builtin_fmaf(c.yp[k], v1[k], acc2[k]);
-                }
-            };
-            int step = 0;
-            for (; step + 1 < a.n_sub; step += 2) {
-                substep(xg);
-                substep(xg + LPW * XLEN);
-            }
-            if (step < a.n_sub) substep(xg);
-            // kernel mass: per thread in cell order, xor butterfly per wave,
-            // the line's waves in order
+            flat_substeps<R, false>(Gs, c, xg, xg + LPW * XLEN, own, a.n_sub, 0u);
+            // kernel mass: per thread in cell order, then over the line's threads
             double ms = 0.0;
             if (act) {
 #pragma unroll
-                for (int k = 0; k < RUN; ++k) ms += (double)G(k);
+                for (int k = 0; k < RUN; ++k) ms += (double)Gs[k];
             }
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) ms += __shfl_xor(ms, off, 64);
-            __syncthreads();
-            if ((t & 63) == 0) red[t >> 6] = ms;
-            __syncthreads();
-            double m;
-            if constexpr (SG == 256) m = ((red[0] + red[1]) + red[2]) + red[3];
-            else if constexpr (SG == 128) m = red[2 * g] + red[2 * g + 1];
-            else m = red[g];
-            if (cs != 0.0) {
-                kmin = fmin(kmin, m);
-                kmax = fmax(kmax, m);
+            const double m = flat_window_sum<R>(ms, red, g);
+            // (the source is read again, not kept across the sub-steps)
+            int gv = g;
+            asm volatile("" : "+v"(gv));
+            cs = live ? a.c_in[(int64_t)sz * nxy + line0 + gv] : 0.0;
+            if (tg == 0 && cs != 0.0) {
+                fig[3 * g] = fmin(fig[3 * g], m);
+                fig[3 * g + 1] = fmax(fig[3 * g + 1], m);
+                fig[3 * g + 2] += 1.0;
             }
             const double scale = cs != 0.0 ? cs / m : 0.0;
 #pragma unroll
-            for (int k = 0; k < RUN; ++k) acc[k] = __builtin_fma(scale, (double)G(k), acc[k]);
-#undef G
+            for (int k = 0; k < RUN; ++k) acc[k] = __builtin_fma(scale, (double)Gs[k], acc[k]);
         }
+        s0v = act ? s0 : F::NCELL;
+        asm volatile("" : "+v"(s0v));
         // window plane z = 0 is plane sz - R of the output, complete for this
         // line: its cells go to the LDS plane by column, so that the flush
         // below gives consecutive lanes consecutive columns (coalesced atomics)
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
-            FDIRW_POS(k, cx, cy, zw, ok);
-            (void)cx; (void)cy;
-            if (zw == 0) {
-                if (ok) plane[par][g * W2 + col_k] = acc[k];
+            const FlatCell<R> p(s0v + k);
+            if (p.z == 0) {
+                if (p.ok) plane[(par * LPW + g) * W2 + p.col] = acc[k];
                 acc[k] = 0.0;
             }
         }
-        // shift by one cell: the window of source sz + 1 (nothing enters a
-        // line's last thread from the next line's first)
-        shbuf[par][t] = act ? acc[0] : 0.0;
+        // shift by one cell: the window of source sz + 1.  The run's top cell
+        // takes the next thread's bottom cell (the next lane's, or through
+        // LDS the next wave's first; a line's last thread takes 0)
+        const double bottom = act ? acc[0] : 0.0;
+        double *const ed = edge + par * (FLAT_EDGE / 2);
+        if ((t & 63) == 0) ed[t >> 6] = bottom;
         __syncthreads();
-        if (live) flush_plane<R, SG, DET>(a, plane[par] + g * W2, sx, sy, sz - R, tg);
-        const double top = tg + 1 < SG ? shbuf[par][t + 1] : 0.0;
+        if (live) flush_plane<R, SG, DET>(a, plane + (par * LPW + g) * W2, sx, sy, sz - R, tg);
+        double top = __shfl_down(bottom, 1, 64);
+        if ((t & 63) == 63) top = ed[(t >> 6) + 1];
+        if (tg + 1 == SG) top = 0.0;
 #pragma unroll
         for (int k = 0; k < RUN - 1; ++k) acc[k] = acc[k + 1];
         acc[RUN - 1] = top;
@@ -453,30 +230,28 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     }
     // the planes still held: after the last shift cell (col, z) holds plane
     // z1 - R + z (z = W - 1 holds the plane no source reached yet: zeros)
-    const int s0v = act ? s0 : W3;
+    const int s0v = act ? s0 : F::NCELL;
     for (int zp = 0; zp < W - 1; ++zp) {
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
-            FDIRW_POS(k, cx, cy, zw, ok);
-            (void)cx; (void)cy;
-            if (ok && zw == zp) plane[par][g * W2 + col_k] = acc[k];
+            const FlatCell<R> p(s0v + k);
+            if (p.ok && p.z == zp) plane[(par * LPW + g) * W2 + p.col] = acc[k];
         }
         __syncthreads();
-        if (live) flush_plane<R, SG, DET>(a, plane[par] + g * W2, sx, sy, z1 - R + zp, tg);
+        if (live) flush_plane<R, SG, DET>(a, plane + (par * LPW + g) * W2, sx, sy, z1 - R + zp, tg);
         par ^= 1;
     }
-#undef FDIRW_POS
 }
 
 template <int R, bool LAB, bool DET>
-__global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(3)))
 flat_line_kernel(LineArgs a)
 {
     using F = Flat<R>;
-    __shared__ __align__(16) float xb[2 * F::LPW * F::XLEN];
+    __shared__ __align__(16) float xb[FLAT_XB<R>];
     __shared__ double red[4];
-    __shared__ double shbuf[2][FLAT_NT + 1];
-    __shared__ double plane[2][FLAT_PLANE];
+    __shared__ double edge[FLAT_EDGE];
+    __shared__ double plane[FLAT_PLANE<R>];
     // block b: lines LPW lg .. + LPW - 1 (those inside the domain), segment sgi
     const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
     const int lg = b / a.n_seg, sgi = b - lg * a.n_seg;
@@ -484,26 +259,34 @@ flat_line_kernel(LineArgs a)
     const int z0 = a.z_begin + sgi * a.seg_len;
     const int z1 = min(a.z_end, z0 + a.seg_len);
     if (z0 >= z1) return;                                   // uniform per block
-    double kmin = INFINITY, kmax = -INFINITY;
-    int used = 0;
+    __shared__ double fig[3 * F::LPW];
     if constexpr (LAB) {
         const FaceLabels<float> f{a.label, (const float *)a.lam_tab, a.n_phase, a.nx, a.ny, a.nz};
         const FlatLine<FaceLabels<float>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, f,
                                              a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
-        flat_line<R, DET>(fl, line0, nlines, z0, z1, xb, red, shbuf, plane, kmin, kmax, used);
+        flat_line<R, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
     } else {
         const float *lx = (const float *)a.lx;
         const FlatLine<FaceArrays<float>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, {lx, lx + a.n, lx + 2 * a.n},
                                              a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
-        flat_line<R, DET>(fl, line0, nlines, z0, z1, xb, red, shbuf, plane, kmin, kmax, used);
+        flat_line<R, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
     }
     // per line and segment: entry line n_seg + sgi of the kernel-mass range
     const int g = (int)threadIdx.x / F::SG;
     if ((int)threadIdx.x == g * F::SG && g < nlines) {
         const int64_t e = (int64_t)(line0 + g) * a.n_seg + sgi;
-        if (a.wg_kmass) { a.wg_kmass[2 * e] = kmin; a.wg_kmass[2 * e + 1] = kmax; }
-        if (a.n_used && used) atomicAdd(a.n_used, (unsigned long long)used);
+        if (a.wg_kmass) { a.wg_kmass[2 * e] = fig[3 * g]; a.wg_kmass[2 * e + 1] = fig[3 * g + 1]; }
+        if (a.n_used && fig[3 * g + 2] > 0.0) atomicAdd(a.n_used, (unsigned long long)fig[3 * g + 2]);
     }
+}
+
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T> __device__ __forceinline__ T *uniform(T *p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = (uint32_t)uniform((int)(uint32_t)v), hi = (uint32_t)uniform((int)(uint32_t)(v >> 32));
+    return (T *)((uint64_t)hi << 32 | lo);
 }
 
 // The lines of one batched item as a separate function per radius (the
@@ -513,25 +296,25 @@ flat_line_kernel(LineArgs a)
 template <int R>
 __device__ __attribute__((noinline)) void flat_line_item(const FlatLine<FaceArrays<float>> &a, int line0, int nlines,
                                                           int z0, int z1, float *xb, double *red,
-                                                          double (*shbuf)[FLAT_NT + 1],
-                                                          double (*plane)[FLAT_PLANE], double *km, int *used)
+                                                          double *edge, double *plane, double *fig, double *km, int *used)
 {
-    constexpr int SG = Flat<R>::SG;
-    double kmin = INFINITY, kmax = -INFINITY;
-    int u = 0;
-    flat_line<R, false>(a, line0, nlines, z0, z1, xb, red, shbuf, plane, kmin, kmax, u);
-    // combine the lines' figures through LDS (shbuf is free once every
-    // thread has left flat_line)
-    const int t = threadIdx.x, g = t / SG;
-    __syncthreads();
-    if (t == g * SG) { shbuf[0][2 * g] = kmin; shbuf[0][2 * g + 1] = kmax; shbuf[1][g] = (double)u; }
-    __syncthreads();
+    // arguments of a function arrive in vector registers: without this the
+    // sub-step loop counts per lane, and its registers are copied every trip
+    const int nx = uniform(a.nx), ny = uniform(a.ny), nz = uniform(a.nz);
+    const int64_t n = (int64_t)nx * ny * nz;
+    const float *lx = uniform(a.f.lx);
+    const FlatLine<FaceArrays<float>> u{nx, ny, nz, n, uniform(a.n_sub), {lx, lx + n, lx + 2 * n},
+                                        uniform(a.c_in), uniform(a.c_out), nullptr, 0, 0};
+    nlines = uniform(nlines);
+    flat_line<R, false>(u, uniform(line0), nlines, uniform(z0), uniform(z1), xb, red, edge, plane, fig);
+    const int t = threadIdx.x;
+    __syncthreads();                                         // every line's figures are there
     if (t == 0) {
         double lo = INFINITY, hi = -INFINITY, n = 0.0;
         for (int h = 0; h < nlines; ++h) {
-            lo = fmin(lo, shbuf[0][2 * h]);
-            hi = fmax(hi, shbuf[0][2 * h + 1]);
-            n += shbuf[1][h];
+            lo = fmin(lo, fig[3 * h]);
+            hi = fmax(hi, fig[3 * h + 1]);
+            n += fig[3 * h + 2];
         }
         km[0] = lo;
         km[1] = hi;
@@ -543,13 +326,14 @@ __device__ __attribute__((noinline)) void flat_line_item(const FlatLine<FaceArra
 // workgroup pulls items (domain, a run of source lines, plane range) from the
 // atomic counter and runs flat_line for the domain's radius.  An item holds
 // up to Flat<r>::LPW consecutive lines of its domain (flat_lines_per_group).
-__global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(3)))
 flat_batched_kernel(BatchArgs a)
 {
-    __shared__ __align__(16) float xb[FLAT_XB];
+    __shared__ __align__(16) float xb[flat_xb_max<8>()];
     __shared__ double red[4];
-    __shared__ double shbuf[2][FLAT_NT + 1];
-    __shared__ double plane[2][FLAT_PLANE];
+    __shared__ double edge[FLAT_EDGE];
+    __shared__ double plane[flat_plane_max<8>()];
+    __shared__ double fig[3 * (FLAT_NT / 32)];
     __shared__ int s_item;
     for (;;) {
         if (threadIdx.x == 0) s_item = (int)atomicAdd(a.head, 1u);
@@ -565,15 +349,15 @@ flat_batched_kernel(BatchArgs a)
         double km[2];
         int used = 0;
         switch (d.r) {
-        case 0: flat_line_item<0>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        case 1: flat_line_item<1>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        case 2: flat_line_item<2>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        case 3: flat_line_item<3>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        case 4: flat_line_item<4>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        case 5: flat_line_item<5>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        case 6: flat_line_item<6>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        case 7: flat_line_item<7>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
-        default: flat_line_item<8>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, shbuf, plane, km, &used); break;
+        case 0: flat_line_item<0>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 1: flat_line_item<1>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 2: flat_line_item<2>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 3: flat_line_item<3>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 4: flat_line_item<4>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 5: flat_line_item<5>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 6: flat_line_item<6>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 7: flat_line_item<7>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        default: flat_line_item<8>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
         }
         if (threadIdx.x == 0) {
             if (a.item_kmass) { a.item_kmass[2 * it] = km[0]; a.item_kmass[2 * it + 1] = km[1]; }
@@ -596,194 +380,6 @@ hipError_t batched_flat_occupancy(int *blocks)
 int flat_lines_per_group(int r)
 {
     return r >= 0 && r <= 8 ? FLAT_NT / line_threads(r) : 1;
-}
-
-// Window kernels with a steady flow (the flow_window_kernel update: diffusion
-// plus first-order upwind advection through every face, far-field cells held
-// at 0) in the flat layout, FP32: Flat<R>::LPW sources per workgroup side by
-// side (as many as flat_line runs lines), the seven update coefficients of a
-// thread's RUN cells in registers, the same neighbour reads as flat_line and
-// the same FMA sequence per cell as flow_window_kernel (diagonal, then x-,
-// x+, y-, y+, z-, z+).  G leaves in the window's (z, y, x) order through the
-// LDS run region of the window's second exchange buffer (coalesced stores).
-// A window group past the list, or on a source outside every group, runs on
-// zeros and writes nothing.
-template <int R>
-__global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(2)))
-flat_flow_kernel(FlowArgs a)
-{
-    using F = Flat<R>;
-    constexpr int W = F::W, W2 = F::W2, W3 = F::W3, RUN = F::RUN, PAD = F::PAD, XLEN = F::XLEN;
-    constexpr int SG = F::SG, LPW = F::LPW;
-    static_assert(RUN <= 32, "sink flags in one word");
-    __shared__ __align__(16) float xb[2 * LPW * XLEN];
-    __shared__ double red[4];
-    const int t = threadIdx.x;
-    const int g = LPW == 1 ? 0 : t / SG;                      // the thread's window in the workgroup
-    const int tg = t - g * SG;
-    const int s0 = tg * RUN;
-    const bool act = tg < F::NACT;
-    const int own = PAD + s0;
-    float *const xg = xb + g * XLEN;                         // the window's first exchange buffer
-    const float *lx = (const float *)a.lam, *ly = lx + a.n, *lz = ly + a.n;
-    const double *ux = a.u, *uy = ux + a.n, *uz = uy + a.n;
-    const double cour = a.dt / a.h;
-    const int64_t nxy = (int64_t)a.nx * a.ny;
-    for (int i = t; i < 2 * LPW * XLEN; i += F::NT) xb[i] = 0.0f;
-
-    for (int64_t q0 = (int64_t)blockIdx.x * LPW; q0 < a.n_src; q0 += (int64_t)gridDim.x * LPW) {
-        // the sources of the workgroup's windows: those outside every group
-        // are skipped (when all are, the whole step: uniform per block)
-        bool any = false, live = false;
-        int64_t src = 0;
-#pragma unroll
-        for (int h = 0; h < LPW; ++h) {
-            if (q0 + h < a.n_src) {
-                const int64_t sh = a.src ? a.src[q0 + h] : a.src_base + q0 + h;
-                const bool lh = !(a.node && a.node[sh] < 0);
-                any = any || lh;
-                if (h == g) { live = lh; src = sh; }
-            }
-        }
-        if (!any) continue;
-        const int64_t q = q0 + g;
-        __syncthreads();                                       // LDS of the previous sources is no longer read
-        const int sx = (int)(src % a.nx), sy = (int)((src / a.nx) % a.ny), sz = (int)(src / nxy);
-        int s0v = act ? s0 : W3;
-        asm volatile("" : "+v"(s0v));
-        float c0[RUN], cxm[RUN], cxp[RUN], cym[RUN], cyp[RUN], czm[RUN], czp[RUN];
-        unsigned sink = 0;
-        float Gs[RUN];
-#pragma unroll
-        for (int k = 0; k < RUN; ++k) {
-            const int i = s0v + k;
-            const int colk = i / W, zw = i - colk * W;
-            const int cx = colk % W, cy = colk / W;
-            const int X = sx - R + cx, Y = sy - R + cy, Z = sz - R + zw;
-            const bool in = live && i < W3 && X >= 0 && X < a.nx && Y >= 0 && Y < a.ny && Z >= 0 && Z < a.nz;
-            // per face: lambda (diffusion) and the Courant number of the flow
-            // (through the -x, +x, -y, +y, -z, +z faces); the inflow adds to
-            // the neighbour's coefficient, the outflow leaves the diagonal
-            float fl[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, vl[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (in) {
-                const int64_t c = (int64_t)Z * nxy + (int64_t)Y * a.nx + X;
-                if (cx > 0 && X > 0) { fl[0] = lx[c - 1]; vl[0] = (float)(ux[c - 1] * cour); }
-                if (cx < W - 1 && X < a.nx - 1) { fl[1] = lx[c]; vl[1] = (float)(ux[c] * cour); }
-                if (cy > 0 && Y > 0) { fl[2] = ly[c - a.nx]; vl[2] = (float)(uy[c - a.nx] * cour); }
-                if (cy < W - 1 && Y < a.ny - 1) { fl[3] = ly[c]; vl[3] = (float)(uy[c] * cour); }
-                if (zw > 0 && Z > 0) { fl[4] = lz[c - nxy]; vl[4] = (float)(uz[c - nxy] * cour); }
-                if (zw < W - 1 && Z < a.nz - 1) { fl[5] = lz[c]; vl[5] = (float)(uz[c] * cour); }
-                if (a.node && a.node[c] == COARSE_RESERVOIR) sink |= 1u << k;
-            }
-            double out = 0.0, lam = 0.0;
-#pragma unroll
-            for (int ax = 0; ax < 3; ++ax) {
-                lam += (double)fl[2 * ax] + (double)fl[2 * ax + 1];
-                out += (vl[2 * ax] < 0.f ? -(double)vl[2 * ax] : 0.0) + (vl[2 * ax + 1] > 0.f ? (double)vl[2 * ax + 1] : 0.0);
-            }
-            c0[k] = (float)(1.0 - lam - out);
-            cxm[k] = fl[0] + (vl[0] > 0.f ? vl[0] : 0.f);
-            cxp[k] = fl[1] + (vl[1] < 0.f ? -vl[1] : 0.f);
-            cym[k] = fl[2] + (vl[2] > 0.f ? vl[2] : 0.f);
-            cyp[k] = fl[3] + (vl[3] < 0.f ? -vl[3] : 0.f);
-            czm[k] = fl[4] + (vl[4] > 0.f ? vl[4] : 0.f);
-            czp[k] = fl[5] + (vl[5] < 0.f ? -vl[5] : 0.f);
-            Gs[k] = (live && i < W3 && cx == R && cy == R && zw == R) ? 1.0f : 0.0f;
-        }
-        auto substep = [&](float *buf) {
-            // (raising the wave priority after the barrier, as flat_line
-            // does, measured 6 % slower here)
-#pragma unroll
-            for (int qd = 0; qd < RUN / 4; ++qd)
-                *(float4 *)(buf + own + 4 * qd) = make_float4(Gs[4 * qd], Gs[4 * qd + 1], Gs[4 * qd + 2], Gs[4 * qd + 3]);
-            __syncthreads();
-            float zlo, zhi;
-            float v0[RUN], v1[RUN];
-            read_x_runs<RUN, W>(buf, own, Gs, v0, v1, zlo, zhi);
-            float acc2[RUN];
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) acc2[k] = __builtin_fmaf(cxm[k], v0[k], c0[k] * Gs[k]);
-            read_run<RUN, -W2>(buf, own, v0);
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) acc2[k] = __builtin_fmaf(cxp[k], v1[k], acc2[k]);
-            read_run<RUN, W2>(buf, own, v1);
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) acc2[k] = __builtin_fmaf(cym[k], v0[k], acc2[k]);
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) acc2[k] = __builtin_fmaf(cyp[k], v1[k], acc2[k]);
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) {
-                float v = __builtin_fmaf(czm[k], k > 0 ? Gs[k - 1] : zlo, acc2[k]);
-                v = __builtin_fmaf(czp[k], k < RUN - 1 ? Gs[k + 1] : zhi, v);
-                acc2[k] = v;
-            }
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) Gs[k] = (sink >> k) & 1u ? 0.0f : acc2[k];
-        };
-        int step = 0;
-        for (; step + 1 < a.n_sub; step += 2) {
-            substep(xg);
-            substep(xg + LPW * XLEN);
-        }
-        if (step < a.n_sub) substep(xg);
-        // mass: per thread in cell order, xor butterfly per wave, the
-        // window's waves in order
-        double ms = 0.0;
-        if (act) {
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) ms += (double)Gs[k];
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) ms += __shfl_xor(ms, off, 64);
-        __syncthreads();                                       // every exchange read is done
-        if ((t & 63) == 0) red[t >> 6] = ms;
-        if (a.G && live) {
-            // the kernel in (z, y, x) window order into the run region of
-            // the second buffer (rewritten by every sub-step before a read)
-            float *stage = xg + LPW * XLEN + PAD;
-#pragma unroll
-            for (int k = 0; k < RUN; ++k) {
-                const int i = s0v + k;
-                const int colk = i / W, zw = i - colk * W;
-                if (i < W3) stage[(zw * W + colk / W) * W + colk % W] = Gs[k];
-            }
-        }
-        __syncthreads();
-        if (tg == 0 && live && a.mass) {
-            double m;
-            if constexpr (SG == 256) m = ((red[0] + red[1]) + red[2]) + red[3];
-            else if constexpr (SG == 128) m = red[2 * g] + red[2 * g + 1];
-            else m = red[g];
-            a.mass[q] = m;
-        }
-        if (a.G && live) {
-            const float *stage = xg + LPW * XLEN + PAD;
-            float *go = (float *)a.G + q * (int64_t)W3;
-            for (int w = tg; w < W3; w += SG) go[w] = stage[w];
-        }
-    }
-}
-
-template <int R>
-static hipError_t launch_flow_flat_r(const FlowArgs &a, hipStream_t st)
-{
-    const int64_t groups = (a.n_src + Flat<R>::LPW - 1) / Flat<R>::LPW;
-    const int64_t nblk = groups < 65536 * 16 ? groups : 65536 * 16;
-    if (nblk <= 0) return hipSuccess;
-    hipLaunchKernelGGL((flat_flow_kernel<R>), dim3((unsigned)nblk), dim3(FLAT_NT), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_flow_flat(int r, const FlowArgs &a, hipStream_t st)
-{
-    switch (r) {
-    case 4: return launch_flow_flat_r<4>(a, st);
-    case 5: return launch_flow_flat_r<5>(a, st);
-    case 6: return launch_flow_flat_r<6>(a, st);
-    case 7: return launch_flow_flat_r<7>(a, st);
-    case 8: return launch_flow_flat_r<8>(a, st);
-    default: return hipErrorInvalidValue;
-    }
 }
 
 template <int R, bool LAB>
