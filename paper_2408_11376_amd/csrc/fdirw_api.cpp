@@ -268,16 +268,31 @@ static int step_det(const fdirw_domain *d, const fdirw_opts *o, LineArgs a, DevC
     return FDIRW_OK;
 }
 
-// The flat-layout fused kernel (fdirw_flat.hip) serves FP32 steps with
-// r = 4..8; the environment variable FDIRW_FUSED_LAYOUT=segments selects the
-// segment-layout kernel instead (same kernels, for comparison).
-bool use_flat_layout(int prec, int r)
+// The flat layout (fdirw_flat.hip, fdirw_flatwin.hip) serves r = 4..8 with an
+// FP32 state; the environment variable FDIRW_FUSED_LAYOUT=segments selects the
+// segment-layout kernels instead (same kernels, for comparison).
+static bool flat_radius(int r)
 {
     static const bool segments = [] {
         const char *v = std::getenv("FDIRW_FUSED_LAYOUT");
         return v && std::strcmp(v, "segments") == 0;
     }();
-    return !segments && prec == FDIRW_FP32 && r >= 4 && r <= 8;
+    return !segments && r >= 4 && r <= 8;
+}
+
+bool use_flat_layout(int prec, int r) { return prec == FDIRW_FP32 && flat_radius(r); }
+
+// A segment-layout workgroup puts 10 waves on one window where a flat one has
+// 4 for one to four of them, so it is the faster one until the flat
+// workgroups fill the 256 CUs about one and a half times.  Measured (us per
+// call, segments / flat; 200, 113, 50 sub-steps): r = 8, 256 sources 192 /
+// 247, 384 304 / 261; r = 6, 512 137 / 176, 768 177 / 190, 1024 244 / 198; r =
+// 4, 1024 94 / 96, 1536 103 / 101, 4096 145 / 129.
+bool use_flat_window(int prec, int r, int64_t n_src)
+{
+    const bool mode = prec == FDIRW_FP32 || prec == FDIRW_FP16_BANK || prec == FDIRW_BF16_BANK;
+    const int per = flat_lines_per_group(r);
+    return mode && flat_radius(r) && n_src > (per > 1 ? 384 * per : 256);
 }
 
 int step_one(const fdirw_domain *d, const fdirw_opts *o, const double *c_in, double *c_out,

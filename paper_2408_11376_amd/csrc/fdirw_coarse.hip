@@ -11,6 +11,7 @@
 //   FDiRW      C' = P C (row form: 2K+1 threads per node, one per z offset)
 //   remapping  c'(i) = C'(node of i); cells outside every group keep c(i)
 #include "fdirw_device.h"
+#include "fdirw_host.h"
 #include "fdirw_launch.h"
 
 namespace fdirw {
@@ -804,6 +805,7 @@ static hipError_t launch_cw_m(int r, const CoarseGenArgs &a, hipStream_t st)
 
 hipError_t launch_coarse_window(int fp64, int sink, int r, const CoarseGenArgs &a, hipStream_t st)
 {
+    if (!fp64 && use_flat_window(M_FP32, r, a.n)) return launch_coarse_flat(sink, r, a, st);
     if (sink) return fp64 ? launch_cw_m<M_FP64, true>(r, a, st) : launch_cw_m<M_FP32, true>(r, a, st);
     return fp64 ? launch_cw_m<M_FP64, false>(r, a, st) : launch_cw_m<M_FP32, false>(r, a, st);
 }

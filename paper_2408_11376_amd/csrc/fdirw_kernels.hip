@@ -13,6 +13,7 @@
 // source of the line can reach is flushed with one FP64 atomic per window
 // column, i.e. W^2 atomics per source instead of W^3.
 #include "fdirw_device.h"
+#include "fdirw_host.h"
 #include "fdirw_launch.h"
 
 namespace fdirw {
@@ -704,6 +705,7 @@ hipError_t launch_line_labels(int mode, int r, const LineArgs &a, hipStream_t st
 
 hipError_t launch_window(int mode, int r, const WindowArgs &a, hipStream_t st)
 {
+    if (use_flat_window(mode, r, a.n_src)) return launch_window_flat(mode, r, a, st);
     switch (mode) {
     case M_FP64: return launch_window_m<M_FP64>(r, a, st);
     case M_FP32: return launch_window_m<M_FP32>(r, a, st);

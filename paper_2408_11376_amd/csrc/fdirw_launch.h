@@ -155,6 +155,10 @@ hipError_t launch_line(int mode, int r, const LineArgs &a, hipStream_t st);
 hipError_t launch_line_flat(int mode, int r, const LineArgs &a, hipStream_t st);
 hipError_t launch_line_flat_labels(int mode, int r, const LineArgs &a, hipStream_t st);
 hipError_t launch_window(int mode, int r, const WindowArgs &a, hipStream_t st);
+// The same and launch_coarse_window (FP32) in the flat layout: FP32 and the
+// 16-bit bank modes, r = 4..8; hipErrorInvalidValue otherwise.
+hipError_t launch_window_flat(int mode, int r, const WindowArgs &a, hipStream_t st);
+hipError_t launch_coarse_flat(int sink, int r, const CoarseGenArgs &a, hipStream_t st);
 hipError_t launch_bank_apply(int prec, int r, const BankArgs &a, hipStream_t st);
 int64_t bank_chat_elems(int nx, int ny, int nz, int r);
 hipError_t launch_bank_gather(int prec, int r, const BankArgs &a, hipStream_t st);   // a.chat given
