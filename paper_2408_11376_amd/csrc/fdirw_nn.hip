@@ -24,6 +24,8 @@
 
 #include "fdirw_launch.h"
 
+#include <type_traits>
+
 namespace fdirw {
 namespace nn {
 
@@ -378,12 +380,39 @@ __global__ void silu_bwd_kernel(const float *__restrict__ dh, const float *__res
 
 // dW[tap][co][ci] = sum over output positions p of dZ[co][p] H[ci][p + off(tap)],
 // as MFMA GEMMs with M = co, N = ci, K = 32 padded slab positions.  Both
-// operands are staged channel-first in LDS; H is also stored shifted by one
-// element so that every tap's operand starts at an even element and is read
-// with 32-bit loads.  Each workgroup accumulates its slabs in registers and
-// writes one partial; db[co] = sum of dZ is accumulated alongside.
+// operands are staged channel-first in LDS.  Wave w takes the three x taps of
+// tap pair (dz, dy) = (w / 3, w % 3): their operands start s, s + 1 and s + 2
+// elements into the same 16-byte chunks (s fixed by the pair, so known at
+// compile time), which are read once and shifted in registers.  Each workgroup
+// accumulates its slabs in registers and writes one partial; db[co] = sum of
+// dZ is accumulated alongside.
+// Bound by the LDS accesses of the staging and of the operands.  Rows are an
+// odd number of chunks apart, so the 16 rows of an operand read meet distinct
+// banks, and the next slab's global loads are in flight during the products.
+// 128 windows, 16 -> 16 channels: 28.6 us; 184 us with four waves that read
+// every tap's operand in 32-bit pieces from rows 32 banks apart (8-way
+// conflicts) and a second copy of H shifted by one element.
+constexpr int WG_NT = 9 * 64;
+
+// Elements t .. t + 7 of the 24 in w (bf16 pairs), t known at compile time.
+template <int T> __device__ __forceinline__ bf16x8 shifted8(const unsigned (&w)[12])
+{
+    unsigned o[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if constexpr (T % 2 == 0) o[j] = w[T / 2 + j];
+        else o[j] = __builtin_amdgcn_alignbit(w[T / 2 + j + 1], w[T / 2 + j], 16);
+    }
+    bf16x8 r;
+    __builtin_memcpy(&r, o, 16);
+    return r;
+}
+
+// The channels of one position.
+template <int C> struct Chan { bf16x8 v[C / 8]; };
+
 template <int CI, int COP>
-__global__ void __launch_bounds__(NTHR)
+__global__ void __launch_bounds__(WG_NT)
 wgrad_kernel(NnWgradArgs a)
 {
     constexpr int NPOS = TZ * P2;                            // 1083 output positions
@@ -392,112 +421,137 @@ wgrad_kernel(NnWgradArgs a)
     // Output position p (padded plane coordinates) reads input element
     // p + P2 + (dz - 1) P2 + (dy - 1) P + (dx - 1); the staged copy starts FRONT
     // elements late so that this index is p + dz P2 + dy P + dx >= 0, and ends
-    // past the highest element read, KP - 1 + 2 P2 + 2 P + 2.
+    // past the last chunk read
     constexpr int FRONT = P + 1;
-    constexpr int HLEN = (KP + 2 * P2 + 2 * P + 2 + 7) / 8 * 8;
-    __shared__ __align__(16) __bf16 hs[2][CI][HLEN];
-    __shared__ __align__(16) __bf16 ds[16][KP];
+    constexpr int OMAX = 2 * P2 + 2 * P;
+    constexpr int HCH = ((KP / 8 - 1) + OMAX / 8 + 3) | 1;   // chunks of a row of hs (odd)
+    constexpr int DCH = (KP / 8) | 1;                        // chunks of a row of ds (odd)
+    constexpr int HLEN = 8 * HCH, DLEN = 8 * DCH;
+    __shared__ __align__(16) __bf16 hs[CI][HLEN];
+    __shared__ __align__(16) __bf16 ds[16][DLEN];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane % 16, kb = lane / 16;
-    constexpr int TPW = 7;                                   // taps per wave: wave + 4 i
-    floatx4 acc[TPW];
+    floatx4 acc[3];
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) acc[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int i = 0; i < 3; ++i) acc[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
     float bsum = 0.0f;
     const __bf16 *hbase = reinterpret_cast<const __bf16 *>(a.h);
     const __bf16 *dbase = reinterpret_cast<const __bf16 *>(a.dz);
 
-    for (int slab_id = blockIdx.x; slab_id < a.n_slab; slab_id += gridDim.x) {
+    // a thread stages the element pairs (2 q, 2 q + 1), q = t, t + WG_NT, ...
+    constexpr int HQ = (HLEN / 2 + WG_NT - 1) / WG_NT, DQ = (DLEN / 2 + WG_NT - 1) / WG_NT;
+    Chan<CI> hv[HQ][2];
+    Chan<COP> dv[DQ][2];
+    auto fetch = [&](int slab_id) {
         const int b = slab_id / NSLAB;
-        const int z0 = (slab_id % NSLAB) * TZ;
+        const int z0 = (slab_id - b * NSLAB) * TZ;
         const int tz = W - z0 < TZ ? W - z0 : TZ;
         const __bf16 *hin = hbase + (int64_t)b * V * CI;
         const __bf16 *din = dbase + (int64_t)b * V * COP;
-        __syncthreads();                                     // previous slab fully consumed
-        for (int j = threadIdx.x; j < HLEN; j += NTHR) {
-            const int e = j - FRONT;
-            const int px = e % P, py = (e / P) % P, pz = e / P2;
-            const int x = px - 1, y = py - 1, z = z0 + pz - 1;
-            const bool in = e >= 0 && e < NIN && x >= 0 && x < W && y >= 0 && y < W && z >= 0 && z < W;
-            __bf16 v[CI];
-            if (in) {
-                const bf16x8 *src = reinterpret_cast<const bf16x8 *>(hin + (int64_t)((z * W + y) * W + x) * CI);
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));                          // positions recomputed per slab, not kept
+#pragma unroll
+        for (int i = 0; i < HQ; ++i)
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int e = 2 * (t + i * WG_NT) + k - FRONT;
+                const int px = e % P, py = (e / P) % P, pz = e / P2;
+                const int x = px - 1, y = py - 1, z = z0 + pz - 1;
+                const bool in = e >= 0 && e < NIN && x >= 0 && x < W && y >= 0 && y < W && z >= 0 && z < W;
+                const bf16x8 *src = reinterpret_cast<const bf16x8 *>(hin + (in ? (z * W + y) * W + x : 0) * CI);
 #pragma unroll
                 for (int j = 0; j < CI / 8; ++j) {
-                    const bf16x8 t = src[j];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) v[8 * j + i] = t[i];
+                    const bf16x8 v = src[j];
+                    hv[i][k].v[j] = in ? v : zero8();
                 }
-            } else {
-#pragma unroll
-                for (int c = 0; c < CI; ++c) v[c] = (__bf16)0.0f;
             }
 #pragma unroll
-            for (int c = 0; c < CI; ++c) {
-                hs[0][c][j] = v[c];
-                if (j > 0) hs[1][c][j - 1] = v[c];
-            }
-        }
-        if (threadIdx.x < CI) hs[1][threadIdx.x][HLEN - 1] = (__bf16)0.0f;
-        for (int e = threadIdx.x; e < KP; e += NTHR) {
-            const int px = e % P, py = (e / P) % P, pz = e / P2;
-            const int x = px - 1, y = py - 1, z = z0 + pz;
-            const bool in = e < NPOS && pz < tz && x >= 0 && x < W && y >= 0 && y < W;
-            __bf16 v[16];
+        for (int i = 0; i < DQ; ++i)
 #pragma unroll
-            for (int c = 0; c < 16; ++c) v[c] = (__bf16)0.0f;
-            if (in) {
-                const bf16x8 *src = reinterpret_cast<const bf16x8 *>(din + (int64_t)((z * W + y) * W + x) * COP);
+            for (int k = 0; k < 2; ++k) {
+                const int e = 2 * (t + i * WG_NT) + k;
+                const int px = e % P, py = (e / P) % P, pz = e / P2;
+                const int x = px - 1, y = py - 1, z = z0 + pz;
+                const bool in = e < NPOS && pz < tz && x >= 0 && x < W && y >= 0 && y < W;
+                const bf16x8 *src = reinterpret_cast<const bf16x8 *>(din + (in ? (z * W + y) * W + x : 0) * COP);
 #pragma unroll
                 for (int j = 0; j < COP / 8; ++j) {
-                    const bf16x8 t = src[j];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) v[8 * j + i] = t[i];
+                    const bf16x8 v = src[j];
+                    dv[i][k].v[j] = in ? v : zero8();
                 }
             }
-#pragma unroll
-            for (int c = 0; c < 16; ++c) ds[c][e] = c < a.co_n ? v[c] : (__bf16)0.0f;
-        }
-        __syncthreads();
-
-        for (int p0 = 0; p0 < KP; p0 += 32) {
-            const bf16x8 av = *reinterpret_cast<const bf16x8 *>(&ds[m][p0 + 8 * kb]);
-            if (wave == 0) {
+    };
+    auto products = [&](auto pair) {
+        constexpr int DZ = decltype(pair)::value / 3, DY = decltype(pair)::value % 3;
+        constexpr int O = DZ * P2 + DY * P, S = O % 8;
+        const bf16x8 *dr = reinterpret_cast<const bf16x8 *>(ds[m]) + kb;
+        const bf16x8 *hr = reinterpret_cast<const bf16x8 *>(hs[m % CI]) + kb + O / 8;
+#pragma unroll 2
+        for (int p0 = 0; p0 < KP / 8; p0 += 4) {
+            const bf16x8 av = dr[p0];
+            if constexpr (decltype(pair)::value == 0) {
 #pragma unroll
                 for (int i = 0; i < 8; ++i) bsum += (float)av[i];
             }
+            unsigned w[12] = {};
+            __builtin_memcpy(w, &hr[p0], 16);
+            __builtin_memcpy(w + 4, &hr[p0 + 1], 16);
+            if constexpr (S + 2 > 8) __builtin_memcpy(w + 8, &hr[p0 + 2], 16);
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, shifted8<S>(w), acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, shifted8<S + 1>(w), acc[1], 0, 0, 0);
+            acc[2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, shifted8<S + 2>(w), acc[2], 0, 0, 0);
+        }
+    };
+
+    if ((int)blockIdx.x < a.n_slab) fetch(blockIdx.x);
+    for (int slab_id = blockIdx.x; slab_id < a.n_slab; slab_id += gridDim.x) {
+        __syncthreads();                                     // previous slab fully consumed
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 #pragma unroll
-            for (int i = 0; i < TPW; ++i) {
-                const int tap = wave + 4 * i;
-                if (tap > 26) break;
-                const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-                const int e = p0 + 8 * kb + dz * P2 + dy * P + dx;
-                bf16x8 bv;
-                if (m < CI) {
-                    const int sh = e & 1;
-                    const unsigned *src = reinterpret_cast<const unsigned *>(&hs[sh][m][e - sh]);
+        for (int i = 0; i < HQ; ++i) {
+            const int q = threadIdx.x + i * WG_NT;
+            if (q < HLEN / 2) {
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const unsigned u = src[j];
-                        bv[2 * j] = __builtin_bit_cast(__bf16, (unsigned short)(u & 0xffffu));
-                        bv[2 * j + 1] = __builtin_bit_cast(__bf16, (unsigned short)(u >> 16));
-                    }
-                } else {
-                    bv = zero8();
-                }
-                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[i], 0, 0, 0);
+                for (int c = 0; c < CI; ++c)
+                    *reinterpret_cast<bf16x2 *>(&hs[c][2 * q]) =
+                        bf16x2{hv[i][0].v[c / 8][c % 8], hv[i][1].v[c / 8][c % 8]};
             }
+        }
+#pragma unroll
+        for (int i = 0; i < DQ; ++i) {
+            const int q = threadIdx.x + i * WG_NT;
+            if (q < DLEN / 2) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) {
+                    bf16x2 o = {(__bf16)0.0f, (__bf16)0.0f};
+                    if constexpr (COP == 16) o = bf16x2{dv[i][0].v[c / 8][c % 8], dv[i][1].v[c / 8][c % 8]};
+                    else if (c < COP) o = bf16x2{dv[i][0].v[0][c % 8], dv[i][1].v[0][c % 8]};
+                    if (c >= a.co_n) o = bf16x2{(__bf16)0.0f, (__bf16)0.0f};
+                    *reinterpret_cast<bf16x2 *>(&ds[c][2 * q]) = o;
+                }
+            }
+        }
+        __syncthreads();
+        const int nxt = slab_id + gridDim.x;
+        if (nxt < a.n_slab) fetch(nxt);
+        switch (wave) {
+        case 0: products(std::integral_constant<int, 0>()); break;
+        case 1: products(std::integral_constant<int, 1>()); break;
+        case 2: products(std::integral_constant<int, 2>()); break;
+        case 3: products(std::integral_constant<int, 3>()); break;
+        case 4: products(std::integral_constant<int, 4>()); break;
+        case 5: products(std::integral_constant<int, 5>()); break;
+        case 6: products(std::integral_constant<int, 6>()); break;
+        case 7: products(std::integral_constant<int, 7>()); break;
+        default: products(std::integral_constant<int, 8>()); break;
         }
     }
     // acc[i][j]: co = 4 kb + j, ci = m
     float *part = a.part + (size_t)blockIdx.x * 27 * 256;
 #pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-        const int tap = wave + 4 * i;
-        if (tap > 26) break;
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[tap * 256 + (4 * kb + j) * 16 + m] = acc[i][j];
-    }
+        for (int j = 0; j < 4; ++j) part[(3 * wave + i) * 256 + (4 * kb + j) * 16 + m] = acc[i][j];
     if (wave == 0) {
         bsum += __shfl_xor(bsum, 16, 64);
         bsum += __shfl_xor(bsum, 32, 64);
@@ -505,25 +559,40 @@ wgrad_kernel(NnWgradArgs a)
     }
 }
 
-// gw[(co ci_n + ci) 27 + tap] += sum over g of part[g][tap][co][ci]; gb[co] likewise.
-__global__ void wgrad_reduce_kernel(const float *__restrict__ part, const float *__restrict__ bpart, int grid,
-                                    int co_n, int ci_n, float *__restrict__ gw, float *__restrict__ gb)
+// gw[(co ci_n + ci) 27 + tap] += sum over g of part[g][tap][co][ci]; gb[co]
+// likewise.  A workgroup takes 64 outputs: its 16 waves each a run of the
+// partials in order, then the 16 sums in order.  (One thread per output
+// walking all partials took 120 us for 512 of them: 27 workgroups, one load in
+// flight per thread; this takes 5 us for 256.)
+constexpr int RED_NT = 1024;
+
+__global__ void __launch_bounds__(RED_NT)
+wgrad_reduce_kernel(const float *__restrict__ part, const float *__restrict__ bpart, int grid,
+                    int co_n, int ci_n, float *__restrict__ gw, float *__restrict__ gb)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < 27 * 256) {
+    __shared__ float sums[RED_NT / 64][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
+    const bool bias = i >= 27 * 256;                         // uniform per block
+    const int per = (grid + RED_NT / 64 - 1) / (RED_NT / 64);
+    const int g0 = wave * per, g1 = g0 + per < grid ? g0 + per : grid;
+    const float *src = bias ? bpart + (i - 27 * 256) : part + i;
+    const size_t step = bias ? 16 : 27 * 256;
+    float s = 0.0f;
+    if (!bias || i < 27 * 256 + 16) {
+#pragma unroll 8
+        for (int g = g0; g < g1; ++g) s += src[(size_t)g * step];
+    }
+    sums[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0) return;
+#pragma unroll
+    for (int w = 1; w < RED_NT / 64; ++w) s += sums[w][lane];
+    if (!bias) {
         const int tap = i / 256, co = (i / 16) % 16, ci = i % 16;
-        if (co < co_n && ci < ci_n) {
-            float s = 0.0f;
-            for (int g = 0; g < grid; ++g) s += part[(size_t)g * 27 * 256 + i];
-            gw[((size_t)co * ci_n + ci) * 27 + tap] += s;
-        }
-    } else if (i < 27 * 256 + 16) {
-        const int co = i - 27 * 256;
-        if (co < co_n) {
-            float s = 0.0f;
-            for (int g = 0; g < grid; ++g) s += bpart[(size_t)g * 16 + co];
-            gb[co] += s;
-        }
+        if (co < co_n && ci < ci_n) gw[((size_t)co * ci_n + ci) * 27 + tap] += s;
+    } else if (i - 27 * 256 < co_n) {
+        gb[i - 27 * 256] += s;
     }
 }
 
@@ -1150,9 +1219,9 @@ hipError_t nn_launch_wgrad(int CI, int COP, const NnWgradArgs &a, int grid, hipS
 {
     if (grid <= 0) return hipSuccess;
     const dim3 g((unsigned)grid);
-    if (CI == 8 && COP == 16) hipLaunchKernelGGL((nn::wgrad_kernel<8, 16>), g, dim3(nn::NTHR), 0, st, a);
-    else if (CI == 16 && COP == 16) hipLaunchKernelGGL((nn::wgrad_kernel<16, 16>), g, dim3(nn::NTHR), 0, st, a);
-    else if (CI == 16 && COP == 8) hipLaunchKernelGGL((nn::wgrad_kernel<16, 8>), g, dim3(nn::NTHR), 0, st, a);
+    if (CI == 8 && COP == 16) hipLaunchKernelGGL((nn::wgrad_kernel<8, 16>), g, dim3(nn::WG_NT), 0, st, a);
+    else if (CI == 16 && COP == 16) hipLaunchKernelGGL((nn::wgrad_kernel<16, 16>), g, dim3(nn::WG_NT), 0, st, a);
+    else if (CI == 16 && COP == 8) hipLaunchKernelGGL((nn::wgrad_kernel<16, 8>), g, dim3(nn::WG_NT), 0, st, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -1160,7 +1229,7 @@ hipError_t nn_launch_wgrad(int CI, int COP, const NnWgradArgs &a, int grid, hipS
 hipError_t nn_launch_wgrad_reduce(const float *part, const float *bpart, int grid, int co_n, int ci_n, float *gw,
                                   float *gb, hipStream_t st)
 {
-    hipLaunchKernelGGL(nn::wgrad_reduce_kernel, dim3((27 * 256 + 16 + 255) / 256), dim3(256), 0, st, part, bpart,
+    hipLaunchKernelGGL(nn::wgrad_reduce_kernel, dim3(27 * 256 / 64 + 1), dim3(nn::RED_NT), 0, st, part, bpart,
                        grid, co_n, ci_n, gw, gb);
     return hipGetLastError();
 }

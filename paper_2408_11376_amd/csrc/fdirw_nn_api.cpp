@@ -22,7 +22,7 @@ static const int kChan[6] = {3, 16, 16, 16, 16, 1};
 static const int kStoreCI[5] = {8, 16, 16, 16, 16};     // input channels as stored (BF16 vectors of 8)
 static const int kMbTrain = 128;                          // windows per training micro-batch
 static const int kMbInfer = 4096;                         // windows per inference chunk
-static const int kWgradGrid = 512;
+static const int kWgradGrid = 256;                        // one weight-gradient workgroup per CU (95 KB of LDS)
 
 static int64_t layer_w_off(int l)
 {
