@@ -391,11 +391,10 @@ struct NnConvArgs {
     const uint16_t *in;       // [B][V][CI] BF16 channel-last
     const uint16_t *wpack;    // packed B operands
     const float *bias;        // [16] (modes 0, 1)
-    int mode;                 // 0 hidden layer, 1 last layer, 2 input gradient
-    float *zpre;              // mode 0: [B][V][16] pre-activation, or null
-    uint16_t *hout;           // mode 0: [B][V][16] SiLU output (BF16)
+    int mode;                 // 0 hidden layer, 1 last layer, 2 input gradient through the SiLU below
+    float *zpre;              // [B][V][16] pre-activation: mode 0 written (or null), mode 2 read
+    uint16_t *hout;           // [B][V][16] BF16: mode 0 SiLU output, mode 2 dh * SiLU'(zpre); not in
     float *z5;                // mode 1: [B][V]
-    float *dh;                // mode 2: [B][V][16]
 };
 
 struct NnLossArgs {
@@ -448,7 +447,6 @@ hipError_t nn_launch_pack(const float *w, int co_n, int ci_n, int CI, int flip, 
 int nn_pack_chunks(int CI);
 hipError_t nn_launch_conv(int CI, const NnConvArgs &a, int batch, hipStream_t st);
 hipError_t nn_launch_loss(const NnLossArgs &a, int batch, hipStream_t st);
-hipError_t nn_launch_silu_bwd(const float *dh, const float *zpre, uint16_t *dz, int64_t n, hipStream_t st);
 hipError_t nn_launch_wgrad(int CI, int COP, const NnWgradArgs &a, int grid, hipStream_t st);
 hipError_t nn_launch_wgrad_reduce(const float *part, const float *bpart, int grid, int co_n, int ci_n,
                                   float *gw, float *gb, hipStream_t st);

@@ -190,28 +190,48 @@ __global__ void pack_kernel(const float *__restrict__ w, int co_n, int ci_n, int
 // ----------------------------------------------------------------- conv
 
 // One workgroup: window blockIdx.x / NSLAB, output planes z0 .. z0 + TZ - 1.
+// The slab is staged in 8-channel halves, [half][cell], so that the 16 cells
+// of an operand read are 16 consecutive 16-byte vectors; every load of the
+// staging is in flight before the first is stored.  Mode 2 ends with the
+// SiLU derivative of the layer below (its input's gradient never exists in
+// FP32 in memory).  Bound by its HBM traffic (hidden layer, 16 channels: 128
+// B per voxel with the FP32 pre-activation) and the staging's latency: 52.6 us
+// per 256 windows, 16 -> 16 channels; 81 us with loads staged one at a time,
+// one tile at a time and two operand cells per bank, and the input gradient
+// then took 19 us more per 128 windows in a SiLU pass of its own.
 template <int CI>
 __global__ void __launch_bounds__(NTHR)
 conv_kernel(NnConvArgs a)
 {
     constexpr int NCH = nchunks(CI);
-    __shared__ __align__(16) __bf16 slab[(TZ + 2) * P2 * CI];
+    constexpr int NHALF = CI / 8;
+    constexpr int NCELL = (TZ + 2) * P2;
+    __shared__ __align__(16) __bf16 slab[NHALF * NCELL * 8];
     const int b = blockIdx.x / NSLAB;
     const int z0 = (blockIdx.x % NSLAB) * TZ;
     const int tz = W - z0 < TZ ? W - z0 : TZ;
     const __bf16 *in = reinterpret_cast<const __bf16 *>(a.in) + (int64_t)b * V * CI;
 
     // planes z0 - 1 .. z0 + TZ with a zero halo, 8 channels per 16-byte vector
-    constexpr int VPC = CI / 8;
-    constexpr int NCELL = (TZ + 2) * P2;
-    for (int e = threadIdx.x; e < NCELL * VPC; e += NTHR) {
-        const int cell = e / VPC, vv = e - cell * VPC;
-        const int px = cell % P, py = (cell / P) % P, pz = cell / P2;
-        const int x = px - 1, y = py - 1, z = z0 + pz - 1;
-        bf16x8 val = zero8();
-        if (x >= 0 && x < W && y >= 0 && y < W && z >= 0 && z < W)
-            val = *reinterpret_cast<const bf16x8 *>(in + (int64_t)((z * W + y) * W + x) * CI + vv * 8);
-        *reinterpret_cast<bf16x8 *>(slab + (size_t)cell * CI + vv * 8) = val;
+    constexpr int NV = (NCELL * NHALF + NTHR - 1) / NTHR;
+    {
+        bf16x8 st[NV];
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int e = threadIdx.x + i * NTHR;
+            const int cell = e / NHALF, vv = e - cell * NHALF;
+            const int px = cell % P, py = (cell / P) % P, pz = cell / P2;
+            const int x = px - 1, y = py - 1, z = z0 + pz - 1;
+            const bool ok = pz < TZ + 2 && x >= 0 && x < W && y >= 0 && y < W && z >= 0 && z < W;
+            const bf16x8 v = *reinterpret_cast<const bf16x8 *>(in + (ok ? (z * W + y) * W + x : 0) * CI + vv * 8);
+            st[i] = ok ? v : zero8();
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int e = threadIdx.x + i * NTHR;
+            const int cell = e / NHALF, vv = e - cell * NHALF;
+            if (e < NCELL * NHALF) *reinterpret_cast<bf16x8 *>(slab + (vv * NCELL + cell) * 8) = st[i];
+        }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int m = lane % 16, kb = lane / 16;
@@ -221,45 +241,64 @@ conv_kernel(NnConvArgs a)
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         wreg[c] = wp[c * 64 + lane];
-        int tap, ch0;
-        if (CI == 16) { tap = 2 * c + (kb >> 1); ch0 = 8 * (kb & 1); }
-        else          { tap = 4 * c + kb;        ch0 = 0; }
+        int tap, half;
+        if (CI == 16) { tap = 2 * c + (kb >> 1); half = kb & 1; }
+        else          { tap = 4 * c + kb;        half = 0; }
         if (tap > 26) tap = 26;                              // padding taps carry zero weights
         const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;
-        offs[c] = ((dz * P + dy) * P + dx) * CI + ch0;
+        offs[c] = (half * NCELL + (dz * P + dy) * P + dx) * 8;
     }
     __syncthreads();
 
     const int nvox = tz * W2;
     const int ntile = (nvox + 15) / 16;
-    for (int tile = wave; tile < ntile; tile += NTHR / 64) {
-        int t = tile * 16 + m;
-        if (t >= nvox) t = nvox - 1;                         // padding rows, results dropped
-        const int ox = t % W, oy = (t / W) % W, oz = t / W2;
-        const int base = ((oz * P + oy) * P + ox) * CI;
-        floatx4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    const float bias = a.mode == 0 ? a.bias[m] : a.mode == 1 ? a.bias[0] : 0.0f;
+    // two tiles at a time: two independent chains of products
+    for (int pair = wave; 2 * pair < ntile; pair += NTHR / 64) {
+        int base[2];
+        float zp[2][4];
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-            const bf16x8 av = *reinterpret_cast<const bf16x8 *>(slab + base + offs[c]);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, wreg[c], acc, 0, 0, 0);
-        }
-        // acc[j]: voxel row 4 kb + j of the tile, output channel m
+        for (int u = 0; u < 2; ++u) {
+            const int tile = 2 * pair + u;
+            int t = tile * 16 + m;
+            if (t >= nvox) t = nvox - 1;                     // padding rows, results dropped
+            const int ox = t % W, oy = (t / W) % W, oz = t / W2;
+            base[u] = ((oz * P + oy) * P + ox) * 8;
+            if (a.mode == 2) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int tt = tile * 16 + 4 * kb + j;
-            if (tt >= nvox) continue;
-            const int64_t v = (int64_t)b * V + z0 * W2 + tt;
-            const float val = acc[j];
-            if (a.mode == 0) {
-                const float zz = val + a.bias[m];
-                if (a.zpre) a.zpre[v * 16 + m] = zz;
-                reinterpret_cast<__bf16 *>(a.hout)[v * 16 + m] = (__bf16)silu_f(zz);
-            } else if (a.mode == 1) {
-                if (m == 0) a.z5[v] = val + a.bias[0];
-            } else {
-                a.dh[v * 16 + m] = val;
+                for (int j = 0; j < 4; ++j) {
+                    const int tt = tile * 16 + 4 * kb + j;
+                    zp[u][j] = a.zpre[((int64_t)b * V + z0 * W2 + (tt < nvox ? tt : 0)) * 16 + m];
+                }
             }
         }
+        floatx4 acc[2] = {floatx4{0.0f, 0.0f, 0.0f, 0.0f}, floatx4{0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+        for (int c = 0; c < NCH; ++c)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const bf16x8 av = *reinterpret_cast<const bf16x8 *>(slab + base[u] + offs[c]);
+                acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, wreg[c], acc[u], 0, 0, 0);
+            }
+        // acc[u][j]: voxel row 4 kb + j of the tile, output channel m
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int tt = (2 * pair + u) * 16 + 4 * kb + j;
+                if (tt >= nvox) continue;
+                const int64_t v = (int64_t)b * V + z0 * W2 + tt;
+                const float val = acc[u][j];
+                if (a.mode == 0) {
+                    const float zz = val + bias;
+                    if (a.zpre) a.zpre[v * 16 + m] = zz;
+                    reinterpret_cast<__bf16 *>(a.hout)[v * 16 + m] = (__bf16)silu_f(zz);
+                } else if (a.mode == 1) {
+                    if (m == 0) a.z5[v] = val + bias;
+                } else {
+                    reinterpret_cast<__bf16 *>(a.hout)[v * 16 + m] = (__bf16)(val * silu_grad_f(zp[u][j]));
+                }
+            }
     }
 }
 
@@ -283,16 +322,20 @@ __device__ __forceinline__ T block_reduce_sum(T x, T *red)
 // KL(q || G) and sum |q - G|, and d loss / d logits = (G - q) + G (sbar -
 // sign(q - G)), sbar = sum sign(q - G) G, times grad_scale, written as BF16
 // channel 0 of an 8-channel field.  The loss path evaluates G in FP64.
-__global__ void __launch_bounds__(NTHR)
+// One window per CU: 16 waves hide the latency of the FP64 exp and log (52 ->
+// 28 us per 256 windows against 4 waves).
+constexpr int LOSS_NT = 1024;
+
+__global__ void __launch_bounds__(LOSS_NT)
 softmax_loss_kernel(NnLossArgs a)
 {
-    __shared__ float redf[NTHR / 64];
-    __shared__ double redd[NTHR / 64];
+    __shared__ float redf[LOSS_NT / 64];
+    __shared__ double redd[LOSS_NT / 64];
     const int b = blockIdx.x;
     const float *z5 = a.z5 + (int64_t)b * V;
     const uint8_t *S = a.support + (int64_t)b * V;
     float mx = -INFINITY;
-    for (int v = threadIdx.x; v < V; v += NTHR)
+    for (int v = threadIdx.x; v < V; v += LOSS_NT)
         if (S[v]) mx = fmaxf(mx, a.prior[v] + z5[v]);
     {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -300,80 +343,87 @@ softmax_loss_kernel(NnLossArgs a)
         if (lane == 0) redf[wave] = mx;
         __syncthreads();
         mx = redf[0];
-        for (int w = 1; w < NTHR / 64; ++w) mx = fmaxf(mx, redf[w]);
+        for (int w = 1; w < LOSS_NT / 64; ++w) mx = fmaxf(mx, redf[w]);
     }
     float *G = a.G ? a.G + (int64_t)b * V : nullptr;
     if (a.logits)
-        for (int v = threadIdx.x; v < V; v += NTHR) a.logits[(int64_t)b * V + v] = a.prior[v] + z5[v];
+        for (int v = threadIdx.x; v < V; v += LOSS_NT) a.logits[(int64_t)b * V + v] = a.prior[v] + z5[v];
     if (!a.target) {
         double se = 0.0;
-        for (int v = threadIdx.x; v < V; v += NTHR)
+        for (int v = threadIdx.x; v < V; v += LOSS_NT)
             if (S[v]) se += (double)expf(a.prior[v] + z5[v] - mx);
-        se = block_reduce_sum(se, redd);
+        se = block_reduce_sum<double, LOSS_NT / 64>(se, redd);
         const float inv = (float)(1.0 / se);
         double ms = 0.0;
-        for (int v = threadIdx.x; v < V; v += NTHR) {
+        for (int v = threadIdx.x; v < V; v += LOSS_NT) {
             const float g = S[v] ? expf(a.prior[v] + z5[v] - mx) * inv : 0.0f;
             if (G) G[v] = g;
             ms += (double)g;
         }
-        ms = block_reduce_sum(ms, redd);
+        ms = block_reduce_sum<double, LOSS_NT / 64>(ms, redd);
         if (threadIdx.x == 0 && a.mass) a.mass[b] = ms;
         return;
     }
     const float *tg = a.target + (int64_t)b * V;
+    constexpr int NJ = (V + LOSS_NT - 1) / LOSS_NT;
+    double lg[NJ], g[NJ], qv[NJ];                            // a thread's cells: log G and G, q (support only)
+    unsigned sup = 0u;
     double se = 0.0, tm = 0.0;
-    for (int v = threadIdx.x; v < V; v += NTHR) {
-        if (S[v]) se += exp((double)(a.prior[v] + z5[v]) - (double)mx);
-        tm += (double)tg[v];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int v = threadIdx.x + j * LOSS_NT;
+        lg[j] = qv[j] = 0.0;
+        if (v >= V) continue;
+        if (S[v]) {
+            sup |= 1u << j;
+            lg[j] = (double)(a.prior[v] + z5[v]) - (double)mx;
+            se += exp(lg[j]);
+        }
+        qv[j] = (double)tg[v];
+        tm += qv[j];
     }
-    se = block_reduce_sum(se, redd);
-    tm = block_reduce_sum(tm, redd);
+    se = block_reduce_sum<double, LOSS_NT / 64>(se, redd);
+    tm = block_reduce_sum<double, LOSS_NT / 64>(tm, redd);
     const double lse = log(se), tinv = 1.0 / tm;
     double kl = 0.0, l1 = 0.0, sbar = 0.0;
-    for (int v = threadIdx.x; v < V; v += NTHR) {
-        if (!S[v]) continue;
-        const double lg = (double)(a.prior[v] + z5[v]) - (double)mx - lse;
-        const double g = exp(lg), qv = (double)tg[v] * tinv;
-        if (qv > 0.0) kl += qv * (log(qv) - lg);
-        l1 += fabs(qv - g);
-        sbar += (qv > g ? 1.0 : (qv < g ? -1.0 : 0.0)) * g;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        g[j] = 0.0;
+        if (!((sup >> j) & 1u)) continue;
+        lg[j] -= lse;
+        g[j] = exp(lg[j]);
+        qv[j] *= tinv;
+        if (qv[j] > 0.0) kl += qv[j] * (log(qv[j]) - lg[j]);
+        l1 += fabs(qv[j] - g[j]);
+        sbar += (qv[j] > g[j] ? 1.0 : (qv[j] < g[j] ? -1.0 : 0.0)) * g[j];
     }
-    kl = block_reduce_sum(kl, redd);
-    l1 = block_reduce_sum(l1, redd);
-    sbar = block_reduce_sum(sbar, redd);
+    kl = block_reduce_sum<double, LOSS_NT / 64>(kl, redd);
+    l1 = block_reduce_sum<double, LOSS_NT / 64>(l1, redd);
+    sbar = block_reduce_sum<double, LOSS_NT / 64>(sbar, redd);
     if (threadIdx.x == 0) {
         a.loss[2 * b] = kl;
         a.loss[2 * b + 1] = l1;
     }
     double ms = 0.0;
     __bf16 *d8 = reinterpret_cast<__bf16 *>(a.dlog8) + (int64_t)b * V * 8;
-    for (int v = threadIdx.x; v < V; v += NTHR) {
-        float dz = 0.0f, gv = 0.0f;
-        if (S[v]) {
-            const double g = exp((double)(a.prior[v] + z5[v]) - (double)mx - lse);
-            const double qv = (double)tg[v] * tinv;
-            const double sg = qv > g ? 1.0 : (qv < g ? -1.0 : 0.0);
-            dz = (float)(((g - qv) + g * (sbar - sg)) * (double)a.grad_scale);
-            gv = (float)g;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int v = threadIdx.x + j * LOSS_NT;
+        if (v >= V) continue;
+        float dz = 0.0f;
+        if ((sup >> j) & 1u) {
+            const double sg = qv[j] > g[j] ? 1.0 : (qv[j] < g[j] ? -1.0 : 0.0);
+            dz = (float)(((g[j] - qv[j]) + g[j] * (sbar - sg)) * (double)a.grad_scale);
         }
+        const float gv = (float)g[j];
         if (G) G[v] = gv;
         ms += (double)gv;
         bf16x8 o = zero8();
         o[0] = (__bf16)dz;
         *reinterpret_cast<bf16x8 *>(d8 + (int64_t)v * 8) = o;
     }
-    ms = block_reduce_sum(ms, redd);
+    ms = block_reduce_sum<double, LOSS_NT / 64>(ms, redd);
     if (threadIdx.x == 0 && a.mass) a.mass[b] = ms;
-}
-
-// dz = dh * SiLU'(zpre), rounded to BF16
-__global__ void silu_bwd_kernel(const float *__restrict__ dh, const float *__restrict__ zpre,
-                                uint16_t *__restrict__ dz, int64_t n)
-{
-    __bf16 *o = reinterpret_cast<__bf16 *>(dz);
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        o[i] = (__bf16)(dh[i] * silu_grad_f(zpre[i]));
 }
 
 // ----------------------------------------------------------------- weight gradient
@@ -1205,13 +1255,7 @@ hipError_t nn_launch_conv(int CI, const NnConvArgs &a, int batch, hipStream_t st
 hipError_t nn_launch_loss(const NnLossArgs &a, int batch, hipStream_t st)
 {
     if (batch <= 0) return hipSuccess;
-    hipLaunchKernelGGL(nn::softmax_loss_kernel, dim3(batch), dim3(nn::NTHR), 0, st, a);
-    return hipGetLastError();
-}
-
-hipError_t nn_launch_silu_bwd(const float *dh, const float *zpre, uint16_t *dz, int64_t n, hipStream_t st)
-{
-    hipLaunchKernelGGL(nn::silu_bwd_kernel, dim3(grid_1d(n, 256)), dim3(256), 0, st, dh, zpre, dz, n);
+    hipLaunchKernelGGL(nn::softmax_loss_kernel, dim3(batch), dim3(nn::LOSS_NT), 0, st, a);
     return hipGetLastError();
 }
 

@@ -20,7 +20,7 @@ namespace fdirw {
 
 static const int kChan[6] = {3, 16, 16, 16, 16, 1};
 static const int kStoreCI[5] = {8, 16, 16, 16, 16};     // input channels as stored (BF16 vectors of 8)
-static const int kMbTrain = 128;                          // windows per training micro-batch
+static const int kMbTrain = 256;                          // windows per training micro-batch (one FD target per CU)
 static const int kMbInfer = 4096;                         // windows per inference chunk
 static const int kWgradGrid = 256;                        // one weight-gradient workgroup per CU (95 KB of LDS)
 
@@ -35,7 +35,7 @@ static int64_t num_params() { return layer_w_off(5); }
 
 struct NnWork {
     int cap = 0;              // windows
-    Buf src, X, S, h[4], zpre[4], z5, G, mass, targ, tmass, loss, dlog8, dh, dz, part, bpart, l1, kmm;
+    Buf src, X, S, h[4], zpre[4], z5, G, mass, targ, tmass, loss, dlog8, dz[2], part, bpart, l1, kmm;
 };
 
 struct NnModel {
@@ -61,8 +61,8 @@ static void free_model(NnModel *m)
     for (Buf *b : {&m->theta, &m->grad, &m->m, &m->v, &m->prior}) free_buf(*b);
     for (int l = 0; l < 5; ++l) { free_buf(m->wp[l]); free_buf(m->wpf[l]); free_buf(m->wfu[l]); }
     NnWork &w = m->ws;
-    for (Buf *b : {&w.src, &w.X, &w.S, &w.z5, &w.G, &w.mass, &w.targ, &w.tmass, &w.loss, &w.dlog8, &w.dh, &w.dz,
-                   &w.part, &w.bpart, &w.l1, &w.kmm})
+    for (Buf *b : {&w.src, &w.X, &w.S, &w.z5, &w.G, &w.mass, &w.targ, &w.tmass, &w.loss, &w.dlog8, &w.dz[0],
+                   &w.dz[1], &w.part, &w.bpart, &w.l1, &w.kmm})
         free_buf(*b);
     for (int l = 0; l < 4; ++l) { free_buf(w.h[l]); free_buf(w.zpre[l]); }
 }
@@ -126,8 +126,8 @@ static int ensure_work(NnModel *m, int cap, bool train)
         }
         if ((rc = ensure(w.loss, (size_t)cap * 16))) return rc;
         if ((rc = ensure(w.dlog8, (size_t)cap * V * 8 * 2))) return rc;
-        if ((rc = ensure(w.dh, (size_t)cap * V * 16 * 4))) return rc;
-        if ((rc = ensure(w.dz, (size_t)cap * V * 16 * 2))) return rc;
+        for (int k = 0; k < 2; ++k)
+            if ((rc = ensure(w.dz[k], (size_t)cap * V * 16 * 2))) return rc;
         if ((rc = ensure(w.part, (size_t)kWgradGrid * 27 * 256 * 4))) return rc;
         if ((rc = ensure(w.bpart, (size_t)kWgradGrid * 16 * 4))) return rc;
     }
@@ -198,7 +198,7 @@ static int run_forward(NnModel *m, int n, bool train, hipStream_t st)
         a.in = in;
         a.wpack = (const uint16_t *)m->wp[l].p;
         a.bias = th + layer_b_off(l);
-        a.zpre = nullptr; a.hout = nullptr; a.z5 = nullptr; a.dh = nullptr;
+        a.zpre = nullptr; a.hout = nullptr; a.z5 = nullptr;
         if (l < 4) {
             a.mode = 0;
             uint16_t *out = (uint16_t *)(train ? w.h[l].p : w.h[l & 1].p);
@@ -223,7 +223,6 @@ static int run_backward(NnModel *m, int n, hipStream_t st)
     float *g = (float *)m->grad.p;
     const int nslab = n * nn_slabs_per_window();
     const int grid = nslab < kWgradGrid ? nslab : kWgradGrid;
-    const int64_t nel = (int64_t)n * NN_V * 16;
     hipError_t e = hipSuccess;
     const uint16_t *dz = (const uint16_t *)w.dlog8.p;     // gradient at the output of layer l
     int cop = 8;
@@ -241,19 +240,18 @@ static int run_backward(NnModel *m, int n, hipStream_t st)
             e = nn_launch_wgrad_reduce(wa.part, wa.bpart, grid, kChan[l + 1], kChan[l], g + layer_w_off(l),
                                        g + layer_b_off(l), st);
         if (l == 0 || e != hipSuccess) break;
-        // gradient at the input of layer l = output of layer l - 1 (FP32), then
-        // through that layer's SiLU into BF16
+        // gradient at the input of layer l = output of layer l - 1, through
+        // that layer's SiLU
         NnConvArgs ca;
         ca.in = dz;
         ca.wpack = (const uint16_t *)m->wpf[l].p;
         ca.bias = nullptr;
         ca.mode = 2;
-        ca.zpre = nullptr; ca.hout = nullptr; ca.z5 = nullptr;
-        ca.dh = (float *)w.dh.p;
+        ca.z5 = nullptr;
+        ca.zpre = (float *)w.zpre[l - 1].p;
+        ca.hout = (uint16_t *)w.dz[l & 1].p;
         e = nn_launch_conv(cop, ca, n, st);
-        if (e == hipSuccess) e = nn_launch_silu_bwd((const float *)w.dh.p, (const float *)w.zpre[l - 1].p,
-                                                    (uint16_t *)w.dz.p, nel, st);
-        dz = (const uint16_t *)w.dz.p;
+        dz = ca.hout;
         cop = 16;
     }
     return e == hipSuccess ? FDIRW_OK : hip_fail(e, "backward launch");
@@ -627,7 +625,7 @@ int fdirw_nn_backward(void *nn, const fdirw_domain *d, const int64_t *src, int64
     Geometry geo;
     const void *lam32 = nullptr;
     if ((rc = coef_buffers(d, FDIRW_FP32, st, dc, &geo, &lam32))) return rc;
-    if ((rc = ensure_work(m, kMbTrain, true))) return rc;
+    if ((rc = ensure_work(m, n_src < kMbTrain ? (int)n_src : kMbTrain, true))) return rc;
     if ((rc = pack_weights(m, st, false))) return rc;
     NnWork &w = m->ws;
     const int64_t np = num_params();
