@@ -8,6 +8,7 @@
 // applies P (one thread per node) and remaps.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -80,6 +81,110 @@ int check_handle(const Coarse *h)
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev != h->dev)
         return fail(FDIRW_E_ARG, "coarse handle belongs to device %d, current device is %d", h->dev, dev);
+    return FDIRW_OK;
+}
+
+// Node windows by cells, where that is the cheaper way; *done: S is written.
+// The windows of 64 neighbouring nodes share the rows of the blocks around
+// them, so a lane is wasted on every cell outside its own window; the other way
+// (launch_nodewin) visits every cell of every window, those that can hold
+// nothing included.  Lanes per window cell, and ms for rows / whole windows
+// (60^3, 100 sub-steps): particle 0.28 12.4 / 52 (250 sub-steps), 0.84 5.7 /
+// 9.9; porous medium, block 3, r 12 1.54 91 / 108; block 2, r 9 (60) 1.57 137 /
+// 133; block 4, r 12, pores 2.16 36 / 41; block 20, r 20 2.37 8.6 / 6.8; block 6,
+// r 12 2.94 25 / 17; block 10, r 10 6.3 9.6 / 4.8.  The rows take at most ~2 GB
+// per buffer (else *done stays false).
+constexpr double NODEWIN_LANES = 1.5;
+
+int nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> ids, const double *count, double *S,
+                 hipStream_t st, bool *done, hipError_t *err)
+{
+    *done = false;
+    if (ids.empty()) return FDIRW_OK;
+    struct Bufs {
+        void *block = nullptr, *start = nullptr, *row = nullptr, *cells = nullptr, *lanes = nullptr, *units = nullptr,
+             *ga = nullptr, *gb = nullptr;
+        hipStream_t st;
+        ~Bufs()
+        {
+            (void)hipStreamSynchronize(st);
+            for (void *p : {block, start, row, cells, lanes, units, ga, gb}) (void)hipFree(p);
+        }
+    } m;
+    m.st = st;
+    int rc;
+    if ((rc = coarse_alloc(&m.block, (size_t)w.n_nodes * sizeof(int)))) return rc;
+    if ((rc = coarse_alloc(&m.start, (size_t)(w.n_nodes + 1) * sizeof(int)))) return rc;
+    if ((rc = coarse_alloc(&m.row, (size_t)w.n * sizeof(int)))) return rc;
+    std::vector<int> start((size_t)w.n_nodes + 1);
+    hipError_t e = launch_nodewin_number(fp64, w, (int *)m.block, (int *)m.start, (int *)m.row, st);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(start.data(), m.start, start.size() * sizeof(int), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) { *err = e; return FDIRW_OK; }
+    const int n_act = start[(size_t)w.n_nodes];
+    const size_t chunk_bytes = (size_t)(n_act + 1) * 64 * (fp64 ? 8 : 4), most = (size_t)2 << 30;
+    if (n_act <= 0 || chunk_bytes > most) return FDIRW_OK;
+    // nodes along a Morton curve, 64 to a chunk: compact groups, and halves of them
+    const int ncx = w.ncx, ncy = w.ncy, ncz = w.ncz, K = w.K;
+    auto morton = [&](int J) {
+        const uint64_t p[3] = {(uint64_t)(J % ncx), (uint64_t)(J / ncx % ncy), (uint64_t)(J / (ncx * ncy))};
+        uint64_t key = 0;
+        for (int bit = 0; bit < 21; ++bit)
+            for (int x = 0; x < 3; ++x) key |= (p[x] >> bit & 1) << (3 * bit + x);
+        return key;
+    };
+    std::sort(ids.begin(), ids.end(), [&](int p, int q) { return morton(p) < morton(q); });
+    const int64_t n_chunk = ((int64_t)ids.size() + 63) / 64;
+    // the blocks within K blocks of each chunk's bounding box, in units of a
+    // workgroup's rows; given up where the lanes are too many for the windows
+    const double windows = (double)ids.size() * w.wb * (double)w.wb * w.wb;
+    const int per = nodewin_unit_rows();
+    std::vector<NodeWinUnit> units;
+    std::vector<size_t> first((size_t)n_chunk + 1, 0);
+    double rows = 0.0;
+    for (int64_t c = 0; c < n_chunk; ++c) {
+        int lo[3] = {ncx, ncy, ncz}, hi[3] = {0, 0, 0};
+        for (size_t k = (size_t)c * 64; k < ids.size() && k < (size_t)(c + 1) * 64; ++k) {
+            const int p[3] = {ids[k] % ncx, ids[k] / ncx % ncy, ids[k] / (ncx * ncy)};
+            for (int x = 0; x < 3; ++x) {
+                lo[x] = std::min(lo[x], std::max(0, p[x] - K));
+                hi[x] = std::max(hi[x], std::min((x == 0 ? ncx : x == 1 ? ncy : ncz), p[x] + K + 1));
+            }
+        }
+        for (int z = lo[2]; z < hi[2]; ++z)
+            for (int y = lo[1]; y < hi[1]; ++y)
+                for (int x = lo[0]; x < hi[0]; ++x) {
+                    const size_t I = ((size_t)z * ncy + y) * ncx + x;
+                    for (int r = start[I]; r < start[I + 1]; r += per)
+                        units.push_back({(int)c, r, std::min(r + per, start[I + 1]), x, y, z});
+                    rows += start[I + 1] - start[I];
+                }
+        if (64.0 * rows > NODEWIN_LANES * windows) return FDIRW_OK;
+        first[(size_t)c + 1] = units.size();
+    }
+    int64_t at_once = std::min<int64_t>(n_chunk, (int64_t)(most / chunk_bytes));
+    if (at_once > 65535) at_once = 65535;
+    for (NodeWinUnit &u : units) u.chunk %= (int)at_once;      // chunks are numbered within their launch
+    ids.resize((size_t)n_chunk * 64, -1);
+    if ((rc = coarse_alloc(&m.cells, (size_t)n_act * nodewin_cell_bytes(fp64)))) return rc;
+    if ((rc = coarse_alloc(&m.lanes, ids.size() * sizeof(int)))) return rc;
+    if ((rc = coarse_alloc(&m.units, units.size() * sizeof(NodeWinUnit)))) return rc;
+    if ((rc = coarse_alloc(&m.ga, (size_t)at_once * chunk_bytes))) return rc;
+    if ((rc = coarse_alloc(&m.gb, (size_t)at_once * chunk_bytes))) return rc;
+    e = hipMemcpyAsync(m.lanes, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess && !units.empty())
+        e = hipMemcpyAsync(m.units, units.data(), units.size() * sizeof(NodeWinUnit), hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = launch_nodewin_cells(fp64, w, (const int *)m.row, n_act, m.cells, st);
+    for (int64_t c = 0; c < n_chunk && e == hipSuccess; c += at_once) {
+        const int64_t end = std::min(n_chunk, c + at_once);
+        e = launch_nodewin_rows(fp64, w, n_sub, (const int *)m.row, n_act, m.cells, (const int *)m.lanes + c * 64,
+                                (int)(end - c), (const NodeWinUnit *)m.units + first[(size_t)c],
+                                (int)(first[(size_t)end] - first[(size_t)c]), m.ga, m.gb, count, S, st);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    *err = e;
+    *done = e == hipSuccess;
     return FDIRW_OK;
 }
 
@@ -254,25 +359,31 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
                 if (nbat < 1) nbat = 1;
                 if (nbat > 65535) nbat = 65535;
                 if (nbat > (int64_t)ids.size()) nbat = (int64_t)ids.size();
-                int *dids = nullptr;
-                void *ga = nullptr, *gb = nullptr;
-                rc = coarse_alloc((void **)&dids, ids.size() * sizeof(int));
-                if (!rc) rc = coarse_alloc(&ga, (size_t)nbat * wb * wb * wb * esz);
-                if (!rc) rc = coarse_alloc(&gb, (size_t)nbat * wb * wb * wb * esz);
-                if (!rc && !ids.empty())
-                    e = hipMemcpyAsync(dids, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice, st);
                 NodeWinArgs w;
                 w.nx = d->nx; w.ny = d->ny; w.nz = d->nz; w.n = h->n;
                 w.B = block; w.K = K; w.ncx = h->ncx; w.ncy = h->ncy; w.ncz = h->ncz;
                 w.n_nodes = h->n_nodes;
                 w.lx = lam;
                 w.node = (const int *)h->node;
+                w.batch = nullptr;
+                w.n_batch = 0;
                 w.wb = wb;
                 w.sink = h->far_field ? 1 : 0;
-                for (int64_t b0 = 0; !rc && e == hipSuccess && b0 < (int64_t)ids.size(); b0 += nbat) {
-                    w.batch = dids + b0;
-                    w.n_batch = (int)(b0 + nbat <= (int64_t)ids.size() ? nbat : (int64_t)ids.size() - b0);
-                    e = launch_nodewin(prec == FDIRW_FP64, w, d->n_sub, ga, gb, (const double *)h->count, S, st);
+                bool done = false;
+                rc = nodewin_rows(w, prec == FDIRW_FP64, d->n_sub, ids, (const double *)h->count, S, st, &done, &e);
+                int *dids = nullptr;
+                void *ga = nullptr, *gb = nullptr;
+                if (!rc && e == hipSuccess && !done) {
+                    rc = coarse_alloc((void **)&dids, ids.size() * sizeof(int));
+                    if (!rc) rc = coarse_alloc(&ga, (size_t)nbat * wb * wb * wb * esz);
+                    if (!rc) rc = coarse_alloc(&gb, (size_t)nbat * wb * wb * wb * esz);
+                    if (!rc && !ids.empty())
+                        e = hipMemcpyAsync(dids, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice, st);
+                    for (int64_t b0 = 0; !rc && e == hipSuccess && b0 < (int64_t)ids.size(); b0 += nbat) {
+                        w.batch = dids + b0;
+                        w.n_batch = (int)(b0 + nbat <= (int64_t)ids.size() ? nbat : (int64_t)ids.size() - b0);
+                        e = launch_nodewin(prec == FDIRW_FP64, w, d->n_sub, ga, gb, (const double *)h->count, S, st);
+                    }
                 }
                 (void)hipStreamSynchronize(st);
                 (void)hipFree(dids);

@@ -182,6 +182,23 @@ struct NodeWinArgs {
 // ga, gb: n_batch * wb^3 elements each; 2K + 1 <= 17
 hipError_t launch_nodewin(int fp64, const NodeWinArgs &a, int n_sub, void *ga, void *gb, const double *count,
                           double *S, hipStream_t st);
+// Node windows by cells (fdirw_nodewin.hip).  number: block[I] = rows of block
+// I, start[I] = its first row (start[n_nodes]: the rows in all), row[i] = the
+// row of cell i (-1: none).  rows: the windows of the nodes lanes[n_chunk][64]
+// (-1: none) over the units (at most nodewin_unit_rows() rows of one block, for
+// one chunk, every block within K of one of its nodes); ga, gb: n_chunk *
+// (n_act + 1) * 64 elements each; a.batch, a.n_batch, a.wb unused.
+struct NodeWinUnit {
+    int chunk, row, end;
+    int bx, by, bz;           // the block
+};
+int nodewin_unit_rows();
+size_t nodewin_cell_bytes(int fp64);
+hipError_t launch_nodewin_number(int fp64, const NodeWinArgs &a, int *block, int *start, int *row, hipStream_t st);
+hipError_t launch_nodewin_cells(int fp64, const NodeWinArgs &a, const int *row, int n_act, void *cells, hipStream_t st);
+hipError_t launch_nodewin_rows(int fp64, const NodeWinArgs &a, int n_sub, const int *row, int n_act, void *cells,
+                               const int *lanes, int n_chunk, const NodeWinUnit *units, int n_unit, void *ga, void *gb,
+                               const double *count, double *S, hipStream_t st);
 hipError_t launch_coarse_pbc_fd(int fp64, const void *lam, const int *node, int nx, int ny, int nz, int n_sub,
                                 const double *u, double cour, double *a, double *b, double **result, hipStream_t st);
 hipError_t launch_coarse_fill_reservoir(const int *node, int64_t n, double v, double *c, hipStream_t st);
