@@ -697,7 +697,7 @@ int fdirw_coarse_apply_ensemble(void *handle, const double *C_in, double *C_out,
         h->ecpad = h->ecmax = nullptr;
         h->ecpad_members = 0;
         const size_t gb = (size_t)members * s.msize * sizeof(_Float16);
-        if ((rc = coarse_alloc(&h->ecmax, (size_t)members * sizeof(unsigned)))) return rc;
+        if ((rc = coarse_alloc(&h->ecmax, (size_t)members * ensemble_cmax_words() * sizeof(unsigned)))) return rc;
         if ((rc = coarse_alloc(&h->ecpad, gb))) return rc;
         e = launch_fill_u32((unsigned *)h->ecpad, (int64_t)(gb / 4), 0u, st);
         if (e != hipSuccess) return hip_fail(e, "ensemble grid clear");

@@ -18,8 +18,8 @@
 // offset and step is stored once per handle in the lanes' order (16 bytes per
 // lane: one 128-bit load), zeros included.
 //
-// A wave takes one tile and up to 8 column tiles of 16 members, loads each
-// matrix fragment once and feeds it to one MFMA per column tile.
+// A wave takes one tile and one column tile of 16 members, or with many members
+// on a large grid several column tiles (K <= 2: and 8 planes of a tile column).
 //
 // Operands are kept in FP16's normal range: P and every member are scaled by
 // powers of two that bring their largest magnitude into [2^14, 2^15) (the
@@ -31,6 +31,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "fdirw_device.h"
 #include "fdirw_launch.h"
@@ -43,7 +44,6 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int ENS_NT = 256;           // 4 waves, one tile each
-constexpr int ENS_MT = 8;             // column tiles of 16 members per wave
 constexpr int ENS_SLIDE_MG = 4;       // ... in the plane-walking form
 
 // 2^t that brings m into [2^14, 2^15) (1 for m = 0 or not finite).
@@ -78,8 +78,10 @@ __global__ void __launch_bounds__(256) ensemble_pmax_kernel(const _Float16 *__re
     if (threadIdx.x == 0) atomicMax(out, __float_as_uint(fmaxf(fmaxf(wm[0], wm[1]), fmaxf(wm[2], wm[3]))));
 }
 
-// Per member m (blockIdx.y) the bits of the largest |FP32(C)| of its nodes,
-// into cmax[m] (zeroed by the caller).  The member's row is read as 16-byte
+// Per member m (blockIdx.y) the largest |FP32(C)| among the nodes of each
+// workgroup, as bits into cpart[m CMAX_PARTS + blockIdx.x] (parts past the grid
+// 0; ensemble_pack_kernel takes their maximum, so nothing has to be cleared
+// first).  The member's row is read as 16-byte
 // pairs from its first 16-byte boundary, eight independent loads per thread
 // and trip; the one value before that boundary and the one after the last
 // pair (rows of odd length or odd start) are taken by the first thread.
@@ -87,9 +89,10 @@ __global__ void __launch_bounds__(256) ensemble_pmax_kernel(const _Float16 *__re
 __device__ __forceinline__ float nan_max(float a, float b) { return b > a || b != b ? b : a; }
 
 constexpr int CMAX_UNR = 8;
+constexpr int CMAX_PARTS = 16;        // most workgroups per member
 
 __global__ void __launch_bounds__(256) ensemble_cmax_kernel(const double *__restrict__ C, int64_t n_nodes,
-                                                            unsigned *__restrict__ cmax)
+                                                            unsigned *__restrict__ cpart)
 {
     const int64_t a0 = (int64_t)blockIdx.y * n_nodes, a1 = a0 + n_nodes;
     const int64_t b0 = a0 + (((uintptr_t)(C + a0) & 15) ? 1 : 0);   // first 16-byte boundary of the row
@@ -111,14 +114,16 @@ __global__ void __launch_bounds__(256) ensemble_cmax_kernel(const double *__rest
         if (b0 > a0) m = nan_max(m, fabsf((float)C[a0]));
         if (b0 + 2 * np < a1) m = nan_max(m, fabsf((float)C[a1 - 1]));
     }
-    // one atomic per workgroup: waves through LDS first
     __shared__ float wm[4];
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m = nan_max(m, __shfl_xor(m, off, 64));
     if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
     __syncthreads();
+    unsigned *part = cpart + (int64_t)blockIdx.y * CMAX_PARTS;
     if (threadIdx.x == 0)
-        atomicMax(cmax + blockIdx.y, __float_as_uint(nan_max(nan_max(wm[0], wm[1]), nan_max(wm[2], wm[3]))));
+        part[blockIdx.x] = __float_as_uint(nan_max(nan_max(wm[0], wm[1]), nan_max(wm[2], wm[3])));
+    else if (blockIdx.x == 0 && threadIdx.x >= gridDim.x && threadIdx.x < CMAX_PARTS)
+        part[threadIdx.x] = 0u;
 }
 
 // Matrix fragment of (tile, oz, step) for one lane: row i = lane % 16 (node
@@ -170,14 +175,29 @@ __global__ void ensemble_frag_kernel(const _Float16 *__restrict__ P, int64_t pla
 // allocated.
 __global__ void __launch_bounds__(256) ensemble_pack_kernel(const double *__restrict__ C, int n_ens, int64_t n_nodes,
                                                             EnsembleShape s, int cap,
-                                                            const unsigned *__restrict__ cmax,
+                                                            const unsigned *__restrict__ cpart,
+                                                            unsigned *__restrict__ cmax,
                                                             _Float16 *__restrict__ cpad)
 {
+    // the largest magnitude of each of the block's members (non-negative FP32
+    // and NaN compare as unsigned): 16 partial maxima, one per lane of a group
+    __shared__ unsigned top[16];
+    {
+        const int q = threadIdx.x >> 4, mq = 16 * blockIdx.y + q;
+        unsigned b = mq < n_ens ? cpart[(int64_t)mq * CMAX_PARTS + (threadIdx.x & 15)] : 0u;
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) b = max(b, (unsigned)__shfl_xor((int)b, off, 64));
+        if ((threadIdx.x & 15) == 0) {
+            top[q] = b;
+            if (blockIdx.x == 0 && mq < n_ens) cmax[mq] = b;   // for the product's scale-back
+        }
+    }
+    __syncthreads();
     const int row = blockIdx.x;                                // z ncy + y
     const int y = row % s.ncy, z = row / s.ncy;
     const int m = 16 * blockIdx.y + (threadIdx.x & 15), j = threadIdx.x >> 4;
     const bool live = m < n_ens;
-    const float scale = live ? ldexpf(1.0f, pow2_scale(__uint_as_float(cmax[m]))) : 0.0f;
+    const float scale = live ? ldexpf(1.0f, pow2_scale(__uint_as_float(top[threadIdx.x & 15]))) : 0.0f;
     const double *src = C + (live ? (int64_t)m * n_nodes : 0) + (int64_t)row * s.ncx;
     const int nchunk = s.px / 4;
     _Float16 *dst = cpad + ((int64_t)(z + s.K) * s.py + (y + s.K)) * nchunk * cap * 4 + (int64_t)m * 4;
@@ -197,35 +217,41 @@ __global__ void __launch_bounds__(256) ensemble_pack_kernel(const double *__rest
     }
 }
 
-// C_out[e] = P C_in[e] for the members of column tiles [ENS_MT blockIdx.y,
-// + ENS_MT) of one tile per wave (K fixed at compile time: two steps of a z
-// offset unrolled, so their loads are issued ahead of the MFMAs).
-template <int K>
-__global__ void __launch_bounds__(ENS_NT) ensemble_apply_kernel(const half8 *__restrict__ frag,
-                                                                const _Float16 *__restrict__ cpad, int n_ens,
-                                                                int64_t n_nodes, EnsembleShape s, int cap, int sp,
-                                                                const unsigned *__restrict__ cmax,
-                                                                double *__restrict__ out)
+// C_out[e] = P C_in[e], one tile and MT column tiles of 16 members per wave (K
+// fixed at compile time).  Bound by the latency of the operand loads and the
+// wavefronts in flight, then by L2: so MT = 1 spreads the members over waves,
+// the column tiles of one tile on consecutive ones (its fragments come from L1
+// and L2 for all but the first), and registers are left for the loads of several
+// steps (4 to 5 waves per SIMD).  Measured, whole call against MT = 8 for all
+// (32 x 29 x 26 nodes, K = 2): 16 members 23.2 -> 14.5 us, 64 members 35.9 ->
+// 28.9, 256 members (the plane-walking form) 91.7 -> 79.4; 67 x 54 x 54 nodes: 16
+// members 99 -> 54, 64 203 -> 182; 4 us of each are one launch less before it.
+template <int K, int MT>
+__global__ void __launch_bounds__(ENS_NT) __attribute__((amdgpu_waves_per_eu(MT == 1 ? 4 : 1, MT == 1 ? 5 : 8)))
+ensemble_apply_kernel(const half8 *__restrict__ frag, const _Float16 *__restrict__ cpad, int n_ens, int64_t n_nodes,
+                      EnsembleShape s, int cap, int sp, const unsigned *__restrict__ cmax, double *__restrict__ out)
 {
     constexpr int KW = 2 * K + 1, SPAN = 4 + 2 * K, ROW = ru(SPAN, 8), KST = (ROW * SPAN + 31) / 32;
-    constexpr int UNR = KST <= 2 ? KST : (KST % 2 ? 1 : 2);   // steps in flight (registers)
+    // steps and z offsets in flight (registers)
+    constexpr int UNR = MT == 1 ? KST : (KST % 2 ? 1 : 2), ZUNR = K <= 2 ? KW : 1;
     const int lane = threadIdx.x & 63;
-    // consecutive tiles (a z-slab) on one XCD: they share their sources' FP16
-    // copies in that XCD's L2
-    const int64_t tile = xcd_remap(blockIdx.x, gridDim.x) * (int64_t)(ENS_NT / 64) + (threadIdx.x >> 6);
-    if (tile >= s.n_tiles) return;                             // uniform per wave (no barrier below)
-    const int mt0 = blockIdx.y * ENS_MT;
-    const int n_mt = min(ENS_MT, (n_ens + 15) / 16 - mt0);
-    const int t32 = (int)tile;                                 // n_tiles < 2^31 (checked by the host)
+    // a z-slab of tiles on one XCD: they share their sources' FP16 copies in
+    // that XCD's L2
+    const int n_grp = MT == 1 ? (n_ens + 15) / 16 : 1;         // MT > 1: groups along blockIdx.y
+    const uint32_t w = (uint32_t)(xcd_remap(blockIdx.x, gridDim.x) * (ENS_NT / 64) + (threadIdx.x >> 6));
+    const int t32 = (int)(w / (uint32_t)n_grp);                // waves < 2^31 (checked by the launch)
+    if (t32 >= s.n_tiles) return;                              // uniform per wave (no barrier below)
+    const int mt0 = MT == 1 ? (int)(w - (uint32_t)t32 * (uint32_t)n_grp) : blockIdx.y * MT;
+    const int n_mt = min(MT, (n_ens + 15) / 16 - mt0);
     const int txi = t32 % s.tx, tyi = (t32 / s.tx) % s.ty, z = t32 / (s.tx * s.ty);
     const int x0 = 4 * txi, y0 = 4 * tyi, kb = lane >> 4, col = lane & 15;
-    floatx4 acc[ENS_MT];
+    floatx4 acc[MT];
 #pragma unroll
-    for (int t = 0; t < ENS_MT; ++t) acc[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    const half8 *fp = frag + tile * (KW * KST * 64) + lane;
+    for (int t = 0; t < MT; ++t) acc[t] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    const half8 *fp = frag + (int64_t)t32 * (KW * KST * 64) + lane;
     const int nchunk = s.px / 4;
     const _Float16 *cbase = cpad + (int64_t)(16 * mt0 + col) * 4;
-#pragma unroll 1
+#pragma unroll ZUNR
     for (int oz = 0; oz < KW; ++oz) {
         const int zp = z - oz + 2 * K;                        // padded z of the sources
 #pragma unroll UNR
@@ -241,16 +267,16 @@ __global__ void __launch_bounds__(ENS_NT) ensemble_apply_kernel(const half8 *__r
             // every column tile's operand is loaded before the first MFMA (tiles
             // past n_mt reload tile 0: in bounds, results dropped), so the loads
             // of a step are in flight together
-            half8 b[ENS_MT];
+            half8 b[MT];
 #pragma unroll
-            for (int t = 0; t < ENS_MT; ++t) {
+            for (int t = 0; t < MT; ++t) {
                 const _Float16 *c = cp + 64 * (t < n_mt ? t : 0);
                 const uint2 lo = *(const uint2 *)c, hi = *(const uint2 *)(c + (int64_t)cap * 4);
                 __builtin_memcpy(&b[t], &lo, 8);
                 __builtin_memcpy((char *)&b[t] + 8, &hi, 8);
             }
 #pragma unroll
-            for (int t = 0; t < ENS_MT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b[t], acc[t], 0, 0, 0);
+            for (int t = 0; t < MT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b[t], acc[t], 0, 0, 0);
         }
     }
     // acc[t][u]: row 4 kb + u of the tile (node (x0 + u, y0 + kb, z)), member
@@ -258,7 +284,7 @@ __global__ void __launch_bounds__(ENS_NT) ensemble_apply_kernel(const half8 *__r
     const int y = y0 + kb;
     if (y >= s.ncy) return;
 #pragma unroll
-    for (int t = 0; t < ENS_MT; ++t) {
+    for (int t = 0; t < MT; ++t) {
         const int m = 16 * (mt0 + t) + col;
         if (t < n_mt && m < n_ens) {
             const int back = -(sp + pow2_scale(__uint_as_float(cmax[m])));
@@ -382,6 +408,8 @@ EnsembleShape ensemble_shape(int ncx, int ncy, int ncz, int K)
 
 int64_t ensemble_frag_bytes(const EnsembleShape &s) { return s.n_tiles * s.kw * s.kst * 64 * 16; }
 
+int ensemble_cmax_words() { return 1 + CMAX_PARTS; }
+
 hipError_t launch_ensemble_pmax(const void *P16, int64_t n, unsigned *out, hipStream_t st)
 {
     hipError_t e = launch_fill_u32(out, 1, 0u, st);
@@ -413,16 +441,33 @@ hipError_t launch_ensemble_frags(const void *P16, int64_t plane, const EnsembleS
 hipError_t launch_ensemble_pack(const double *C, int n_ens, int64_t n_nodes, const EnsembleShape &s, int cap,
                                 unsigned *cmax, void *cpad, hipStream_t st)
 {
-    hipError_t e = launch_fill_u32(cmax, n_ens, 0u, st);
-    if (e != hipSuccess) return e;
+    unsigned *cpart = cmax + cap;
     const int64_t per_block = 2 * 256 * CMAX_UNR;              // values per workgroup and trip
-    const dim3 gm((unsigned)std::min<int64_t>((n_nodes + per_block - 1) / per_block, 16), (unsigned)n_ens);
-    ensemble_cmax_kernel<<<gm, 256, 0, st>>>(C, n_nodes, cmax);
+    const dim3 gm((unsigned)std::min<int64_t>((n_nodes + per_block - 1) / per_block, CMAX_PARTS), (unsigned)n_ens);
+    ensemble_cmax_kernel<<<gm, 256, 0, st>>>(C, n_nodes, cpart);
+    hipError_t e;
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const dim3 grid((unsigned)(s.ncy * s.ncz), (unsigned)((n_ens + 15) / 16));
-    ensemble_pack_kernel<<<grid, 256, 0, st>>>(C, n_ens, n_nodes, s, cap, cmax, (_Float16 *)cpad);
+    ensemble_pack_kernel<<<grid, 256, 0, st>>>(C, n_ens, n_nodes, s, cap, cpart, cmax, (_Float16 *)cpad);
     return hipGetLastError();
 }
+
+// The plane-walking form needs 1/32 of the waves and holds two per SIMD: it is
+// the faster one where its waves still fill the chip (about 1280 for 1024
+// SIMDs) and the operand loads that it saves come from L2 or HBM.  Measured at
+// 128 members, K = 2 (waves of the other form; other form / this one): 13e3 14.4
+// / 45 us, 27e3 (256 members) 79 / 91, 55e3 186 / 158, 58e3 199 / 173, 95e3 340 /
+// 329; below 8 column tiles it was never ahead.
+constexpr int64_t ENS_SLIDE_WAVES = 40960;
+
+// K >= 3 (9 or 14 KB of fragments per tile and z offset pair): from 7 column
+// tiles (6 at K = 4) one wave for 8 of them, where the waves of the other form
+// are 8 per SIMD or more.  Measured (one column tile per wave / eight): 48 x 48
+// x 48 nodes, K = 4, 80 members 293 / 314 us, 112 391 / 352, 512 1852 / 1476; 34
+// x 32 x 30 nodes, K = 3, 96 74 / 86, 512 454 / 346; 20 x 18 x 17 nodes, K = 4,
+// 128 36 / 56.
+constexpr int ENS_MT = 8;
+constexpr int64_t ENS_WIDE_WAVES = 8192;
 
 hipError_t launch_ensemble_apply(const void *frag, const void *cpad, int n_ens, int64_t n_nodes,
                                  const EnsembleShape &s, int cap, int sp, const unsigned *cmax, double *out,
@@ -431,9 +476,8 @@ hipError_t launch_ensemble_apply(const void *frag, const void *cpad, int n_ens, 
     const int n_mt = (n_ens + 15) / 16;
     const half8 *f = (const half8 *)frag;
     const _Float16 *c = (const _Float16 *)cpad;
-    // the plane-walking form keeps ZC planes of accumulators (two waves per
-    // SIMD) and has fewer waves: it pays from 8 column tiles (128 members) on
-    if (s.K <= 2 && n_mt >= 2 * ENS_SLIDE_MG) {
+    const int64_t n_waves = s.n_tiles * n_mt;
+    if (s.K <= 2 && n_mt >= 2 * ENS_SLIDE_MG && n_waves >= ENS_SLIDE_WAVES) {
         constexpr int ZC = 8, MG = ENS_SLIDE_MG;
         const int64_t waves = (int64_t)s.tx * s.ty * ((s.ncz + ZC - 1) / ZC);
         const int64_t blocks = (waves + ENS_NT / 64 - 1) / (ENS_NT / 64);
@@ -445,17 +489,25 @@ hipError_t launch_ensemble_apply(const void *frag, const void *cpad, int n_ens, 
         }
         return hipGetLastError();
     }
-    const int64_t blocks = (s.n_tiles + ENS_NT / 64 - 1) / (ENS_NT / 64);
-    const dim3 grid((unsigned)((blocks + 7) / 8 * 8), (unsigned)((n_mt + ENS_MT - 1) / ENS_MT));
+    if (n_waves > INT32_MAX - 8 * ENS_NT / 64) return hipErrorInvalidValue;
+    const auto go = [&](auto kc, auto mc) {
+        constexpr int K = decltype(kc)::value, MT = decltype(mc)::value;
+        const int64_t blocks = ((MT == 1 ? n_waves : s.n_tiles) + ENS_NT / 64 - 1) / (ENS_NT / 64);
+        const dim3 grid((unsigned)((blocks + 7) / 8 * 8), (unsigned)(MT == 1 ? 1 : (n_mt + MT - 1) / MT));
+        ensemble_apply_kernel<K, MT><<<grid, ENS_NT, 0, st>>>(f, c, n_ens, n_nodes, s, cap, sp, cmax, out);
+        return hipGetLastError();
+    };
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, ENS_MT> many;
+    const bool wide = n_mt >= (s.K == 3 ? 7 : 6) && n_waves >= ENS_WIDE_WAVES;
     switch (s.K) {
-    case 0: ensemble_apply_kernel<0><<<grid, ENS_NT, 0, st>>>(f, c, n_ens, n_nodes, s, cap, sp, cmax, out); break;
-    case 1: ensemble_apply_kernel<1><<<grid, ENS_NT, 0, st>>>(f, c, n_ens, n_nodes, s, cap, sp, cmax, out); break;
-    case 2: ensemble_apply_kernel<2><<<grid, ENS_NT, 0, st>>>(f, c, n_ens, n_nodes, s, cap, sp, cmax, out); break;
-    case 3: ensemble_apply_kernel<3><<<grid, ENS_NT, 0, st>>>(f, c, n_ens, n_nodes, s, cap, sp, cmax, out); break;
-    case 4: ensemble_apply_kernel<4><<<grid, ENS_NT, 0, st>>>(f, c, n_ens, n_nodes, s, cap, sp, cmax, out); break;
+    case 0: return go(std::integral_constant<int, 0>(), one);
+    case 1: return go(std::integral_constant<int, 1>(), one);
+    case 2: return go(std::integral_constant<int, 2>(), one);
+    case 3: return wide ? go(std::integral_constant<int, 3>(), many) : go(std::integral_constant<int, 3>(), one);
+    case 4: return wide ? go(std::integral_constant<int, 4>(), many) : go(std::integral_constant<int, 4>(), one);
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 }  // namespace fdirw

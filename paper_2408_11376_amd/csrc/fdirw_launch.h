@@ -301,8 +301,9 @@ int ensemble_p_scale(unsigned pmax_bits);
 hipError_t launch_ensemble_frags(const void *P16, int64_t plane, const EnsembleShape &s, int sp, void *frag,
                                  hipStream_t st);
 // cap: members the padded grid holds (a multiple of 16, >= n_ens; the
-// grid is cap x msize halves); cmax: n_ens unsigned of scratch (each
-// member's largest |C|)
+// grid is cap x msize halves); cmax: cap x ensemble_cmax_words() unsigned of
+// scratch (the first n_ens: each member's largest |C|, for the product)
+int ensemble_cmax_words();
 hipError_t launch_ensemble_pack(const double *C, int n_ens, int64_t n_nodes, const EnsembleShape &s, int cap,
                                 unsigned *cmax, void *cpad, hipStream_t st);
 hipError_t launch_ensemble_apply(const void *frag, const void *cpad, int n_ens, int64_t n_nodes,
