@@ -257,7 +257,7 @@ static int step_det(const fdirw_domain *d, const fdirw_opts *o, LineArgs a, DevC
         s.part_z0 = za - d->r;
         s.part_planes = part_planes;
         s.wg_kmass = (double *)dc.wgk.p + (size_t)k * lines * 2;
-        hipError_t e = use_flat_layout(o->prec, d->r) ? launch_line_flat(o->prec, d->r, s, stream)
+        hipError_t e = use_flat_layout(o->prec, d->r, d->n_sub) ? launch_line_flat(o->prec, d->r, s, stream)
                                                       : launch_line(o->prec, d->r, s, stream);
         if (e != hipSuccess) return hip_fail(e, "deterministic step launch");
         s.c_out = c_out;
@@ -269,18 +269,31 @@ static int step_det(const fdirw_domain *d, const fdirw_opts *o, LineArgs a, DevC
 }
 
 // The flat layout (fdirw_flat.hip, fdirw_flatwin.hip) serves r = 4..8 with an
-// FP32 state; the environment variable FDIRW_FUSED_LAYOUT=segments selects the
-// segment-layout kernels instead (same kernels, for comparison).
-static bool flat_radius(int r)
+// FP32 state and, in the fused step, r = 3..8 with an FP64 one; the environment
+// variable FDIRW_FUSED_LAYOUT=segments selects the segment-layout kernels
+// instead (same kernels, for comparison).
+static bool flat_radius(int r, int lo)
 {
     static const bool segments = [] {
         const char *v = std::getenv("FDIRW_FUSED_LAYOUT");
         return v && std::strcmp(v, "segments") == 0;
     }();
-    return !segments && r >= 4 && r <= 8;
+    return !segments && r >= lo && r <= 8;
 }
 
-bool use_flat_layout(int prec, int r) { return prec == FDIRW_FP32 && flat_radius(r); }
+constexpr int FLAT64_MIN_SUB = 28;
+
+// FP64: a source costs the flat layout more before its first sub-step (a
+// thread's coefficients lie along z, so its loads are not coalesced) and less
+// in each, so it pays from about 8 (r = 6) to 26 (r = 5) sub-steps on.  Measured
+// (61 x 57 x 60 cells, ms, segments / flat; 2 sub-steps, then 28 (r / 3)^2): r =
+// 3 0.45 / 0.80, 1.68 / 1.46; r = 5 1.23 / 2.49, 16.1 / 13.4; r = 6 3.5 / 4.9,
+// 59.0 / 32.1; r = 7 4.3 / 6.7, 97.3 / 70.8; r = 8 7.0 / 11.4, 160 / 119.
+bool use_flat_layout(int prec, int r, int n_sub)
+{
+    if (prec == FDIRW_FP64) return n_sub >= FLAT64_MIN_SUB && flat_radius(r, 3);
+    return prec == FDIRW_FP32 && flat_radius(r, 4);
+}
 
 // A segment-layout workgroup puts 10 waves on one window where a flat one has
 // 4 for one to four of them, so it is the faster one until the flat
@@ -292,7 +305,7 @@ bool use_flat_window(int prec, int r, int64_t n_src)
 {
     const bool mode = prec == FDIRW_FP32 || prec == FDIRW_FP16_BANK || prec == FDIRW_BF16_BANK;
     const int per = flat_lines_per_group(r);
-    return mode && flat_radius(r) && n_src > (per > 1 ? 384 * per : 256);
+    return mode && flat_radius(r, 4) && n_src > (per > 1 ? 384 * per : 256);
 }
 
 int step_one(const fdirw_domain *d, const fdirw_opts *o, const double *c_in, double *c_out,
@@ -336,7 +349,7 @@ int step_one(const fdirw_domain *d, const fdirw_opts *o, const double *c_in, dou
     if (o->deterministic) {
         if ((rc = step_det(d, o, a, dc, stream, &nblk))) return rc;
     } else {
-        e = use_flat_layout(o->prec, d->r) ? launch_line_flat(o->prec, d->r, a, stream)
+        e = use_flat_layout(o->prec, d->r, d->n_sub) ? launch_line_flat(o->prec, d->r, a, stream)
                                            : launch_line(o->prec, d->r, a, stream);
         if (e != hipSuccess) return hip_fail(e, "fused step launch");
     }

@@ -1,23 +1,24 @@
 // fdirw_flat.hip -- the fused FDiRW big step with a flat window layout
-// (gfx950, FP32 state).
+// (gfx950, FP32 or FP64 state).
 //
 // Same computation as line_kernel (the column form of Eq. 8 of arXiv
 // 2408.11376: every source's window kernel of Sec. 3.1 is generated by the
-// explicit 7-point FD and added, times c(s), into the output), organised for
-// a 256-thread workgroup of four waves, one per SIMD, that runs one source
-// line (r = 7, 8), two (r = 5, 6) or four (r = 4) side by side:
+// explicit 7-point FD and added, times c(s), into the output), organised in
+// FP32 for a 256-thread workgroup of four waves, one per SIMD, that runs one
+// source line (r = 7, 8), two (r = 5, 6) or four (r = 4) side by side, and in
+// FP64 for a workgroup of 64 to 576 threads per line (r = 3..8):
 //   * the W^3 window cells are numbered flat, i = cy PY + cx W + z (z fastest;
-//     PY is W^2 rounded up to a multiple of 4, the cells between are unused),
-//     and thread t of a line's SG threads owns the RUN consecutive cells
-//     [RUN t, RUN t + RUN) in registers (RUN = 20 at r = 8: 249 of 256 lanes
-//     busy; RUN / 4 odd, so the exchange accesses of 16 consecutive lanes
-//     meet no LDS bank twice);
+//     PY is W^2 rounded up to whole 16-byte chunks, the cells between are
+//     unused), and thread t of a line's SG threads owns the RUN consecutive
+//     cells [RUN t, RUN t + RUN) in registers (FP32, r = 8: RUN = 20, 249 of 256
+//     lanes busy; an odd number of chunks, so the exchange accesses of 16
+//     consecutive lanes meet no LDS bank twice);
 //   * the z neighbours of a cell are its run neighbours (registers), except
 //     at the two run ends (from LDS); a run crossing a column boundary meets
 //     a window wall there (coefficient 0);
 //   * the y neighbours are the runs at offsets +-PY, read from the LDS copy of
-//     the window as aligned 128-bit loads (RUN / 4 each).  The runs at +-W (x)
-//     overlap the own run where RUN > W (every radius 4..8): only the W cells
+//     the window as aligned 128-bit loads.  The runs at +-W (x) overlap the own
+//     run where RUN > W (FP32, every radius 4..8): only the W cells
 //     before and after it are read (aligned, ceil(W / 4) loads each, which
 //     also hold the two run-end z neighbours), the rest come from registers;
 //   * double-buffered exchange, one barrier per sub-step;
@@ -27,9 +28,9 @@
 //     c_out with one atomic per window column; then every accumulator moves
 //     down one cell (cell i takes cell i + 1, the run's top cell takes the
 //     next thread's bottom cell), which is the window of source sz + 1.
-// What bounds a sub-step is the LDS pipe: a 128-bit write of a wave takes 13.6
-// clocks of it and a read 5.2 (measured alone), 5 + 20 of them per wave at r =
-// 8, i.e. 690 clocks per window and sub-step against 560 of FP32 FMAs.  The
+// What bounds a sub-step is the LDS pipe.  FP32: a 128-bit write of a wave takes
+// 13.6 clocks of it and a read 5.2 (measured alone), 5 + 20 of them per wave at
+// r = 8, i.e. 690 clocks per window and sub-step against 560 of FP32 FMAs.  The
 // pitch PY saves two reads per wave and sub-step (the offset W^2 is odd, and a
 // misaligned run spans RUN / 4 + 1 loads).  LDS (<= 53 KB) and 168 registers
 // let three workgroups share a CU and fill each other's barrier and LDS waits;
@@ -38,6 +39,13 @@
 // pitch PY against 2 of pitch W^2: r = 4 (50 sub-steps) 12.3 -> 8.9 ms, r = 5
 // (78) 31.1 -> 24.8 ms, r = 6 (113) 68.6 -> 63.0 ms, r = 7 (153) 174 -> 163 ms,
 // r = 8 (200) 233 -> 222 ms.
+// FP64 moves twice the bytes: at r = 8 its 8 waves take 5 + 22 accesses of 16
+// bytes and two of 8 per wave and sub-step, ~1,520 clocks of the LDS pipe, where
+// line_kernel's columns of 9 cells take ~1,750 (top and first cells of a segment
+// go through LDS twice more) and spill in the loop.  The registers let only one
+// workgroup per CU run, so its barriers are not filled by another.  61 x 57 x 60
+// cells, line_kernel / this (ms): r = 3 (28 sub-steps) 1.68 / 1.46, r = 4 7.1 /
+// 4.4, r = 5 16.1 / 13.4, r = 6 59.0 / 32.1, r = 7 97.3 / 70.8, r = 8 160 / 119.
 // Per cell and sub-step the arithmetic is that of one_substep (same terms,
 // same order), so the kernels equal line_kernel's bit for bit.
 #include "fdirw_flat.h"
@@ -46,8 +54,8 @@
 namespace fdirw {
 
 // One source line of one domain for the flat layout; the face coefficients
-// come from the accessor f (FaceArrays<float> over [3][n] FP32 owned-face
-// coefficients, or FaceLabels<float> over a phase-pair table).  part (the
+// come from the accessor f (FaceArrays over [3][n] owned-face coefficients, or
+// FaceLabels over a phase-pair table).  part (the
 // deterministic form): completed planes go to the partial slots part[(col
 // part_planes + Z - part_z0) nxy + Y nx + X] as plain stores instead of FP64
 // atomics into c_out.
@@ -101,27 +109,27 @@ template <int R> constexpr int flat_plane_max()
     if constexpr (R == 0) return FLAT_PLANE<0>;
     else return flat_max(FLAT_PLANE<R>, flat_plane_max<R - 1>());
 }
-constexpr int FLAT_EDGE = 2 * (FLAT_NT / 64 + 1);            // one value per wave and parity, and a 0
 
 // The sources (sx, sy, z0 .. z1 - 1) of the lines line0 .. line0 + nlines - 1
-// (line = sy nx + sx; 1 <= nlines <= Flat<R>::LPW) by a workgroup of FLAT_NT
-// threads, Flat<R>::SG threads per line, the lines side by side in lockstep
+// (line = sy nx + sx; 1 <= nlines <= F::LPW) by a workgroup of F::NT
+// threads, F::SG threads per line, the lines side by side in lockstep
 // (their sub-steps share the barriers): kernels generated and superposed into
-// a.c_out (FP64 atomics).  xb: FLAT_XB<R> floats of LDS (16-byte aligned),
-// red: 4 doubles, edge: FLAT_EDGE doubles, plane: FLAT_PLANE<R> doubles.  Every thread of the block calls it; the
-// first thread of line g leaves the line's smallest and largest kernel mass
+// a.c_out (FP64 atomics).  xb: 2 LPW XLEN cells of LDS (16-byte aligned),
+// red: NT / 64 doubles, edge: EDGE doubles, plane: 2 LPW W2 doubles.  Every
+// thread of the block calls it; the first thread of line g leaves the line's smallest and largest kernel mass
 // and its number of kernels in fig[3 g .. 3 g + 2] (LDS; kept there and not in
 // registers, which the sub-step loop needs all).  A window group
 // past nlines runs on zero coefficients and writes nothing.  DET:
 // the deterministic form (partial slots, a.part).
-template <int R, bool DET, typename Faces>
-__device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, int nlines, int z0, int z1, float *xb,
-                                          double *red, double *edge, double *plane, double *fig)
+template <typename F, bool DET, typename Faces>
+__device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, int nlines, int z0, int z1,
+                                          typename F::S *xb, double *red, double *edge, double *plane, double *fig)
 {
-    using F = Flat<R>;
+    using S = typename F::S;
+    constexpr int R = F::R, FLAT_EDGE = F::EDGE;
+    constexpr bool RENORM = sizeof(S) == 4;                   // FP64 kernels are taken as they are
     constexpr int W = F::W, W2 = F::W2, RUN = F::RUN, PAD = F::PAD, XLEN = F::XLEN;
     constexpr int SG = F::SG, LPW = F::LPW;
-    static_assert(F::NT == FLAT_NT, "workgroup size");
 
     const int t = threadIdx.x;
     const int g = LPW == 1 ? 0 : t / SG;                      // the thread's line in the workgroup
@@ -136,9 +144,9 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     int lofs[LPW];                                           // (y, x) offsets of the workgroup's lines
 #pragma unroll
     for (int h = 0; h < LPW; ++h) lofs[h] = line0 + h;
-    float *const xg = xb + g * XLEN;                         // the line's first exchange buffer
+    S *const xg = xb + g * XLEN;                         // the line's first exchange buffer
     __syncthreads();                                        // LDS of a previous line is no longer read
-    for (int i = t; i < 2 * LPW * XLEN; i += F::NT) xb[i] = 0.0f;
+    for (int i = t; i < 2 * LPW * XLEN; i += F::NT) xb[i] = S(0);
     if (t < FLAT_EDGE) edge[t] = 0.0;
     if (tg == 0) { fig[3 * g] = INFINITY; fig[3 * g + 1] = -INFINITY; fig[3 * g + 2] = 0.0; }
     __syncthreads();
@@ -170,22 +178,22 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
             }
         }
         if (any) {
-            FlatSeg<R> c;
-            flat_load<R>(c, a.f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
-            float Gs[RUN];
+            FlatSeg<F> c;
+            flat_load<F>(c, a.f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
+            S Gs[RUN];
 #pragma unroll
             for (int k = 0; k < RUN; ++k) {
-                const FlatCell<R> p(s0v + k);
-                Gs[k] = (p.ok && p.cx == R && p.cy == R && p.z == R) ? 1.0f : 0.0f;
+                const FlatCell<F> p(s0v + k);
+                Gs[k] = (p.ok && p.cx == R && p.cy == R && p.z == R) ? S(1) : S(0);
             }
-            flat_substeps<R, false>(Gs, c, xg, xg + LPW * XLEN, own, a.n_sub, 0u);
+            flat_substeps<F, false>(Gs, c, xg, xg + LPW * XLEN, own, a.n_sub, 0u);
             // kernel mass: per thread in cell order, then over the line's threads
             double ms = 0.0;
             if (act) {
 #pragma unroll
                 for (int k = 0; k < RUN; ++k) ms += (double)Gs[k];
             }
-            const double m = flat_window_sum<R>(ms, red, g);
+            const double m = flat_window_sum<F>(ms, red, g);
             // (the source is read again, not kept across the sub-steps)
             int gv = g;
             asm volatile("" : "+v"(gv));
@@ -195,7 +203,7 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
                 fig[3 * g + 1] = fmax(fig[3 * g + 1], m);
                 fig[3 * g + 2] += 1.0;
             }
-            const double scale = cs != 0.0 ? cs / m : 0.0;
+            const double scale = cs != 0.0 ? (RENORM ? cs / m : cs) : 0.0;
 #pragma unroll
             for (int k = 0; k < RUN; ++k) acc[k] = __builtin_fma(scale, (double)Gs[k], acc[k]);
         }
@@ -206,7 +214,7 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
         // below gives consecutive lanes consecutive columns (coalesced atomics)
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
-            const FlatCell<R> p(s0v + k);
+            const FlatCell<F> p(s0v + k);
             if (p.z == 0) {
                 if (p.ok) plane[(par * LPW + g) * W2 + p.col] = acc[k];
                 acc[k] = 0.0;
@@ -234,7 +242,7 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     for (int zp = 0; zp < W - 1; ++zp) {
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
-            const FlatCell<R> p(s0v + k);
+            const FlatCell<F> p(s0v + k);
             if (p.ok && p.z == zp) plane[(par * LPW + g) * W2 + p.col] = acc[k];
         }
         __syncthreads();
@@ -243,15 +251,15 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     }
 }
 
-template <int R, bool LAB, bool DET>
-__global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(3)))
+template <typename F, bool LAB, bool DET>
+__global__ void __launch_bounds__(F::NT) __attribute__((amdgpu_waves_per_eu(F::WPE)))
 flat_line_kernel(LineArgs a)
 {
-    using F = Flat<R>;
-    __shared__ __align__(16) float xb[FLAT_XB<R>];
-    __shared__ double red[4];
-    __shared__ double edge[FLAT_EDGE];
-    __shared__ double plane[FLAT_PLANE<R>];
+    using S = typename F::S;
+    __shared__ __align__(16) S xb[2 * F::LPW * F::XLEN];
+    __shared__ double red[F::NT / 64];
+    __shared__ double edge[F::EDGE];
+    __shared__ double plane[2 * F::LPW * F::W2];
     // block b: lines LPW lg .. + LPW - 1 (those inside the domain), segment sgi
     const int b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
     const int lg = b / a.n_seg, sgi = b - lg * a.n_seg;
@@ -261,15 +269,15 @@ flat_line_kernel(LineArgs a)
     if (z0 >= z1) return;                                   // uniform per block
     __shared__ double fig[3 * F::LPW];
     if constexpr (LAB) {
-        const FaceLabels<float> f{a.label, (const float *)a.lam_tab, a.n_phase, a.nx, a.ny, a.nz};
-        const FlatLine<FaceLabels<float>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, f,
-                                             a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
-        flat_line<R, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
+        const FaceLabels<S> f{a.label, (const S *)a.lam_tab, a.n_phase, a.nx, a.ny, a.nz};
+        const FlatLine<FaceLabels<S>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, f,
+                                         a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
+        flat_line<F, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
     } else {
-        const float *lx = (const float *)a.lx;
-        const FlatLine<FaceArrays<float>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, {lx, lx + a.n, lx + 2 * a.n},
-                                             a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
-        flat_line<R, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
+        const S *lx = (const S *)a.lx;
+        const FlatLine<FaceArrays<S>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, {lx, lx + a.n, lx + 2 * a.n},
+                                         a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
+        flat_line<F, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
     }
     // per line and segment: entry line n_seg + sgi of the kernel-mass range
     const int g = (int)threadIdx.x / F::SG;
@@ -306,7 +314,7 @@ __device__ __attribute__((noinline)) void flat_line_item(const FlatLine<FaceArra
     const FlatLine<FaceArrays<float>> u{nx, ny, nz, n, uniform(a.n_sub), {lx, lx + n, lx + 2 * n},
                                         uniform(a.c_in), uniform(a.c_out), nullptr, 0, 0};
     nlines = uniform(nlines);
-    flat_line<R, false>(u, uniform(line0), nlines, uniform(z0), uniform(z1), xb, red, edge, plane, fig);
+    flat_line<Flat<R>, false>(u, uniform(line0), nlines, uniform(z0), uniform(z1), xb, red, edge, plane, fig);
     const int t = threadIdx.x;
     __syncthreads();                                         // every line's figures are there
     if (t == 0) {
@@ -331,7 +339,7 @@ flat_batched_kernel(BatchArgs a)
 {
     __shared__ __align__(16) float xb[flat_xb_max<8>()];
     __shared__ double red[4];
-    __shared__ double edge[FLAT_EDGE];
+    __shared__ double edge[Flat<8>::EDGE];
     __shared__ double plane[flat_plane_max<8>()];
     __shared__ double fig[3 * (FLAT_NT / 32)];
     __shared__ int s_item;
@@ -382,16 +390,22 @@ int flat_lines_per_group(int r)
     return r >= 0 && r <= 8 ? FLAT_NT / line_threads(r) : 1;
 }
 
-template <int R, bool LAB>
-static hipError_t launch_flat_r(const LineArgs &a, hipStream_t st)
+template <typename F, bool LAB>
+static hipError_t launch_flat_f(const LineArgs &a, hipStream_t st)
 {
-    const int64_t groups = ((int64_t)a.nx * a.ny + Flat<R>::LPW - 1) / Flat<R>::LPW;
+    const int64_t groups = ((int64_t)a.nx * a.ny + F::LPW - 1) / F::LPW;
     const int64_t nblk = groups * a.n_seg;
     if (a.part)
-        hipLaunchKernelGGL((flat_line_kernel<R, LAB, true>), dim3((unsigned)nblk), dim3(Flat<R>::NT), 0, st, a);
+        hipLaunchKernelGGL((flat_line_kernel<F, LAB, true>), dim3((unsigned)nblk), dim3(F::NT), 0, st, a);
     else
-        hipLaunchKernelGGL((flat_line_kernel<R, LAB, false>), dim3((unsigned)nblk), dim3(Flat<R>::NT), 0, st, a);
+        hipLaunchKernelGGL((flat_line_kernel<F, LAB, false>), dim3((unsigned)nblk), dim3(F::NT), 0, st, a);
     return hipGetLastError();
+}
+
+template <int R, bool LAB>
+static hipError_t launch_flat_r(int mode, const LineArgs &a, hipStream_t st)
+{
+    return mode == M_FP64 ? launch_flat_f<Flat64<R>, LAB>(a, st) : launch_flat_f<Flat<R>, LAB>(a, st);
 }
 
 template <bool LAB>
@@ -399,18 +413,19 @@ static hipError_t launch_flat(int mode, int r, const LineArgs &a, hipStream_t st
 {
     // the deterministic form needs whole lines (one plane range per line, so
     // that each partial slot has one writer)
-    if (mode != M_FP32 || (a.part && a.n_seg != 1)) return hipErrorInvalidValue;
+    if ((mode != M_FP32 && mode != M_FP64) || (a.part && a.n_seg != 1)) return hipErrorInvalidValue;
     switch (r) {
-    case 4: return launch_flat_r<4, LAB>(a, st);
-    case 5: return launch_flat_r<5, LAB>(a, st);
-    case 6: return launch_flat_r<6, LAB>(a, st);
-    case 7: return launch_flat_r<7, LAB>(a, st);
-    case 8: return launch_flat_r<8, LAB>(a, st);
+    case 3: return mode == M_FP64 ? launch_flat_f<Flat64<3>, LAB>(a, st) : hipErrorInvalidValue;
+    case 4: return launch_flat_r<4, LAB>(mode, a, st);
+    case 5: return launch_flat_r<5, LAB>(mode, a, st);
+    case 6: return launch_flat_r<6, LAB>(mode, a, st);
+    case 7: return launch_flat_r<7, LAB>(mode, a, st);
+    case 8: return launch_flat_r<8, LAB>(mode, a, st);
     default: return hipErrorInvalidValue;
     }
 }
 
-// The flat-layout fused step: FP32 mode, radii 4..8, atomic superposition or,
+// The flat-layout fused step: FP32 mode, radii 4..8, and FP64, 3..8, atomic superposition or,
 // with a.part and one segment per line, the partial slots of the
 // deterministic form.  Returns hipErrorInvalidValue for other requests.
 hipError_t launch_line_flat(int mode, int r, const LineArgs &a, hipStream_t st)

@@ -48,22 +48,22 @@ flat_window_kernel(WindowArgs a)
         // being kept in registers across the sub-step loop
         asm volatile("" : "+v"(s0v));
         __syncthreads();                                       // LDS of the previous sources is no longer read
-        FlatSeg<R> c;
-        flat_load<R>(c, f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
+        FlatSeg<F> c;
+        flat_load<F>(c, f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
         float Gs[RUN];
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
-            const FlatCell<R> p(s0v + k);
+            const FlatCell<F> p(s0v + k);
             Gs[k] = (p.ok && p.cx == R && p.cy == R && p.z == R) ? 1.0f : 0.0f;
         }
-        flat_substeps<R, false>(Gs, c, xg, xg1, PAD + s0, a.n_sub, 0u);
+        flat_substeps<F, false>(Gs, c, xg, xg1, PAD + s0, a.n_sub, 0u);
         double ms = 0.0;
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
             if constexpr (T::bank) Gs[k] = round_to<B>(Gs[k]);
             ms += (double)Gs[k];                               // cells past the window hold 0
         }
-        const double m = flat_window_sum<R>(ms, red, g);
+        const double m = flat_window_sum<F>(ms, red, g);
         if (tg == 0 && live && a.mass) a.mass[q] = m;
         const bool norm = !T::bank && a.normalize;
         const double inv = norm ? 1.0 / m : 1.0;
@@ -76,7 +76,7 @@ flat_window_kernel(WindowArgs a)
             const int64_t plane = (int64_t)((a.nz + zb - 1) / zb) * nxy * zb;
 #pragma unroll
             for (int k = 0; k < RUN; ++k) {
-                const FlatCell<R> p(s0v + k);
+                const FlatCell<F> p(s0v + k);
                 const int X = sx - R + p.cx, Y = sy - R + p.cy, Z = sz - R + p.z;
                 if (!p.ok || X < 0 || X >= a.nx || Y < 0 || Y >= a.ny || Z < 0 || Z >= a.nz) continue;
                 const int64_t o = (int64_t)(p.z * W2 + p.col) * plane +
@@ -92,7 +92,7 @@ flat_window_kernel(WindowArgs a)
             float *stage = xg1 + PAD;
 #pragma unroll
             for (int k = 0; k < RUN; ++k) {
-                const FlatCell<R> p(s0v + k);
+                const FlatCell<F> p(s0v + k);
                 if (p.ok) stage[p.z * W2 + p.col] = norm ? (float)((double)Gs[k] * inv) : Gs[k];
             }
             __syncthreads();
@@ -189,19 +189,19 @@ flat_coarse_kernel(CoarseGenArgs a)
                 if constexpr (SINK) sink |= v[k] == 2.0f ? 1u << k : 0u;
             }
         }
-        FlatSeg<R> c;
-        flat_load<R>(c, f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
+        FlatSeg<F> c;
+        flat_load<F>(c, f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
         float Gs[RUN];
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
-            const FlatCell<R> p(s0v + k);
+            const FlatCell<F> p(s0v + k);
             Gs[k] = (p.ok && p.cx == R && p.cy == R && p.z == R) ? 1.0f : 0.0f;
         }
-        flat_substeps<R, SINK>(Gs, c, xg, xg + LPW * XLEN, PAD + s0, a.n_sub, sink);
+        flat_substeps<F, SINK>(Gs, c, xg, xg + LPW * XLEN, PAD + s0, a.n_sub, sink);
         double part = 0.0;
 #pragma unroll
         for (int k = 0; k < RUN; ++k) part += (grp >> k) & 1u ? (double)Gs[k] : 0.0;
-        const double m = flat_window_sum<R>(part, red, g);
+        const double m = flat_window_sum<F>(part, red, g);
         const double inv = SINK ? 1.0 : 1.0 / m;
         for (int o = tg; o < nb; o += SG) bins[o] = 0.0;
         __syncthreads();
@@ -211,7 +211,7 @@ flat_coarse_kernel(CoarseGenArgs a)
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
             if ((grp >> k) & 1u && Gs[k] != 0.0f) {
-                const FlatCell<R> p(s0v + k);
+                const FlatCell<F> p(s0v + k);
                 const int o = (dest[g][2][p.z] * KW + dest[g][1][p.cy]) * KW + dest[g][0][p.cx];
                 if (o != cur) {
                     if (cur >= 0) atomicAdd(&bins[cur], sum);
@@ -294,7 +294,7 @@ flat_flow_kernel(FlowArgs a)
         float Gs[RUN];
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
-            const FlatCell<R> p(s0v + k);
+            const FlatCell<F> p(s0v + k);
             const int cx = p.cx, cy = p.cy, zw = p.z;
             const int X = sx - R + cx, Y = sy - R + cy, Z = sz - R + zw;
             const bool in = live && p.ok && X >= 0 && X < a.nx && Y >= 0 && Y < a.ny && Z >= 0 && Z < a.nz;
@@ -380,7 +380,7 @@ flat_flow_kernel(FlowArgs a)
             float *stage = xg + LPW * XLEN + PAD;
 #pragma unroll
             for (int k = 0; k < RUN; ++k) {
-                const FlatCell<R> p(s0v + k);
+                const FlatCell<F> p(s0v + k);
                 if (p.ok) stage[p.z * W2 + p.col] = Gs[k];
             }
         }

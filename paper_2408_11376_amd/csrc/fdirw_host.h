@@ -71,7 +71,7 @@ int coef_buffers(const fdirw_domain *d, int prec, hipStream_t st, DevCache &dc, 
 int field_sum_dev(const double *c, int64_t n, hipStream_t st, DevCache &dc, double *out_host);
 void line_shape(const fdirw_domain *d, int tune, int *seg_len, int *n_seg);
 // True when the fused step of this precision and radius runs the flat-layout kernel.
-bool use_flat_layout(int prec, int r);
+bool use_flat_layout(int prec, int r, int n_sub);
 // ... and for the window kernels of n_src sources (fdirw_kernels, the bank, the coarse build)
 bool use_flat_window(int prec, int r, int64_t n_src);
 // Source planes per launch of the deterministic step (a function of the

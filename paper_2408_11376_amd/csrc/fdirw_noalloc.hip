@@ -146,7 +146,7 @@ extern "C" int fdirw_step_noalloc(const fdirw_domain *d, const fdirw_opts *o, co
     a.label = d->label;
     a.lam_tab = ptab;
     a.n_phase = d->n_phase;
-    e = use_flat_layout(o->prec, d->r) ? launch_line_flat_labels(o->prec, d->r, a, stream)
+    e = use_flat_layout(o->prec, d->r, d->n_sub) ? launch_line_flat_labels(o->prec, d->r, a, stream)
                                        : launch_line_labels(o->prec, d->r, a, stream);
     if (e != hipSuccess) return hip_fail(e, "fused step launch");
     if (st) {
