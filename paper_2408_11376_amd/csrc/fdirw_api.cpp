@@ -281,17 +281,26 @@ static bool flat_radius(int r, int lo)
     return !segments && r >= lo && r <= 8;
 }
 
-constexpr int FLAT64_MIN_SUB = 28;
+// FP64: the flat layout costs a source more outside its sub-steps (coefficient
+// loads along z, the ring's shift) and less in each, so it pays from
+// flat64_min_sub sub-steps on.  Measured (61 x 57 x 60 cells, ms, segments /
+// flat; 2 sub-steps, then 28 (r / 3)^2): r = 3 0.45 / 0.80, 1.68 / 1.46; r = 4
+// 1.05 / 0.93, 7.1 / 4.4; r = 5 1.23 / 2.49, 16.1 / 13.4; r = 6 3.5 / 4.9, 59.0 /
+// 32.1; r = 7 4.3 / 6.7, 97.3 / 70.8; r = 8 7.0 / 11.4, 160 / 119.
+static int flat64_min_sub(int r)
+{
+    switch (r) {
+    case 4: return 2;
+    case 5: return 28;
+    case 6: return 8;
+    case 7: return 16;
+    default: return 24;
+    }
+}
 
-// FP64: a source costs the flat layout more before its first sub-step (a
-// thread's coefficients lie along z, so its loads are not coalesced) and less
-// in each, so it pays from about 8 (r = 6) to 26 (r = 5) sub-steps on.  Measured
-// (61 x 57 x 60 cells, ms, segments / flat; 2 sub-steps, then 28 (r / 3)^2): r =
-// 3 0.45 / 0.80, 1.68 / 1.46; r = 5 1.23 / 2.49, 16.1 / 13.4; r = 6 3.5 / 4.9,
-// 59.0 / 32.1; r = 7 4.3 / 6.7, 97.3 / 70.8; r = 8 7.0 / 11.4, 160 / 119.
 bool use_flat_layout(int prec, int r, int n_sub)
 {
-    if (prec == FDIRW_FP64) return n_sub >= FLAT64_MIN_SUB && flat_radius(r, 3);
+    if (prec == FDIRW_FP64) return flat_radius(r, 3) && n_sub >= flat64_min_sub(r);
     return prec == FDIRW_FP32 && flat_radius(r, 4);
 }
 

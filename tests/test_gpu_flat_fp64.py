@@ -1,12 +1,12 @@
-"""GPU: the flat-layout fused step in FP64 (r = 3..8, from 28 sub-steps on).
+"""GPU: the flat-layout fused step in FP64 (r = 3..8, from 2 to 28 sub-steps on).
 
 Against the FP64 oracle (1e-13, the bar of the FP64 step), the deterministic
 form (the same kernels, sums in another order: 1e-13 relative; repeats bitwise),
 the step with coefficients by phase pair, and, for a one-hot field, the kernel
 of fdirw_kernels (segment layout, the same arithmetic per cell): bit for bit.
 Domains smaller than the window, ragged lines, zero sources between nonzero
-ones, lines cut into segments, odd and even sub-step counts, and 27 sub-steps
-(the segment layout)."""
+ones, lines cut into segments, odd and even sub-step counts, and 15 sub-steps
+at r = 7 (the segment layout)."""
 import numpy as np
 import pytest
 
@@ -30,7 +30,7 @@ def _dev(d):
 @pytest.mark.parametrize("shape,r,n_sub,tune", [
     ((9, 10, 11), 3, 28, 0), ((4, 3, 21), 3, 29, 3), ((12, 7, 13), 4, 31, 0), ((6, 15, 8), 5, 30, 2),
     ((10, 9, 11), 6, 29, 0), ((16, 14, 15), 7, 28, 0), ((19, 18, 20), 8, 29, 0), ((5, 6, 7), 8, 30, 5),
-    ((23, 1, 4), 8, 31, 3), ((11, 12, 5), 7, 27, 0)])
+    ((23, 1, 4), 8, 31, 3), ((11, 12, 5), 7, 15, 0), ((7, 9, 17), 4, 2, 0), ((13, 5, 8), 6, 9, 0)])
 def test_step(shape, r, n_sub, tune):
     d = synth.random_small(shape, 3, r=r, n_sub=n_sub, seed=940 + r + n_sub)
     c0 = d.c0.copy()
