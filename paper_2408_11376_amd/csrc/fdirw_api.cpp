@@ -83,7 +83,7 @@ static void release_all()
     for (auto &kv : g_cache) {
         (void)hipSetDevice(kv.first);
         DevCache &c = kv.second;
-        for (Buf *b : {&c.lam64, &c.lam32, &c.flags, &c.part, &c.wgk, &c.small, &c.bank, &c.bank_mass, &c.bank_chat, &c.blam,
+        for (Buf *b : {&c.lam64, &c.lam32, &c.flags, &c.part, &c.wgk, &c.small, &c.bank, &c.bank_mass, &c.bank_chat, &c.bank_part, &c.blam,
                        &c.bsmall, &c.bdoms, &c.bitems, &c.det}) {
             if (b->p) (void)hipFree(b->p);
             b->p = nullptr;

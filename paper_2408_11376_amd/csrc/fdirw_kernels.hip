@@ -410,12 +410,12 @@ line_kernel(LineArgs a)
 // Within one offset plane the cells are ordered [z / ZB][y][x][z % ZB] with
 // ZB = 16 bytes / element size, so that the ZB z-consecutive values a thread
 // needs are one 16-byte load and a wave reads 1 KB contiguously.
-// A workgroup owns a tile of 64 (x) x 1 (y) x TZ (z) output cells; every bank
-// value is read once and every output written once: no atomics, a fixed
-// summation order per cell.  c^ is read from a zero-padded copy (halo R on
-// each side); per source row y - oy the block stages the (TZ + 2R) x (64 + 2R)
-// slab of it in LDS, and each thread keeps the ZB + 2R values its z-run needs
-// in registers across the W z-offsets.
+// A workgroup owns a tile of 64 (x) x 1 (y) x TZ (z) output cells, on a small
+// grid a range of its source rows (bank_split); every bank value is read once:
+// no atomics, a fixed summation order per cell.  c^ is read from a zero-padded
+// copy (halo R on each side); per source row y - oy the block stages the (TZ +
+// 2R) x (64 + 2R) slab of it in LDS, and each thread keeps the ZB + 2R values its
+// z-run needs in registers across the W z-offsets.
 template <typename B> struct BankZ {
     static constexpr int ZB = 16 / (int)sizeof(B);   // z cells per 16-byte group
 };
@@ -477,7 +477,11 @@ __global__ void __launch_bounds__((Gath<B, R>::NT)) bank_gather_kernel(BankArgs 
     constexpr int W = G_::W, W2 = G_::W2, ZB = G_::ZB, SX = G_::SX, SZ = G_::SZ, NT = G_::NT;
     __shared__ double slab[SZ * SX];
     const int tx = threadIdx.x % G_::TX, tz = threadIdx.x / G_::TX;
-    const int x0 = blockIdx.x * G_::TX, y = blockIdx.y, z0 = blockIdx.z * G_::TZ;
+    // part pt of the n_split parts of the source rows: offsets oy0 .. oy1
+    const int n_zt = (a.nz + G_::TZ - 1) / G_::TZ;
+    const int pt = blockIdx.z / n_zt, rows = (W + a.n_split - 1) / a.n_split;
+    const int oy0 = -R + pt * rows, oy1 = min(R, oy0 + rows - 1);
+    const int x0 = blockIdx.x * G_::TX, y = blockIdx.y, z0 = (blockIdx.z - pt * n_zt) * G_::TZ;
     const int x = x0 + tx;
     const int zt = z0 + tz * ZB;                      // first output z of the thread (uniform per wave)
     const int px = a.nx + 2 * R, py = a.ny + 2 * R, pz = a.nz + 2 * R;
@@ -490,7 +494,7 @@ __global__ void __launch_bounds__((Gath<B, R>::NT)) bank_gather_kernel(BankArgs 
 #pragma unroll
     for (int k = 0; k < ZB; ++k) acc[k] = 0.0;
 
-    for (int oy = -R; oy <= R; ++oy) {
+    for (int oy = oy0; oy <= oy1; ++oy) {
         const int64_t row = (int64_t)(y - oy + R) * px;   // padded source row
         __syncthreads();                                  // the previous slab is consumed
         for (int i = threadIdx.x; i < SZ * SX; i += NT) {
@@ -526,9 +530,21 @@ __global__ void __launch_bounds__((Gath<B, R>::NT)) bank_gather_kernel(BankArgs 
     if (act) {
         const int64_t o0 = ((int64_t)zt * a.ny + y) * a.nx + x;
         const int64_t nxy = (int64_t)a.nx * a.ny;
+        double *out = a.n_split > 1 ? a.part + (int64_t)pt * a.n : a.c_out;
 #pragma unroll
         for (int k = 0; k < ZB; ++k)
-            if (zt + k < a.nz) a.c_out[o0 + k * nxy] = acc[k];
+            if (zt + k < a.nz) out[o0 + k * nxy] = acc[k];
+    }
+}
+
+// The parts of every cell, in order.
+__global__ void __launch_bounds__(256) bank_sum_kernel(const double *__restrict__ part, int n_split, int64_t n,
+                                                       double *__restrict__ out)
+{
+    for (int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        double s = part[i];
+        for (int q = 1; q < n_split; ++q) s += part[(int64_t)q * n + i];
+        out[i] = s;
     }
 }
 
@@ -536,8 +552,13 @@ template <typename B, int R>
 static hipError_t launch_gather_r(const BankArgs &a, hipStream_t st)
 {
     using G_ = Gath<B, R>;
-    const dim3 grid((unsigned)((a.nx + G_::TX - 1) / G_::TX), (unsigned)a.ny, (unsigned)((a.nz + G_::TZ - 1) / G_::TZ));
+    const dim3 grid((unsigned)((a.nx + G_::TX - 1) / G_::TX), (unsigned)a.ny,
+                    (unsigned)((a.nz + G_::TZ - 1) / G_::TZ * a.n_split));
     hipLaunchKernelGGL((bank_gather_kernel<B, R>), grid, dim3(G_::NT), 0, st, a);
+    if (a.n_split > 1) {
+        const unsigned g = (unsigned)std::min<int64_t>((a.n + 255) / 256, 8192);
+        hipLaunchKernelGGL(bank_sum_kernel, dim3(g), dim3(256), 0, st, a.part, a.n_split, a.n, a.c_out);
+    }
     return hipGetLastError();
 }
 
@@ -567,6 +588,25 @@ int64_t bank_elems(int nx, int ny, int nz, int r, int elem_bytes)
 {
     const int64_t w = 2 * r + 1;
     return w * w * w * bank_plane_elems(nx, ny, nz, 16 / elem_bytes);
+}
+
+// Parts that the source rows (offsets oy) of a tile are cut into: a wave keeps
+// W KB of bank reads in flight and waits for them (W times per row), so a small
+// grid needs more workgroups than it has tiles: up to BANK_GROUPS, about what
+// 256 CUs hold at once.  The parts are summed in order by a second launch.
+// Measured, 50 applies with the bank's generation (2 sub-steps), ms, whole /
+// split: FP16 20 x 18 x 16 r = 8 19.8 / 2.6, 24^3 r = 3 2.46 / 0.85, 56 x 48 x 52
+// r = 8 36.6 / 24.4, 70 x 64 x 64 57.7 / 54.5; FP32 56 x 48 x 52 36.7 / 35.8; a
+// target of 256 or 1024 groups: 25.7 and 25.3 for the 24.4.
+constexpr int BANK_GROUPS = 768;
+
+int bank_split(int prec, int r, int nx, int ny, int nz)
+{
+    const int zb = 16 / (int)bank_elem_bytes(prec), tz = FDIRW_GATHER_TZW * zb;
+    const int64_t groups = (int64_t)((nx + 63) / 64) * ny * ((nz + tz - 1) / tz);
+    const int w = 2 * r + 1;
+    const int rows = (int)std::max<int64_t>(1, w * groups / BANK_GROUPS);   // source rows per part
+    return rows >= w ? 1 : (w + rows - 1) / rows;
 }
 
 hipError_t launch_bank_apply(int prec, int r, const BankArgs &a, hipStream_t st)

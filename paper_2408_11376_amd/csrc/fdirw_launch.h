@@ -68,6 +68,8 @@ struct BankArgs {
     const double *c_in;
     double *c_out;            // every cell written
     double *chat;             // scratch of bank_chat_elems() doubles
+    int n_split;              // bank_split(): parts the source rows of a cell are cut into
+    double *part;             // scratch of n_split n doubles (n_split > 1 only)
 };
 
 // Coarse-mesh FDiRW (fdirw_coarse.hip).
@@ -161,6 +163,7 @@ hipError_t launch_window_flat(int mode, int r, const WindowArgs &a, hipStream_t 
 hipError_t launch_coarse_flat(int sink, int r, const CoarseGenArgs &a, hipStream_t st);
 hipError_t launch_bank_apply(int prec, int r, const BankArgs &a, hipStream_t st);
 int64_t bank_chat_elems(int nx, int ny, int nz, int r);
+int bank_split(int prec, int r, int nx, int ny, int nz);
 hipError_t launch_bank_gather(int prec, int r, const BankArgs &a, hipStream_t st);   // a.chat given
 hipError_t launch_coarse_nodes(const uint8_t *label, const CoarseTable &tab, int nx, int ny, int nz, int B,
                                int ncx, int ncy, int *node, double *count, hipStream_t st);

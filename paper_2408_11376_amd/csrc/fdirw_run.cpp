@@ -41,6 +41,12 @@ int run_one(const fdirw_domain *d, const fdirw_opts *o, int n_steps, double *c, 
             ensure(dc.bank_chat, (size_t)n_chat * sizeof(double)) != FDIRW_OK)
             use_bank = false;
     }
+    // the parts of the apply's sums, within the budget too
+    int n_split = use_bank ? bank_split(o->prec, d->r, d->nx, d->ny, d->nz) : 1;
+    const size_t part_bytes = (size_t)n_split * (size_t)n * sizeof(double);
+    if (n_split > 1 && (bank_bytes + (double)part_bytes > (double)o->bank_budget_bytes ||
+                        ensure(dc.bank_part, part_bytes) != FDIRW_OK))
+        n_split = 1;
     double kmin = INFINITY, kmax = -INFINITY;
     if (use_bank) {
         // entries P[o][x] whose source x - o lies outside the domain are never
@@ -89,6 +95,8 @@ int run_one(const fdirw_domain *d, const fdirw_opts *o, int n_steps, double *c, 
             b.mass = (const double *)dc.bank_mass.p;
             b.c_in = cur; b.c_out = nxt;
             b.chat = (double *)dc.bank_chat.p;
+            b.n_split = n_split;
+            b.part = (double *)dc.bank_part.p;
             EventPair ev;
             if (sst && e == hipSuccess) e = ev.create();
             if (sst && e == hipSuccess) e = hipEventRecord(ev.a, stream);
