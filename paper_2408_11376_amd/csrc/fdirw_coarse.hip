@@ -16,10 +16,11 @@
 
 namespace fdirw {
 
-// node[i] = block index of cell i if its phase is grouped, else -1; count[I]
-// += 1 for every grouped cell of block I (exact in FP64).
+// node[i] = block index of cell i if its phase is grouped, else -1; role[i] =
+// CELL_*; count[I] += 1 for every grouped cell of block I (exact in FP64).
 __global__ void coarse_nodes_kernel(const uint8_t *__restrict__ label, CoarseTable tab, int nx, int ny, int nz,
-                                    int B, int ncx, int ncy, int *__restrict__ node, double *__restrict__ count)
+                                    int B, int ncx, int ncy, int *__restrict__ node, uint8_t *__restrict__ role,
+                                    double *__restrict__ count)
 {
     const int64_t n = (int64_t)nx * ny * nz;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -34,6 +35,7 @@ __global__ void coarse_nodes_kernel(const uint8_t *__restrict__ label, CoarseTab
             atomicAdd(&count[v], 1.0);
         }
         node[i] = v;
+        role[i] = v >= 0 ? CELL_GROUPED : v == COARSE_RESERVOIR ? CELL_RESERVOIR : CELL_OUTSIDE;
     }
 }
 
@@ -384,13 +386,13 @@ __device__ __forceinline__ typename CoarseArith<A>::Acc coarse_bc_term(typename 
 // Eq. 13 on the coarse grid padded by K, for grids where most blocks hold
 // grouped cells.  One workgroup per (by, bz) row of blocks: each thread sums
 // one fine x column over the block's B x B (z, y) rows (coalesced across the
-// threads, eight loads in flight), then one thread per block adds its B
+// threads, UNR loads in flight), then one thread per block adds its B
 // columns in x order: a fixed order, so the mapping is deterministic.  Blocks
 // without grouped cells read nothing and keep the 0 written when the handle
 // was built, as does the halo.
-template <typename TC>
+template <typename TC, int UNR>
 __global__ void __launch_bounds__(256) coarse_map_rows_kernel(const double *__restrict__ c,
-                                                             const int *__restrict__ node,
+                                                             const uint8_t *__restrict__ role,
                                                              const double *__restrict__ count, int nx, int ny, int nz,
                                                              int B, int ncx, int ncy, CoarsePad pad,
                                                              TC *__restrict__ cpad)
@@ -407,23 +409,23 @@ __global__ void __launch_bounds__(256) coarse_map_rows_kernel(const double *__re
         const bool used = threadIdx.x < nbk * B && cnt[xb0 + threadIdx.x / B] > 0.0;
         if (used && x < nx) {
             const int ny_b = y1 - y0, n_q = (z1 - z0) * ny_b;
-            for (int q0 = 0; q0 < n_q; q0 += 8) {
-                int64_t at[8];
-                int nd[8];
-                double v[8];
+            for (int q0 = 0; q0 < n_q; q0 += UNR) {
+                int64_t at[UNR];
+                uint8_t nd[UNR];
+                double v[UNR];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
+                for (int u = 0; u < UNR; ++u) {
                     const int q = q0 + u < n_q ? q0 + u : n_q - 1;
                     at[u] = ((int64_t)(z0 + q / ny_b) * ny + (y0 + q % ny_b)) * nx + x;
-                    nd[u] = node[at[u]];
+                    nd[u] = role[at[u]];
                 }
-                // values loaded with their node indices (every at[] is a cell
+                // values loaded with their roles (every at[] is a cell
                 // of the domain), only the grouped ones added
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = c[at[u]];
+                for (int u = 0; u < UNR; ++u) v[u] = c[at[u]];
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (q0 + u < n_q && nd[u] >= 0) s += v[u];
+                for (int u = 0; u < UNR; ++u)
+                    if (q0 + u < n_q && nd[u] == CELL_GROUPED) s += v[u];
             }
         }
         __syncthreads();                                          // col of the previous pass is read
@@ -713,6 +715,49 @@ __global__ void coarse_remap_kernel(const double *__restrict__ c_in, const int *
     }
 }
 
+// The same for large grids, bound by memory: a cell's node follows from its
+// position, so only its role (1 byte) is read instead of the node index (4).  A
+// workgroup takes REMAP_ROWS rows of x, a thread the same x of each: one division
+// by B per thread, the rows' blocks are uniform, and the rows' loads are in
+// flight together.  It pays where the two fields and the indices (20 bytes per
+// cell) outgrow the 256 MB last-level cache.  Measured (us per coarse step,
+// by index / by role): 300 x 256 x 256 130 / 118, 256 x 256 x 200 70.0 / 63.7,
+// 192^3 43.6 / 43.5, 97 x 91 x 88 16.7 / 18.3.
+constexpr int REMAP_ROWS = 4;
+constexpr int REMAP_MIN_NX = 40;                // narrower rows leave the lanes idle
+constexpr int64_t REMAP_MIN_CELLS = 1 << 23;
+
+__global__ void __launch_bounds__(256) coarse_remap_rows_kernel(const double *__restrict__ c_in,
+                                                                const uint8_t *__restrict__ role,
+                                                                const double *__restrict__ cnew, int nx, int ny,
+                                                                int64_t n_rows, int B, int ncx, int ncy,
+                                                                double *__restrict__ c_out)
+{
+    const int64_t row0 = (int64_t)blockIdx.x * REMAP_ROWS;
+    const int64_t z0 = row0 / ny;
+    const int y0 = (int)(row0 - z0 * ny);
+    for (int x = threadIdx.x; x < nx; x += blockDim.x) {
+        const int bx = x / B;
+        uint8_t ro[REMAP_ROWS];
+        double v[REMAP_ROWS];
+#pragma unroll
+        for (int u = 0; u < REMAP_ROWS; ++u)
+            ro[u] = row0 + u < n_rows ? role[(row0 + u) * nx + x] : CELL_RESERVOIR;
+        int y = y0;
+        int64_t z = z0;
+#pragma unroll
+        for (int u = 0; u < REMAP_ROWS; ++u) {
+            v[u] = 0.0;
+            if (ro[u] == CELL_GROUPED) v[u] = cnew[((z / B) * ncy + y / B) * ncx + bx];
+            else if (ro[u] == CELL_OUTSIDE) v[u] = c_in[(row0 + u) * nx + x];
+            if (++y == ny) { y = 0; ++z; }
+        }
+#pragma unroll
+        for (int u = 0; u < REMAP_ROWS; ++u)
+            if (row0 + u < n_rows) c_out[(row0 + u) * nx + x] = v[u];
+    }
+}
+
 // c[i] = v on the far-field cells.
 __global__ void coarse_fill_reservoir_kernel(const int *__restrict__ node, int64_t n, double v, double *__restrict__ c)
 {
@@ -770,10 +815,10 @@ static unsigned grid_for(int64_t n)
 }
 
 hipError_t launch_coarse_nodes(const uint8_t *label, const CoarseTable &tab, int nx, int ny, int nz, int B,
-                               int ncx, int ncy, int *node, double *count, hipStream_t st)
+                               int ncx, int ncy, int *node, uint8_t *role, double *count, hipStream_t st)
 {
     hipLaunchKernelGGL(coarse_nodes_kernel, dim3(grid_for((int64_t)nx * ny * nz)), dim3(256), 0, st, label, tab,
-                       nx, ny, nz, B, ncx, ncy, node, count);
+                       nx, ny, nz, B, ncx, ncy, node, role, count);
     return hipGetLastError();
 }
 
@@ -934,14 +979,24 @@ hipError_t launch_coarse_finalize(int prec, const double *S, const double *count
 }
 
 template <typename TC>
-static hipError_t coarse_map_t(const double *c, const int *node, const double *count, int nx, int ny, int nz, int B,
-                               int ncx, int ncy, int ncz, int K, TC *cpad, hipStream_t st, int dense,
-                               const int *used, int64_t n_used)
+static hipError_t coarse_map_t(const double *c, const int *node, const uint8_t *role, const double *count, int nx,
+                               int ny, int nz, int B, int ncx, int ncy, int ncz, int K, TC *cpad, hipStream_t st,
+                               int dense, const int *used, int64_t n_used)
 {
     if (dense && B <= 256) {
         if (ncx <= 0 || ncy <= 0 || ncz <= 0) return hipSuccess;
-        hipLaunchKernelGGL(coarse_map_rows_kernel<TC>, dim3((unsigned)ncy, (unsigned)ncz), dim3(256), 0, st, c, node,
-                           count, nx, ny, nz, B, ncx, ncy, coarse_pad(ncx, ncy, ncz, K), cpad);
+        // loads in flight per thread: 5 or 8, whichever wastes fewer on the
+        // last round of a block's B^2 rows.  Measured (us per coarse step, 5 /
+        // 8): B = 5, 192^3 43.6 / 45.3, 80 x 64 x 72 14.4 / 14.9; B = 3, 41 x 200
+        // x 200 23.1 / 25.4; B = 4, 97 x 91 x 88 16.7 / 15.8; B = 8, 256 x 256 x
+        // 200 70.0 / 68.7
+        const int n_q = B * B;
+        const auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, dim3((unsigned)ncy, (unsigned)ncz), dim3(256), 0, st, c, role, count, nx, ny, nz,
+                               B, ncx, ncy, coarse_pad(ncx, ncy, ncz, K), cpad);
+        };
+        if (ru(n_q, 5) < ru(n_q, 8)) go(coarse_map_rows_kernel<TC, 5>);
+        else go(coarse_map_rows_kernel<TC, 8>);
         return hipGetLastError();
     }
     const int64_t waves = used ? n_used : (int64_t)ncx * ncy * ncz;
@@ -952,28 +1007,28 @@ static hipError_t coarse_map_t(const double *c, const int *node, const double *c
     return hipGetLastError();
 }
 
-hipError_t launch_coarse_map(const double *c, const int *node, const double *count, int nx, int ny, int nz, int B,
-                             int ncx, int ncy, int ncz, int K, double *cpad, hipStream_t st, int dense,
-                             const int *used, int64_t n_used)
+hipError_t launch_coarse_map(const double *c, const int *node, const uint8_t *role, const double *count, int nx,
+                             int ny, int nz, int B, int ncx, int ncy, int ncz, int K, double *cpad, hipStream_t st,
+                             int dense, const int *used, int64_t n_used)
 {
-    return coarse_map_t<double>(c, node, count, nx, ny, nz, B, ncx, ncy, ncz, K, cpad, st, dense, used, n_used);
+    return coarse_map_t<double>(c, node, role, count, nx, ny, nz, B, ncx, ncy, ncz, K, cpad, st, dense, used, n_used);
 }
 
-hipError_t launch_coarse_map_arith(int arith, const double *c, const int *node, const double *count, int nx, int ny,
-                                   int nz, int B, int ncx, int ncy, int ncz, int K, void *cpad, hipStream_t st,
-                                   int dense, const int *used, int64_t n_used)
+hipError_t launch_coarse_map_arith(int arith, const double *c, const int *node, const uint8_t *role,
+                                   const double *count, int nx, int ny, int nz, int B, int ncx, int ncy, int ncz,
+                                   int K, void *cpad, hipStream_t st, int dense, const int *used, int64_t n_used)
 {
     switch (arith) {
     case COARSE_FP64:
-        return coarse_map_t<double>(c, node, count, nx, ny, nz, B, ncx, ncy, ncz, K, (double *)cpad, st, dense, used,
-                                    n_used);
+        return coarse_map_t<double>(c, node, role, count, nx, ny, nz, B, ncx, ncy, ncz, K, (double *)cpad, st, dense,
+                                    used, n_used);
     case COARSE_FP32:
-        return coarse_map_t<float>(c, node, count, nx, ny, nz, B, ncx, ncy, ncz, K, (float *)cpad, st, dense, used,
-                                   n_used);
+        return coarse_map_t<float>(c, node, role, count, nx, ny, nz, B, ncx, ncy, ncz, K, (float *)cpad, st, dense,
+                                   used, n_used);
     case COARSE_MIXED:
     case COARSE_FP16:
-        return coarse_map_t<_Float16>(c, node, count, nx, ny, nz, B, ncx, ncy, ncz, K, (_Float16 *)cpad, st, dense,
-                                      used, n_used);
+        return coarse_map_t<_Float16>(c, node, role, count, nx, ny, nz, B, ncx, ncy, ncz, K, (_Float16 *)cpad, st,
+                                      dense, used, n_used);
     default: return hipErrorInvalidValue;
     }
 }
@@ -1135,10 +1190,18 @@ hipError_t launch_coarse_apply(int prec, const void *P, const double *cpad, int 
                                      cff_dev, list, n_list, n_split, part);
 }
 
-hipError_t launch_coarse_remap(const double *c_in, const int *node, const double *cnew, int64_t n, double *c_out,
-                               hipStream_t st)
+hipError_t launch_coarse_remap(const double *c_in, const int *node, const uint8_t *role, const double *cnew, int nx,
+                               int ny, int nz, int B, int ncx, int ncy, double *c_out, hipStream_t st)
 {
-    hipLaunchKernelGGL(coarse_remap_kernel, dim3(grid_for(n)), dim3(256), 0, st, c_in, node, cnew, n, c_out);
+    const int64_t n_rows = (int64_t)ny * nz, n = n_rows * nx;
+    const int64_t grid = (n_rows + REMAP_ROWS - 1) / REMAP_ROWS;
+    if (n >= REMAP_MIN_CELLS && nx >= REMAP_MIN_NX && grid <= INT32_MAX) {
+        const int nt = nx < 256 ? ru(nx, 64) : 256;
+        hipLaunchKernelGGL(coarse_remap_rows_kernel, dim3((unsigned)grid), dim3(nt), 0, st, c_in, role, cnew, nx, ny,
+                           n_rows, B, ncx, ncy, c_out);
+    } else {
+        hipLaunchKernelGGL(coarse_remap_kernel, dim3(grid_for(n)), dim3(256), 0, st, c_in, node, cnew, n, c_out);
+    }
     return hipGetLastError();
 }
 

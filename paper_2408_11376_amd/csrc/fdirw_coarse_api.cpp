@@ -34,6 +34,7 @@ struct Coarse {
     int64_t plane = 0;              // elements of one offset plane of P (bank layout; compact for K >= 5)
     std::vector<int> slot;          // K >= 5: chunk -> its place in P's compact layout (-1: not stored)
     void *node = nullptr;           // int [N]
+    void *role = nullptr;           // uint8_t [N]: CELL_*
     void *count = nullptr;          // double [n_nodes]
     void *P = nullptr;              // esz * (2K+1)^3 * plane bytes
     void *cpad = nullptr;           // double [coarse_pad(...).size]: the padded coarse grid
@@ -58,7 +59,7 @@ struct Coarse {
 
     ~Coarse()
     {
-        for (void *p : {node, count, P, cpad, cnew, part, pbc, list, apart, used, cpad_lp, efrag, ecpad, ecmax})
+        for (void *p : {node, role, count, P, cpad, cnew, part, pbc, list, apart, used, cpad_lp, efrag, ecpad, ecmax})
             if (p) (void)hipFree(p);
     }
     int nb() const { return (2 * K + 1) * (2 * K + 1) * (2 * K + 1); }
@@ -263,6 +264,7 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
         rc = coef_buffers(d, prec == FDIRW_FP64 ? FDIRW_FP64 : FDIRW_FP32, st, dc, &g, &lam);
         if (!rc && velocity) rc = flow_stable(d, prec == FDIRW_FP64, lam, velocity, g.dt, st, dc);
         if (!rc) rc = coarse_alloc(&h->node, (size_t)h->n * sizeof(int));
+        if (!rc) rc = coarse_alloc(&h->role, (size_t)h->n);
         if (!rc) rc = coarse_alloc(&h->count, (size_t)h->n_nodes * sizeof(double));
         if (!rc) rc = coarse_alloc(&h->cpad, (size_t)n_pad * sizeof(double));
         if (!rc) rc = coarse_alloc(&h->cnew, (size_t)h->n_nodes * sizeof(double));
@@ -288,7 +290,7 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
         if (e == hipSuccess) e = launch_fill(S, (int64_t)nb * h->n_nodes, 0.0, st);
         if (e == hipSuccess)
             e = launch_coarse_nodes(d->label, tab, d->nx, d->ny, d->nz, block, h->ncx, h->ncy, (int *)h->node,
-                                    (double *)h->count, st);
+                                    (uint8_t *)h->role, (double *)h->count, st);
         if (e == hipSuccess) {
             // the mapping's shape: by rows of blocks when most nodes hold cells
             std::vector<double> hc((size_t)h->n_nodes);
@@ -458,8 +460,8 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
             e = launch_coarse_pbc_fd(prec == FDIRW_FP64, lam, (const int *)h->node, d->nx, d->ny, d->nz, d->n_sub,
                                      velocity, g.dt / d->h, fa, fa + h->n, &field, st);
             if (e == hipSuccess)
-                e = launch_coarse_map(field, (const int *)h->node, (const double *)h->count, h->nx, h->ny, h->nz,
-                                      block, h->ncx, h->ncy, h->ncz, h->K, (double *)h->pbc, st, h->dense,
+                e = launch_coarse_map(field, (const int *)h->node, (const uint8_t *)h->role,
+                                      (const double *)h->count, h->nx, h->ny, h->nz, block, h->ncx, h->ncy, h->ncz, h->K, (double *)h->pbc, st, h->dense,
                                       (const int *)h->used, h->n_used);
             (void)hipStreamSynchronize(st);
             (void)hipFree(fa);
@@ -503,14 +505,16 @@ int coarse_apply_all(Coarse *h, const double *c_in, double *c_out, const double 
     if (ks && e == hipSuccess) e = hipEventRecord(ev.a, st);
     void *cp = h->arith == COARSE_FP64 ? h->cpad : h->cpad_lp;
     if (e == hipSuccess)
-        e = launch_coarse_map_arith(h->arith, c_in, (const int *)h->node, (const double *)h->count, h->nx, h->ny,
-                                    h->nz, h->B, h->ncx, h->ncy, h->ncz, h->K, cp, st, h->dense,
+        e = launch_coarse_map_arith(h->arith, c_in, (const int *)h->node, (const uint8_t *)h->role,
+                                    (const double *)h->count, h->nx, h->ny, h->nz, h->B, h->ncx, h->ncy, h->ncz, h->K, cp, st, h->dense,
                                     (const int *)h->used, h->n_used);
     if (e == hipSuccess)
         e = launch_coarse_apply_arith(h->arith, h->prec, h->P, cp, h->ncx, h->ncy, h->ncz, h->K, pbc, c_ff,
                                       (const double *)h->count, (double *)h->cnew, st, cff_dev,
                                       (const int *)h->list, h->n_list, h->n_split, (double *)h->apart);
-    if (e == hipSuccess) e = launch_coarse_remap(c_in, (const int *)h->node, (const double *)h->cnew, h->n, c_out, st);
+    if (e == hipSuccess)
+        e = launch_coarse_remap(c_in, (const int *)h->node, (const uint8_t *)h->role, (const double *)h->cnew, h->nx,
+                                h->ny, h->nz, h->B, h->ncx, h->ncy, c_out, st);
     if (ks && e == hipSuccess) e = hipEventRecord(ev.b, st);
     if (e != hipSuccess) return hip_fail(e, "coarse step launch");
     if (ks) {
@@ -534,8 +538,8 @@ int coarse_map_apply(void *handle, const double *c_in, const double *cff_dev, hi
     int rc = check_handle(h);
     if (rc) return rc;
     void *cp = h->arith == COARSE_FP64 ? h->cpad : h->cpad_lp;
-    hipError_t e = launch_coarse_map_arith(h->arith, c_in, (const int *)h->node, (const double *)h->count, h->nx,
-                                           h->ny, h->nz, h->B, h->ncx, h->ncy, h->ncz, h->K, cp, st, h->dense,
+    hipError_t e = launch_coarse_map_arith(h->arith, c_in, (const int *)h->node, (const uint8_t *)h->role,
+                                           (const double *)h->count, h->nx, h->ny, h->nz, h->B, h->ncx, h->ncy, h->ncz, h->K, cp, st, h->dense,
                                            (const int *)h->used, h->n_used);
     if (e == hipSuccess)
         e = launch_coarse_apply_arith(h->arith, h->prec, h->P, cp, h->ncx, h->ncy, h->ncz, h->K,

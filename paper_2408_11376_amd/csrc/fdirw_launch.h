@@ -78,6 +78,9 @@ struct CoarseTable {
     uint8_t reservoir[256];   // 1 if the phase is the far-field boundary (Dirichlet cells)
 };
 
+// role[] of a cell: in a group, in none (keeps its value), far-field boundary.
+enum : uint8_t { CELL_GROUPED = 0, CELL_OUTSIDE = 1, CELL_RESERVOIR = 2 };
+
 // node[] values of the cells that are in no group.
 constexpr int COARSE_OUTSIDE = -1;     // keeps its value
 constexpr int COARSE_RESERVOIR = -2;   // far-field boundary cell
@@ -166,7 +169,7 @@ int64_t bank_chat_elems(int nx, int ny, int nz, int r);
 int bank_split(int prec, int r, int nx, int ny, int nz);
 hipError_t launch_bank_gather(int prec, int r, const BankArgs &a, hipStream_t st);   // a.chat given
 hipError_t launch_coarse_nodes(const uint8_t *label, const CoarseTable &tab, int nx, int ny, int nz, int B,
-                               int ncx, int ncy, int *node, double *count, hipStream_t st);
+                               int ncx, int ncy, int *node, uint8_t *role, double *count, hipStream_t st);
 hipError_t launch_coarse_window(int fp64, int sink, int r, const CoarseGenArgs &a, hipStream_t st);
 // Node windows of the coarse build (radius beyond the per-source kernels).
 struct NodeWinArgs {
@@ -246,8 +249,9 @@ __host__ __device__ inline int64_t coarse_pad_at(const CoarsePad &p, int x, int 
 // writes the nodes with grouped cells only: cpad must be zeroed once; dense:
 // one workgroup per row of blocks (most blocks hold grouped cells), else one
 // wave per node
-hipError_t launch_coarse_map(const double *c, const int *node, const double *count, int nx, int ny, int nz, int B,
-                             int ncx, int ncy, int ncz, int K, double *cpad, hipStream_t st, int dense,
+hipError_t launch_coarse_map(const double *c, const int *node, const uint8_t *role, const double *count, int nx,
+                             int ny, int nz, int B, int ncx, int ncy, int ncz, int K, double *cpad, hipStream_t st,
+                             int dense,
                              const int *used = nullptr, int64_t n_used = 0);   // used: the nodes with cells
 hipError_t launch_flow_window(int fp64, int r, const FlowArgs &a, hipStream_t st);
 // FP32 flow window kernels in the flat layout (r = 4..8)
@@ -274,9 +278,9 @@ hipError_t launch_coarse_apply(int prec, const void *P, const double *cpad, int 
 enum CoarseArithId : int { COARSE_FP64 = 0, COARSE_FP32 = 1, COARSE_MIXED = 2, COARSE_FP16 = 3 };
 bool coarse_arith_supported(int arith, int prec);               // P storage the arithmetic takes
 size_t coarse_c_bytes(int arith);                               // bytes of one padded C value
-hipError_t launch_coarse_map_arith(int arith, const double *c, const int *node, const double *count, int nx, int ny,
-                                   int nz, int B, int ncx, int ncy, int ncz, int K, void *cpad, hipStream_t st,
-                                   int dense, const int *used = nullptr, int64_t n_used = 0);
+hipError_t launch_coarse_map_arith(int arith, const double *c, const int *node, const uint8_t *role,
+                                   const double *count, int nx, int ny, int nz, int B, int ncx, int ncy, int ncz,
+                                   int K, void *cpad, hipStream_t st, int dense, const int *used = nullptr, int64_t n_used = 0);
 hipError_t launch_coarse_apply_arith(int arith, int prec, const void *P, const void *cpad, int ncx, int ncy, int ncz,
                                      int K, const double *pbc_pad, double c_ff, const double *count, double *cnew,
                                      hipStream_t st, const double *cff_dev, const int *list, int64_t n_list,
@@ -315,8 +319,8 @@ hipError_t launch_ensemble_apply(const void *frag, const void *cpad, int n_ens, 
 int coarse_apply_zb(int prec);                                  // nodes per chunk
 int coarse_apply_split(int K, int64_t n_chunks);                // the number of pair ranges (1 below the chunk K)
 int64_t coarse_apply_part_elems(int prec, int K, int64_t n_chunks);
-hipError_t launch_coarse_remap(const double *c_in, const int *node, const double *cnew, int64_t n, double *c_out,
-                               hipStream_t st);
+hipError_t launch_coarse_remap(const double *c_in, const int *node, const uint8_t *role, const double *cnew, int nx,
+                               int ny, int nz, int B, int ncx, int ncy, double *c_out, hipStream_t st);
 // Integrated near-field solver (fdirw_mp.hip).  Cell roles come from the
 // coarse node index: >= 0 near-field liquid, COARSE_RESERVOIR far field,
 // COARSE_OUTSIDE solid.  Per-phase tables live in device memory, not in
