@@ -10,6 +10,7 @@
 //   mapping    C = mean of c over each group, on the coarse grid padded by K
 //   FDiRW      C' = P C (row form: 2K+1 threads per node, one per z offset)
 //   remapping  c'(i) = C'(node of i); cells outside every group keep c(i)
+#include "fdirw_balance.h"
 #include "fdirw_device.h"
 #include "fdirw_host.h"
 #include "fdirw_launch.h"
@@ -394,11 +395,18 @@ template <typename TC, int UNR>
 __global__ void __launch_bounds__(256) coarse_map_rows_kernel(const double *__restrict__ c,
                                                              const uint8_t *__restrict__ role,
                                                              const double *__restrict__ count, int nx, int ny, int nz,
-                                                             int B, int ncx, int ncy, CoarsePad pad,
+                                                             int B, int ncx, int ncy, CoarsePad pad, BalanceArgs fin,
                                                              TC *__restrict__ cpad)
 {
     __shared__ double col[256];
     const int by = blockIdx.x, bz = blockIdx.y;
+    if (by >= ncy) {                                             // the workgroups past the grid
+        if (fin.part && bz == 0) {
+            __shared__ double col2[256];
+            balance_finish(fin, col, col2);
+        }
+        return;
+    }
     const int y0 = by * B, z0 = bz * B;
     const int y1 = min(ny, y0 + B), z1 = min(nz, z0 + B);
     const double *cnt = count + ((int64_t)bz * ncy + by) * ncx;
@@ -455,8 +463,14 @@ __global__ void __launch_bounds__(MAP_NT) coarse_map_kernel(const double *__rest
                                                             const double *__restrict__ count, int nx, int ny, int nz,
                                                             int B, int ncx, int ncy, int ncz, CoarsePad pad,
                                                             TC *__restrict__ cpad, const int *__restrict__ used,
-                                                            int64_t n_used)
+                                                            int64_t n_used, BalanceArgs fin)
 {
+    static_assert(MAP_NT == BALANCE_NT, "balance workgroup");
+    if (fin.part && blockIdx.x == gridDim.x - 1) {               // one workgroup more than the nodes need
+        __shared__ double sa[MAP_NT], sb[MAP_NT];
+        balance_finish(fin, sa, sb);
+        return;
+    }
     const int64_t wv = blockIdx.x * (int64_t)(MAP_NT / 64) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int64_t n_nodes = (int64_t)ncx * ncy * ncz;
@@ -981,8 +995,9 @@ hipError_t launch_coarse_finalize(int prec, const double *S, const double *count
 template <typename TC>
 static hipError_t coarse_map_t(const double *c, const int *node, const uint8_t *role, const double *count, int nx,
                                int ny, int nz, int B, int ncx, int ncy, int ncz, int K, TC *cpad, hipStream_t st,
-                               int dense, const int *used, int64_t n_used)
+                               int dense, const int *used, int64_t n_used, const BalanceArgs &fin = {})
 {
+    const int more = fin.part ? 1 : 0;                            // a workgroup for the balance
     if (dense && B <= 256) {
         if (ncx <= 0 || ncy <= 0 || ncz <= 0) return hipSuccess;
         // loads in flight per thread: 5 or 8, whichever wastes fewer on the
@@ -992,18 +1007,18 @@ static hipError_t coarse_map_t(const double *c, const int *node, const uint8_t *
         // 200 70.0 / 68.7
         const int n_q = B * B;
         const auto go = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3((unsigned)ncy, (unsigned)ncz), dim3(256), 0, st, c, role, count, nx, ny, nz,
-                               B, ncx, ncy, coarse_pad(ncx, ncy, ncz, K), cpad);
+            hipLaunchKernelGGL(kern, dim3((unsigned)(ncy + more), (unsigned)ncz), dim3(256), 0, st, c, role, count, nx, ny, nz,
+                               B, ncx, ncy, coarse_pad(ncx, ncy, ncz, K), fin, cpad);
         };
         if (ru(n_q, 5) < ru(n_q, 8)) go(coarse_map_rows_kernel<TC, 5>);
         else go(coarse_map_rows_kernel<TC, 8>);
         return hipGetLastError();
     }
     const int64_t waves = used ? n_used : (int64_t)ncx * ncy * ncz;
-    const int64_t g = (waves + MAP_NT / 64 - 1) / (MAP_NT / 64);
+    const int64_t g = (waves + MAP_NT / 64 - 1) / (MAP_NT / 64) + more;
     if (g <= 0) return hipSuccess;
     hipLaunchKernelGGL(coarse_map_kernel<TC>, dim3((unsigned)g), dim3(MAP_NT), 0, st, c, node, count, nx, ny, nz, B,
-                       ncx, ncy, ncz, coarse_pad(ncx, ncy, ncz, K), cpad, used, n_used);
+                       ncx, ncy, ncz, coarse_pad(ncx, ncy, ncz, K), cpad, used, n_used, fin);
     return hipGetLastError();
 }
 
@@ -1016,19 +1031,19 @@ hipError_t launch_coarse_map(const double *c, const int *node, const uint8_t *ro
 
 hipError_t launch_coarse_map_arith(int arith, const double *c, const int *node, const uint8_t *role,
                                    const double *count, int nx, int ny, int nz, int B, int ncx, int ncy, int ncz,
-                                   int K, void *cpad, hipStream_t st, int dense, const int *used, int64_t n_used)
+                                   int K, void *cpad, hipStream_t st, int dense, const int *used, int64_t n_used, const BalanceArgs &fin)
 {
     switch (arith) {
     case COARSE_FP64:
         return coarse_map_t<double>(c, node, role, count, nx, ny, nz, B, ncx, ncy, ncz, K, (double *)cpad, st, dense,
-                                    used, n_used);
+                                    used, n_used, fin);
     case COARSE_FP32:
         return coarse_map_t<float>(c, node, role, count, nx, ny, nz, B, ncx, ncy, ncz, K, (float *)cpad, st, dense,
-                                   used, n_used);
+                                   used, n_used, fin);
     case COARSE_MIXED:
     case COARSE_FP16:
         return coarse_map_t<_Float16>(c, node, role, count, nx, ny, nz, B, ncx, ncy, ncz, K, (_Float16 *)cpad, st,
-                                      dense, used, n_used);
+                                      dense, used, n_used, fin);
     default: return hipErrorInvalidValue;
     }
 }

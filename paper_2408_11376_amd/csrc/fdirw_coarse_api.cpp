@@ -461,7 +461,8 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
                                      velocity, g.dt / d->h, fa, fa + h->n, &field, st);
             if (e == hipSuccess)
                 e = launch_coarse_map(field, (const int *)h->node, (const uint8_t *)h->role,
-                                      (const double *)h->count, h->nx, h->ny, h->nz, block, h->ncx, h->ncy, h->ncz, h->K, (double *)h->pbc, st, h->dense,
+                                      (const double *)h->count, h->nx, h->ny, h->nz, block, h->ncx, h->ncy,
+                                      h->ncz, h->K, (double *)h->pbc, st, h->dense,
                                       (const int *)h->used, h->n_used);
             (void)hipStreamSynchronize(st);
             (void)hipFree(fa);
@@ -506,8 +507,8 @@ int coarse_apply_all(Coarse *h, const double *c_in, double *c_out, const double 
     void *cp = h->arith == COARSE_FP64 ? h->cpad : h->cpad_lp;
     if (e == hipSuccess)
         e = launch_coarse_map_arith(h->arith, c_in, (const int *)h->node, (const uint8_t *)h->role,
-                                    (const double *)h->count, h->nx, h->ny, h->nz, h->B, h->ncx, h->ncy, h->ncz, h->K, cp, st, h->dense,
-                                    (const int *)h->used, h->n_used);
+                                    (const double *)h->count, h->nx, h->ny, h->nz, h->B, h->ncx, h->ncy, h->ncz,
+                                    h->K, cp, st, h->dense, (const int *)h->used, h->n_used);
     if (e == hipSuccess)
         e = launch_coarse_apply_arith(h->arith, h->prec, h->P, cp, h->ncx, h->ncy, h->ncz, h->K, pbc, c_ff,
                                       (const double *)h->count, (double *)h->cnew, st, cff_dev,
@@ -531,16 +532,18 @@ namespace fdirw {
 
 // Mapping and product of the fast step of the integrated solver, with P_BC
 // c_ff read from device memory (far-field handles); *cnew receives the node
-// values C' (the caller remaps).
-int coarse_map_apply(void *handle, const double *c_in, const double *cff_dev, hipStream_t st, const double **cnew)
+// values C' (the caller remaps).  before: the balance that gives *cff_dev, run
+// beside the mapping.
+int coarse_map_apply(void *handle, const double *c_in, const double *cff_dev, hipStream_t st, const double **cnew,
+                     const BalanceArgs &before)
 {
     Coarse *h = (Coarse *)handle;
     int rc = check_handle(h);
     if (rc) return rc;
     void *cp = h->arith == COARSE_FP64 ? h->cpad : h->cpad_lp;
     hipError_t e = launch_coarse_map_arith(h->arith, c_in, (const int *)h->node, (const uint8_t *)h->role,
-                                           (const double *)h->count, h->nx, h->ny, h->nz, h->B, h->ncx, h->ncy, h->ncz, h->K, cp, st, h->dense,
-                                           (const int *)h->used, h->n_used);
+                                           (const double *)h->count, h->nx, h->ny, h->nz, h->B, h->ncx, h->ncy, h->ncz,
+                                           h->K, cp, st, h->dense, (const int *)h->used, h->n_used, before);
     if (e == hipSuccess)
         e = launch_coarse_apply_arith(h->arith, h->prec, h->P, cp, h->ncx, h->ncy, h->ncz, h->K,
                                       h->far_field ? (const double *)h->pbc : nullptr, 0.0, (const double *)h->count,

@@ -249,6 +249,14 @@ __host__ __device__ inline int64_t coarse_pad_at(const CoarsePad &p, int x, int 
 // writes the nodes with grouped cells only: cpad must be zeroed once; dense:
 // one workgroup per row of blocks (most blocks hold grouped cells), else one
 // wave per node
+// Eq. 7 from per-workgroup partial sums (balance_finish); part null: nothing.
+struct BalanceArgs {
+    const double *part;
+    int nblk;
+    double m_total, v_ff;
+    double *cff, *hist_row;           // hist_row may be null
+};
+// fin: a balance for one more workgroup of the launch
 hipError_t launch_coarse_map(const double *c, const int *node, const uint8_t *role, const double *count, int nx,
                              int ny, int nz, int B, int ncx, int ncy, int ncz, int K, double *cpad, hipStream_t st,
                              int dense,
@@ -280,7 +288,8 @@ bool coarse_arith_supported(int arith, int prec);               // P storage the
 size_t coarse_c_bytes(int arith);                               // bytes of one padded C value
 hipError_t launch_coarse_map_arith(int arith, const double *c, const int *node, const uint8_t *role,
                                    const double *count, int nx, int ny, int nz, int B, int ncx, int ncy, int ncz,
-                                   int K, void *cpad, hipStream_t st, int dense, const int *used = nullptr, int64_t n_used = 0);
+                                   int K, void *cpad, hipStream_t st, int dense, const int *used = nullptr,
+                                   int64_t n_used = 0, const BalanceArgs &fin = {});
 hipError_t launch_coarse_apply_arith(int arith, int prec, const void *P, const void *cpad, int ncx, int ncy, int ncz,
                                      int K, const double *pbc_pad, double c_ff, const double *count, double *cnew,
                                      hipStream_t st, const double *cff_dev, const int *list, int64_t n_list,
@@ -351,8 +360,6 @@ struct MpLocalArgs {
     int solid;                        // 1: one solid sub-step and the Eq. 7 balance
     double dt_s, h;
     double *part;                     // 2 * n_tiles doubles
-    double m_total, v_ff;
-    double *cff, *hist_row;
 };
 int64_t mp_tile_count(int nx, int ny, int nz);
 hipError_t launch_mp_faces(const int *node, int nx, int ny, int nz, unsigned long long *count, hipStream_t st);
@@ -363,8 +370,9 @@ hipError_t launch_mp_tile_flags(const int *node, int nx, int ny, int nz, int *fl
 // list null: counts into cnt[6 n_tiles]; else entries at list[off[6 t + p]..]
 hipError_t launch_mp_tile_pairs(const int *node, int nx, int ny, int nz, const int *tiles, int64_t n_tiles,
                                 const int *off, uint16_t *list, int *cnt, hipStream_t st);
-// the fused local kernel, then (a.solid) the Eq. 7 finish from its partials
+// the fused local kernel; (a.solid) Eq. 7 follows from its partials
 hipError_t launch_mp_local(const MpLocalArgs &a, hipStream_t st);
+hipError_t launch_mp_finish(const BalanceArgs &b, hipStream_t st);
 // sorted lists: mode 0 active cells (not far field), mode 1 solid cells;
 // chunk_count / chunk_off hold ceil(n / MP_CHUNK) entries
 hipError_t launch_mp_list_count(const int *node, int64_t n, int mode, int *chunk_count, hipStream_t st);

@@ -7,11 +7,12 @@
 // loops of 256 threads, coalesced along x, FP64 throughout.
 #include <hip/hip_runtime.h>
 
+#include "fdirw_balance.h"
 #include "fdirw_launch.h"
 
 namespace fdirw {
 
-constexpr int MP_NT = 256;
+constexpr int MP_NT = BALANCE_NT;
 
 static unsigned mp_grid(int64_t n)
 {
@@ -208,54 +209,17 @@ __global__ void mp_solid_scatter_kernel(const int *__restrict__ sol, int64_t n_s
         field[sol[k]] = v[k];
 }
 
-// Block-wide fixed-order tree sum of two values (every thread gets them), in
-// the caller's LDS scratch (2 x MP_NT doubles).
-__device__ void mp_block_sum2_in(double &a, double &b, double *sa, double *sb)
-{
-    __syncthreads();
-    sa[threadIdx.x] = a;
-    sb[threadIdx.x] = b;
-    __syncthreads();
-    for (int w = MP_NT / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            sa[threadIdx.x] += sa[threadIdx.x + w];
-            sb[threadIdx.x] += sb[threadIdx.x + w];
-        }
-        __syncthreads();
-    }
-    a = sa[0];
-    b = sb[0];
-}
-
 __device__ void mp_block_sum2(double &a, double &b)
 {
     __shared__ double sa[MP_NT], sb[MP_NT];
     mp_block_sum2_in(a, b, sa, sb);
 }
 
-// Eq. 7 from the per-workgroup partials of the previous launch (Q_L in
-// part[0..nblk), Q_S in part[nblk..2 nblk)), one workgroup: the partials in
-// workgroup order, then c_ff = (M_total - Q_L - Q_S) / V_ff into *cff and the
-// history row.
-__global__ void __launch_bounds__(MP_NT) mp_finish_kernel(const double *__restrict__ part, int nblk, double m_total,
-                                                         double v_ff, double *__restrict__ cff,
-                                                         double *__restrict__ hist_row)
+// balance_finish as a launch of its own, one workgroup.
+__global__ void __launch_bounds__(MP_NT) mp_finish_kernel(BalanceArgs b)
 {
-    double ql = 0.0, qs = 0.0;
-    for (int k = threadIdx.x; k < nblk; k += MP_NT) {
-        ql += part[k];
-        qs += part[nblk + k];
-    }
-    mp_block_sum2(ql, qs);
-    if (threadIdx.x == 0) {
-        const double v = (m_total - ql - qs) / v_ff;
-        cff[0] = v;
-        if (hist_row) {
-            hist_row[0] = ql;
-            hist_row[1] = qs;
-            hist_row[2] = v;
-        }
-    }
+    __shared__ double sa[MP_NT], sb[MP_NT];
+    balance_finish(b, sa, sb);
 }
 
 // Eq. 7, first level, over the active list: each workgroup sums the
@@ -388,7 +352,7 @@ __device__ __forceinline__ void mp_pass(double *v, const uint16_t *pl, const uin
 // run on the box's interface pairs of each pass (listed once per handle by
 // mp_tile_pairs_kernel); one solid sub-step follows for the tile's solid cells (if
 // a.solid); the tile's cells are written to out, and (if a.solid) its Q_L /
-// Q_S partials go to a.part for mp_finish_kernel (Eq. 7).  The passes move information by at most two cells
+// Q_S partials go to a.part for balance_finish (Eq. 7).  The passes move information by at most two cells
 // per axis and the sub-step by one, so with MP_H = 3 every tile cell gets
 // exactly the values of the whole-grid passes.
 __global__ void __launch_bounds__(MP_NT) mp_local_kernel(MpLocalArgs a)
@@ -409,10 +373,11 @@ __global__ void __launch_bounds__(MP_NT) mp_local_kernel(MpLocalArgs a)
     const int n_pairs = po[6] - pbase;
     for (int m = threadIdx.x; m < n_pairs && m < MP_PAIR_CAP; m += MP_NT) pl[m] = gl[m];
     const int64_t sy = a.nx, sz = (int64_t)a.nx * a.ny;
-    // load (remapping on the fly), in rounds of ROUND cells per thread: the
-    // node indices of a round first, then its values, so that the loads of a
-    // stage are in flight together
-    constexpr int ROUND = 6;
+    // load (remapping on the fly): the node indices of all of a thread's ROUND
+    // cells first, then their values, so that the loads of a stage are in flight
+    // together and their latency is met twice per tile (in three rounds of 6
+    // cells: six times, 46.9 against 45.5 us per step of the 192^3 particle)
+    constexpr int ROUND = (MP_BOX + MP_NT - 1) / MP_NT;
     constexpr int NONE = -3;                                      // outside the domain
     for (int q0 = threadIdx.x; q0 < MP_BOX; q0 += ROUND * MP_NT) {
         int64_t gi[ROUND];
@@ -426,6 +391,7 @@ __global__ void __launch_bounds__(MP_NT) mp_local_kernel(MpLocalArgs a)
             gi[u] = in ? gz * sz + gy * sy + gx : 0;
             nd[u] = in ? a.node[gi[u]] : NONE;
         }
+        __builtin_amdgcn_sched_barrier(0);
         double val[ROUND];
         int sc[ROUND];                                            // ints: no packing, no early waits
 #pragma unroll
@@ -644,10 +610,12 @@ hipError_t launch_mp_local(const MpLocalArgs &a, hipStream_t st)
 {
     if (a.n_tiles <= 0) return hipSuccess;
     hipLaunchKernelGGL(mp_local_kernel, dim3((unsigned)a.n_tiles), dim3(MP_NT), 0, st, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !a.solid) return e;
-    hipLaunchKernelGGL(mp_finish_kernel, dim3(1), dim3(MP_NT), 0, st, (const double *)a.part, (int)a.n_tiles,
-                       a.m_total, a.v_ff, a.cff, a.hist_row);
+    return hipGetLastError();
+}
+
+hipError_t launch_mp_finish(const BalanceArgs &b, hipStream_t st)
+{
+    hipLaunchKernelGGL(mp_finish_kernel, dim3(1), dim3(MP_NT), 0, st, b);
     return hipGetLastError();
 }
 
@@ -664,9 +632,7 @@ hipError_t launch_mp_balance(const int *act, int64_t n_act, const int *node, con
     hipLaunchKernelGGL(mp_balance_kernel, dim3(nb), dim3(MP_NT), 0, st, act, n_act, node, c, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mp_finish_kernel, dim3(1), dim3(MP_NT), 0, st, (const double *)part, (int)nb, m_total, v_ff,
-                       cff, hist_row);
-    return hipGetLastError();
+    return launch_mp_finish({part, (int)nb, m_total, v_ff, cff, hist_row}, st);
 }
 
 hipError_t launch_mp_far_fill(const int *node, int64_t n, const double *cff, const double *src, double *dst,
