@@ -733,13 +733,14 @@ __global__ void coarse_remap_kernel(const double *__restrict__ c_in, const int *
 // position, so only its role (1 byte) is read instead of the node index (4).  A
 // workgroup takes REMAP_ROWS rows of x, a thread the same x of each: one division
 // by B per thread, the rows' blocks are uniform, and the rows' loads are in
-// flight together.  It pays where the two fields and the indices (20 bytes per
-// cell) outgrow the 256 MB last-level cache.  Measured (us per coarse step,
-// by index / by role): 300 x 256 x 256 130 / 118, 256 x 256 x 200 70.0 / 63.7,
-// 192^3 43.6 / 43.5, 97 x 91 x 88 16.7 / 18.3.
+// flight together.  It pays where the fields and the indices (20 bytes per cell)
+// near or outgrow the 256 MB last-level cache.  Measured (us per coarse step
+// marching between two fields, by index / by role): 300 x 256 x 256 130 / 117,
+// 256 x 256 x 200 70.0 / 62.1, 192^3 43.6 / 43.5 (rotating over several pairs of
+// fields 59.7 / 52.9), 97 x 91 x 88 16.7 / 18.3.
 constexpr int REMAP_ROWS = 4;
 constexpr int REMAP_MIN_NX = 40;                // narrower rows leave the lanes idle
-constexpr int64_t REMAP_MIN_CELLS = 1 << 23;
+constexpr int64_t REMAP_MIN_CELLS = 5 << 20;
 
 __global__ void __launch_bounds__(256) coarse_remap_rows_kernel(const double *__restrict__ c_in,
                                                                 const uint8_t *__restrict__ role,

@@ -1,4 +1,4 @@
-"""GPU: mapping and remapping of the coarse step on grids of 2^23 cells and more
+"""GPU: mapping and remapping of the coarse step on grids of 5 2^20 cells and more
 (the remapping by roles), and below (by node indices), with block edges of both
 load rounds of the mapping (B^2 rows in rounds of 5 or 8).
 
