@@ -6,7 +6,7 @@
 // choices the tuner explores: the workgroup layout (the 640-thread segment
 // layout, which packs several small windows per workgroup, or the 256-thread
 // flat layout of the single-domain FP32 step, one to four windows per
-// workgroup by radius and two workgroups per CU), the z extent of an item (long items amortise the
+// workgroup by radius and three workgroups per CU), the z extent of an item (long items amortise the
 // per-item LDS setup; short items balance the load at the end of the queue)
 // and the queue order (natural, or longest-processing-time first).  The tuner
 // times each candidate on an evenly spaced sample of the real items, with HIP
