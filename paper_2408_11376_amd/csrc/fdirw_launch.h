@@ -443,13 +443,18 @@ struct NnLossArgs {
     float grad_scale;         // factor on d loss / d logits (1 / batch)
 };
 
+// The weight gradient is summed per group of NN_GRAD_GROUP windows, in at most
+// NN_GRAD_PARTS partials each: part of the result (the order of FP32 sums).
+constexpr int NN_GRAD_GROUP = 128, NN_GRAD_PARTS = 512;
+
 struct NnWgradArgs {
     const uint16_t *dz;       // [B][V][COP] gradient at the layer output
     const uint16_t *h;        // [B][V][CI] layer input
     int co_n, ci_n;           // real channel counts
     int n_slab;               // B * slabs per window
-    float *part;              // [grid][27][16][16] weight partials
-    float *bpart;             // [grid][16] bias partials
+    int n_part;               // nn_grad_parts(B)
+    float *part;              // [n_part][27][16][16] weight partials (the real channels)
+    float *bpart;             // [n_part][16] bias partials
 };
 
 // Fused inference: one workgroup runs features, support, the five layers
@@ -472,6 +477,7 @@ struct NnFusedArgs {
 };
 
 int nn_slabs_per_window();
+int nn_grad_parts(int windows);   // partials of a batch (groups one after the other)
 int nn_fpack_elems(int layer);
 hipError_t nn_launch_fpack(const float *w, int layer, int co_n, int ci_n, uint16_t *out, hipStream_t st);
 hipError_t nn_launch_fused(const NnFusedArgs &a, int batch, hipStream_t st);
@@ -481,7 +487,8 @@ int nn_pack_chunks(int CI);
 hipError_t nn_launch_conv(int CI, const NnConvArgs &a, int batch, hipStream_t st);
 hipError_t nn_launch_loss(const NnLossArgs &a, int batch, hipStream_t st);
 hipError_t nn_launch_wgrad(int CI, int COP, const NnWgradArgs &a, int grid, hipStream_t st);
-hipError_t nn_launch_wgrad_reduce(const float *part, const float *bpart, int grid, int co_n, int ci_n,
+// at most two groups
+hipError_t nn_launch_wgrad_reduce(const float *part, const float *bpart, int n_part, int co_n, int ci_n,
                                   float *gw, float *gb, hipStream_t st);
 hipError_t nn_launch_adam(float *w, float *m, float *v, const float *g, int n, float lr, float b1, float b2,
                           float eps, float c1, float c2, hipStream_t st);

@@ -22,9 +22,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "fdirw_launch.h"
-
+#include <algorithm>
 #include <type_traits>
+
+#include "fdirw_launch.h"
 
 namespace fdirw {
 namespace nn {
@@ -322,9 +323,37 @@ __device__ __forceinline__ T block_reduce_sum(T x, T *red)
 // KL(q || G) and sum |q - G|, and d loss / d logits = (G - q) + G (sbar -
 // sign(q - G)), sbar = sum sign(q - G) G, times grad_scale, written as BF16
 // channel 0 of an 8-channel field.  The loss path evaluates G in FP64.
-// One window per CU: 16 waves hide the latency of the FP64 exp and log (52 ->
-// 28 us per 256 windows against 4 waves).
+// One window per CU: 16 waves hide the latency of the FP64 exp and log.  The
+// sums over a window keep the order of four waves (thread t the cells t, t +
+// 256, ...; then the wave, then the waves): a step's rounding decides BF16
+// values of the next, so another order would be another training run.  256
+// windows: 26 us, 52 with four waves.
 constexpr int LOSS_NT = 1024;
+
+// Sums over the cells of a window from their terms in LDS: threads t < 256 add
+// f(v) for v = t, t + 256, ... to 0 (f(v, sum) returns the new sum), threads
+// 256 .. 511 the same for a second sum; then each four waves as block_reduce_sum
+// does for four.  Returns the two sums in every thread.
+template <typename F>
+__device__ __forceinline__ void loss_sums(F f, double *red, double &first, double &second)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __syncthreads();                                         // the terms are there
+    if (wave < 2 * (NTHR / 64)) {
+        const int which = wave / (NTHR / 64);                // uniform per wave
+        double x = 0.0;
+#pragma unroll 4
+        for (int v = threadIdx.x % NTHR; v < V; v += NTHR) x = f(which, v, x);
+        for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+        if (lane == 0) red[wave] = x;
+    }
+    __syncthreads();
+    first = second = 0.0;
+    for (int w = 0; w < NTHR / 64; ++w) {
+        first += red[w];
+        second += red[NTHR / 64 + w];
+    }
+}
 
 __global__ void __launch_bounds__(LOSS_NT)
 softmax_loss_kernel(NnLossArgs a)
@@ -368,38 +397,56 @@ softmax_loss_kernel(NnLossArgs a)
     constexpr int NJ = (V + LOSS_NT - 1) / LOSS_NT;
     double lg[NJ], g[NJ], qv[NJ];                            // a thread's cells: log G and G, q (support only)
     unsigned sup = 0u;
-    double se = 0.0, tm = 0.0;
+    __shared__ double ta[V], tb[V];                          // the terms of two sums
+    const auto add = [&](int which, int v, double x) { return x + (which ? tb[v] : ta[v]); };
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
         const int v = threadIdx.x + j * LOSS_NT;
         lg[j] = qv[j] = 0.0;
         if (v >= V) continue;
+        double ex = 0.0;
         if (S[v]) {
             sup |= 1u << j;
             lg[j] = (double)(a.prior[v] + z5[v]) - (double)mx;
-            se += exp(lg[j]);
+            ex = exp(lg[j]);
         }
         qv[j] = (double)tg[v];
-        tm += qv[j];
+        ta[v] = ex;
+        tb[v] = qv[j];
     }
-    se = block_reduce_sum<double, LOSS_NT / 64>(se, redd);
-    tm = block_reduce_sum<double, LOSS_NT / 64>(tm, redd);
+    double se, tm, kl, l1, sbar, none;
+    loss_sums(add, redd, se, tm);
     const double lse = log(se), tinv = 1.0 / tm;
-    double kl = 0.0, l1 = 0.0, sbar = 0.0;
+    double lq[NJ], tq[NJ];                                   // log q - log G, and the target as given
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-        g[j] = 0.0;
-        if (!((sup >> j) & 1u)) continue;
-        lg[j] -= lse;
-        g[j] = exp(lg[j]);
-        qv[j] *= tinv;
-        if (qv[j] > 0.0) kl += qv[j] * (log(qv[j]) - lg[j]);
-        l1 += fabs(qv[j] - g[j]);
-        sbar += (qv[j] > g[j] ? 1.0 : (qv[j] < g[j] ? -1.0 : 0.0)) * g[j];
+        const int v = threadIdx.x + j * LOSS_NT;
+        g[j] = lq[j] = 0.0;
+        tq[j] = qv[j];
+        const bool on = (sup >> j) & 1u;
+        double dist = 0.0, sgn = 0.0;
+        if (on) {
+            lg[j] -= lse;
+            g[j] = exp(lg[j]);
+            qv[j] = tq[j] * tinv;
+            if (qv[j] > 0.0) lq[j] = log(qv[j]) - lg[j];
+            dist = fabs(qv[j] - g[j]);
+            sgn = (qv[j] > g[j] ? 1.0 : (qv[j] < g[j] ? -1.0 : 0.0)) * g[j];
+        }
+        if (v < V) {
+            ta[v] = dist;
+            tb[v] = sgn;
+        }
     }
-    kl = block_reduce_sum<double, LOSS_NT / 64>(kl, redd);
-    l1 = block_reduce_sum<double, LOSS_NT / 64>(l1, redd);
-    sbar = block_reduce_sum<double, LOSS_NT / 64>(sbar, redd);
+    loss_sums(add, redd, l1, sbar);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const int v = threadIdx.x + j * LOSS_NT;
+        if (v >= V) continue;
+        ta[v] = (sup >> j) & 1u && qv[j] > 0.0 ? qv[j] : 0.0;
+        tb[v] = lq[j];
+    }
+    loss_sums([&](int which, int v, double x) { return which ? x : __builtin_fma(ta[v], tb[v], x); }, redd, kl, none);
     if (threadIdx.x == 0) {
         a.loss[2 * b] = kl;
         a.loss[2 * b + 1] = l1;
@@ -413,7 +460,9 @@ softmax_loss_kernel(NnLossArgs a)
         float dz = 0.0f;
         if ((sup >> j) & 1u) {
             const double sg = qv[j] > g[j] ? 1.0 : (qv[j] < g[j] ? -1.0 : 0.0);
-            dz = (float)(((g[j] - qv[j]) + g[j] * (sbar - sg)) * (double)a.grad_scale);
+            // G - q with one rounding of the product in q
+            const double d = __builtin_fma(g[j], sbar - sg, __builtin_fma(-tinv, tq[j], g[j]));
+            dz = (float)(d * (double)a.grad_scale);
         }
         const float gv = (float)g[j];
         if (G) G[v] = gv;
@@ -433,13 +482,18 @@ softmax_loss_kernel(NnLossArgs a)
 // operands are staged channel-first in LDS.  Wave w takes the three x taps of
 // tap pair (dz, dy) = (w / 3, w % 3): their operands start s, s + 1 and s + 2
 // elements into the same 16-byte chunks (s fixed by the pair, so known at
-// compile time), which are read once and shifted in registers.  Each workgroup
-// accumulates its slabs in registers and writes one partial; db[co] = sum of
-// dZ is accumulated alongside.
+// compile time), which are read once and shifted in registers.  Per group of
+// NN_GRAD_GROUP windows, partial g is the sum over the slabs g, g +
+// NN_GRAD_PARTS, ... of the group, accumulated in registers; a workgroup takes
+// the partials blockIdx.x, + gridDim.x, ... of all groups (256 workgroups and
+// full groups: six slabs each).  db[co] = sum of dZ is accumulated alongside.
+// The partials are added in order (wgrad_reduce_kernel), so the gradient does
+// not depend on the launch: training amplifies the rounding of its sums within
+// a few steps.
 // Bound by the LDS accesses of the staging and of the operands.  Rows are an
 // odd number of chunks apart, so the 16 rows of an operand read meet distinct
 // banks, and the next slab's global loads are in flight during the products.
-// 128 windows, 16 -> 16 channels: 28.6 us; 184 us with four waves that read
+// 256 windows, 16 -> 16 channels: 57 us; 184 us per 128 with four waves that read
 // every tap's operand in 32-bit pieces from rows 32 banks apart (8-way
 // conflicts) and a second copy of H shifted by one element.
 constexpr int WG_NT = 9 * 64;
@@ -553,8 +607,14 @@ wgrad_kernel(NnWgradArgs a)
         }
     };
 
-    if ((int)blockIdx.x < a.n_slab) fetch(blockIdx.x);
-    for (int slab_id = blockIdx.x; slab_id < a.n_slab; slab_id += gridDim.x) {
+    // the slabs of partial p: first(p), + NN_GRAD_PARTS, ... below end(p)
+    constexpr int GSLAB = NN_GRAD_GROUP * NSLAB;
+    const auto first = [&](int p) { return p / NN_GRAD_PARTS * GSLAB + p % NN_GRAD_PARTS; };
+    const auto end = [&](int p) { return min(a.n_slab, (p / NN_GRAD_PARTS + 1) * GSLAB); };
+    int p = blockIdx.x;
+    int slab_id = p < a.n_part ? first(p) : 0;
+    if (p < a.n_part) fetch(slab_id);
+    while (p < a.n_part) {
         __syncthreads();                                     // previous slab fully consumed
         typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 #pragma unroll
@@ -582,8 +642,10 @@ wgrad_kernel(NnWgradArgs a)
             }
         }
         __syncthreads();
-        const int nxt = slab_id + gridDim.x;
-        if (nxt < a.n_slab) fetch(nxt);
+        // the next slab of this partial, or the first of the next one
+        const int pn = slab_id + NN_GRAD_PARTS < end(p) ? p : p + (int)gridDim.x;
+        slab_id = pn == p ? slab_id + NN_GRAD_PARTS : first(pn);
+        if (pn < a.n_part) fetch(slab_id);
         switch (wave) {
         case 0: products(std::integral_constant<int, 0>()); break;
         case 1: products(std::integral_constant<int, 1>()); break;
@@ -595,55 +657,96 @@ wgrad_kernel(NnWgradArgs a)
         case 7: products(std::integral_constant<int, 7>()); break;
         default: products(std::integral_constant<int, 8>()); break;
         }
-    }
-    // acc[i][j]: co = 4 kb + j, ci = m
-    float *part = a.part + (size_t)blockIdx.x * 27 * 256;
+        if (pn == p) continue;
+        // acc[i][j]: co = 4 kb + j, ci = m
+        float *part = a.part + (size_t)p * 27 * 256;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
+        for (int i = 0; i < 3; ++i) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) part[(3 * wave + i) * 256 + (4 * kb + j) * 16 + m] = acc[i][j];
-    if (wave == 0) {
-        bsum += __shfl_xor(bsum, 16, 64);
-        bsum += __shfl_xor(bsum, 32, 64);
-        if (kb == 0) a.bpart[(size_t)blockIdx.x * 16 + m] = bsum;
+            for (int j = 0; j < 4; ++j)
+                if (4 * kb + j < a.co_n && m < a.ci_n) part[(3 * wave + i) * 256 + (4 * kb + j) * 16 + m] = acc[i][j];
+            acc[i] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        if (wave == 0) {
+            bsum += __shfl_xor(bsum, 16, 64);
+            bsum += __shfl_xor(bsum, 32, 64);
+            if (kb == 0) a.bpart[(size_t)p * 16 + m] = bsum;
+            bsum = 0.0f;
+        }
+        p = pn;
     }
 }
 
-// gw[(co ci_n + ci) 27 + tap] += sum over g of part[g][tap][co][ci]; gb[co]
-// likewise.  A workgroup takes 64 outputs: its 16 waves each a run of the
-// partials in order, then the 16 sums in order.  (One thread per output
-// walking all partials took 120 us for 512 of them: 27 workgroups, one load in
-// flight per thread; this takes 5 us for 256.)
+// Per group of windows in order: gw[(co ci_n + ci) 27 + tap] += sum over g of
+// part[g][tap][co][ci], the partials added in index order to 0; gb[co] likewise.
+// A workgroup takes 32 outputs of two groups: its 16 waves bring their partials
+// to LDS (all loads in flight, four partials of a lane as one 16-byte write; the
+// pitch of 516 floats spreads 16 lanes' accesses over all banks), one wave adds
+// them, a lane per output and group.  (One thread per output and group walking
+// the partials took 120 us for 512 of them; this takes 9 us for 2 x 512.)
 constexpr int RED_NT = 1024;
+constexpr int RED_OUT = 32;
+constexpr int RED_PITCH = NN_GRAD_PARTS + 4;
 
 __global__ void __launch_bounds__(RED_NT)
-wgrad_reduce_kernel(const float *__restrict__ part, const float *__restrict__ bpart, int grid,
+wgrad_reduce_kernel(const float *__restrict__ part, const float *__restrict__ bpart, int n_part,
                     int co_n, int ci_n, float *__restrict__ gw, float *__restrict__ gb)
 {
-    __shared__ float sums[RED_NT / 64][64];
+    constexpr int WAVES = RED_NT / 64, NQ = NN_GRAD_PARTS / 4 / WAVES, AHEAD = 8;
+    static_assert(2 * RED_OUT == 64 && NN_GRAD_PARTS % (4 * WAVES) == 0 && NN_GRAD_PARTS % (4 * AHEAD) == 0, "split");
+    __shared__ __align__(16) float terms[64 * RED_PITCH];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int i = blockIdx.x * 64 + lane;
-    const bool bias = i >= 27 * 256;                         // uniform per block
-    const int per = (grid + RED_NT / 64 - 1) / (RED_NT / 64);
-    const int g0 = wave * per, g1 = g0 + per < grid ? g0 + per : grid;
-    const float *src = bias ? bpart + (i - 27 * 256) : part + i;
+    const int grp = lane / RED_OUT;
+    const int i = blockIdx.x * RED_OUT + lane % RED_OUT;
+    const bool bias = blockIdx.x == 27 * 256 / RED_OUT;      // uniform per block
+    const int tap = i / 256, co = bias ? i - 27 * 256 : (i / 16) % 16, ci = bias ? 0 : i % 16;
+    const bool used = co < co_n && ci < ci_n;
+    if (!__any(used)) return;                                // the same for every wave
+    const int n0 = min(n_part, NN_GRAD_PARTS), mine = used ? grp ? n_part - n0 : n0 : 0;
     const size_t step = bias ? 16 : 27 * 256;
-    float s = 0.0f;
-    if (!bias || i < 27 * 256 + 16) {
-#pragma unroll 8
-        for (int g = g0; g < g1; ++g) s += src[(size_t)g * step];
+    // a lane without partials reads the first one of the first group's and drops it
+    const float *src = (bias ? bpart + (used ? co : 0) : part + i) + (mine > 0 ? grp * NN_GRAD_PARTS * step : 0);
+    float v[NQ][4];
+#pragma unroll
+    for (int k = 0; k < NQ; ++k)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int g = 4 * (wave + k * WAVES) + u;
+            v[k][u] = src[(size_t)max(0, min(g, mine - 1)) * step];
+        }
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+        const int g = 4 * (wave + k * WAVES);
+        floatx4 o;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = g + u < mine ? v[k][u] : 0.0f;
+        *reinterpret_cast<floatx4 *>(&terms[lane * RED_PITCH + g]) = o;
     }
-    sums[wave][lane] = s;
     __syncthreads();
     if (wave != 0) return;
+    const floatx4 *t = reinterpret_cast<const floatx4 *>(&terms[lane * RED_PITCH]);
+    floatx4 cur[AHEAD], nxt[AHEAD];
 #pragma unroll
-    for (int w = 1; w < RED_NT / 64; ++w) s += sums[w][lane];
-    if (!bias) {
-        const int tap = i / 256, co = (i / 16) % 16, ci = i % 16;
-        if (co < co_n && ci < ci_n) gw[((size_t)co * ci_n + ci) * 27 + tap] += s;
-    } else if (i - 27 * 256 < co_n) {
-        gb[i - 27 * 256] += s;
+    for (int k = 0; k < AHEAD; ++k) cur[k] = t[k];
+    float s = 0.0f;
+    const int n_q = (n0 + 4 * AHEAD - 1) / (4 * AHEAD) * AHEAD;   // the zeros after the last partial change nothing
+    for (int q = 0; q < n_q; q += AHEAD) {
+        const int at = q + AHEAD < n_q ? q + AHEAD : q;
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) nxt[k] = t[at + k];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s += cur[k][u];
+            cur[k] = nxt[k];
+        }
     }
+    const float s1 = __shfl_down(s, RED_OUT, 64);
+    if (grp || !used) return;
+    float *out = bias ? gb + co : gw + ((size_t)co * ci_n + ci) * 27 + tap;
+    float r = *out + s;
+    if (n_part > NN_GRAD_PARTS) r += s1;
+    *out = r;
 }
 
 // ----------------------------------------------------------------- Adam
@@ -1209,6 +1312,12 @@ static unsigned grid_1d(int64_t n, int nt)
     return (unsigned)g;
 }
 
+int nn_grad_parts(int windows)
+{
+    const int last = windows % NN_GRAD_GROUP * nn::NSLAB;
+    return windows / NN_GRAD_GROUP * std::min(NN_GRAD_PARTS, NN_GRAD_GROUP * nn::NSLAB) + std::min(NN_GRAD_PARTS, last);
+}
+
 int nn_slabs_per_window() { return nn::NSLAB; }
 int nn_pack_chunks(int CI) { return nn::nchunks(CI); }
 
@@ -1270,11 +1379,12 @@ hipError_t nn_launch_wgrad(int CI, int COP, const NnWgradArgs &a, int grid, hipS
     return hipGetLastError();
 }
 
-hipError_t nn_launch_wgrad_reduce(const float *part, const float *bpart, int grid, int co_n, int ci_n, float *gw,
+hipError_t nn_launch_wgrad_reduce(const float *part, const float *bpart, int n_part, int co_n, int ci_n, float *gw,
                                   float *gb, hipStream_t st)
 {
-    hipLaunchKernelGGL(nn::wgrad_reduce_kernel, dim3(27 * 256 / 64 + 1), dim3(nn::RED_NT), 0, st, part, bpart,
-                       grid, co_n, ci_n, gw, gb);
+    if (n_part < 0 || n_part > 2 * NN_GRAD_PARTS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(nn::wgrad_reduce_kernel, dim3(27 * 256 / nn::RED_OUT + 1), dim3(nn::RED_NT), 0, st, part, bpart,
+                       n_part, co_n, ci_n, gw, gb);
     return hipGetLastError();
 }
 

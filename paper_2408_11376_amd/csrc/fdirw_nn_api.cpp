@@ -20,7 +20,7 @@ namespace fdirw {
 
 static const int kChan[6] = {3, 16, 16, 16, 16, 1};
 static const int kStoreCI[5] = {8, 16, 16, 16, 16};     // input channels as stored (BF16 vectors of 8)
-static const int kMbTrain = 256;                          // windows per training micro-batch (one FD target per CU)
+static const int kMbTrain = 2 * NN_GRAD_GROUP;            // windows per training micro-batch (one FD target per CU)
 static const int kMbInfer = 4096;                         // windows per inference chunk
 static const int kWgradGrid = 256;                        // one weight-gradient workgroup per CU (95 KB of LDS)
 
@@ -128,8 +128,8 @@ static int ensure_work(NnModel *m, int cap, bool train)
         if ((rc = ensure(w.dlog8, (size_t)cap * V * 8 * 2))) return rc;
         for (int k = 0; k < 2; ++k)
             if ((rc = ensure(w.dz[k], (size_t)cap * V * 16 * 2))) return rc;
-        if ((rc = ensure(w.part, (size_t)kWgradGrid * 27 * 256 * 4))) return rc;
-        if ((rc = ensure(w.bpart, (size_t)kWgradGrid * 16 * 4))) return rc;
+        if ((rc = ensure(w.part, (size_t)nn_grad_parts(cap) * 27 * 256 * 4))) return rc;
+        if ((rc = ensure(w.bpart, (size_t)nn_grad_parts(cap) * 16 * 4))) return rc;
     }
     w.cap = cap;
     return FDIRW_OK;
@@ -222,7 +222,7 @@ static int run_backward(NnModel *m, int n, hipStream_t st)
     NnWork &w = m->ws;
     float *g = (float *)m->grad.p;
     const int nslab = n * nn_slabs_per_window();
-    const int grid = nslab < kWgradGrid ? nslab : kWgradGrid;
+    const int n_part = nn_grad_parts(n), grid = n_part < kWgradGrid ? n_part : kWgradGrid;
     hipError_t e = hipSuccess;
     const uint16_t *dz = (const uint16_t *)w.dlog8.p;     // gradient at the output of layer l
     int cop = 8;
@@ -233,11 +233,12 @@ static int run_backward(NnModel *m, int n, hipStream_t st)
         wa.co_n = kChan[l + 1];
         wa.ci_n = kChan[l];
         wa.n_slab = nslab;
+        wa.n_part = n_part;
         wa.part = (float *)w.part.p;
         wa.bpart = (float *)w.bpart.p;
         e = nn_launch_wgrad(kStoreCI[l], cop, wa, grid, st);
         if (e == hipSuccess)
-            e = nn_launch_wgrad_reduce(wa.part, wa.bpart, grid, kChan[l + 1], kChan[l], g + layer_w_off(l),
+            e = nn_launch_wgrad_reduce(wa.part, wa.bpart, n_part, kChan[l + 1], kChan[l], g + layer_w_off(l),
                                        g + layer_b_off(l), st);
         if (l == 0 || e != hipSuccess) break;
         // gradient at the input of layer l = output of layer l - 1, through
