@@ -56,15 +56,20 @@ static void free_buf(Buf &b)
     b.cap = 0;
 }
 
-static void free_model(NnModel *m)
+static void free_work(NnWork &w)
 {
-    for (Buf *b : {&m->theta, &m->grad, &m->m, &m->v, &m->prior}) free_buf(*b);
-    for (int l = 0; l < 5; ++l) { free_buf(m->wp[l]); free_buf(m->wpf[l]); free_buf(m->wfu[l]); }
-    NnWork &w = m->ws;
     for (Buf *b : {&w.src, &w.X, &w.S, &w.z5, &w.G, &w.mass, &w.targ, &w.tmass, &w.loss, &w.dlog8, &w.dz[0],
                    &w.dz[1], &w.part, &w.bpart, &w.l1, &w.kmm})
         free_buf(*b);
     for (int l = 0; l < 4; ++l) { free_buf(w.h[l]); free_buf(w.zpre[l]); }
+    w.cap = 0;
+}
+
+static void free_model(NnModel *m)
+{
+    for (Buf *b : {&m->theta, &m->grad, &m->m, &m->v, &m->prior}) free_buf(*b);
+    for (int l = 0; l < 5; ++l) { free_buf(m->wp[l]); free_buf(m->wpf[l]); free_buf(m->wfu[l]); }
+    free_work(m->ws);
 }
 
 // SplitMix64 (Steele, Lea, Flood 2014) and Box-Muller normals for the
@@ -626,7 +631,17 @@ int fdirw_nn_backward(void *nn, const fdirw_domain *d, const int64_t *src, int64
     Geometry geo;
     const void *lam32 = nullptr;
     if ((rc = coef_buffers(d, FDIRW_FP32, st, dc, &geo, &lam32))) return rc;
-    if ((rc = ensure_work(m, n_src < kMbTrain ? (int)n_src : kMbTrain, true))) return rc;
+    // half the micro-batch where there is no room for its work buffers (the
+    // gradient is summed per group of windows: the same result)
+    int mb = n_src < kMbTrain ? (int)n_src : kMbTrain;
+    rc = ensure_work(m, mb, true);
+    if (rc == FDIRW_E_NOMEM && mb > NN_GRAD_GROUP) {
+        (void)hipStreamSynchronize(st);
+        free_work(m->ws);
+        mb = NN_GRAD_GROUP;
+        rc = ensure_work(m, mb, true);
+    }
+    if (rc) return rc;
     if ((rc = pack_weights(m, st, false))) return rc;
     NnWork &w = m->ws;
     const int64_t np = num_params();
@@ -634,9 +649,9 @@ int fdirw_nn_backward(void *nn, const fdirw_domain *d, const int64_t *src, int64
     if (e != hipSuccess) return hip_fail(e, "gradient clear");
     const float scale = (float)(1.0 / (double)n_src);
     double kl = 0.0, l1 = 0.0;
-    std::vector<double> hl((size_t)2 * kMbTrain);
-    for (int64_t k0 = 0; k0 < n_src; k0 += kMbTrain) {
-        const int nb = (int)((n_src - k0) < kMbTrain ? (n_src - k0) : kMbTrain);
+    std::vector<double> hl((size_t)2 * mb);
+    for (int64_t k0 = 0; k0 < n_src; k0 += mb) {
+        const int nb = (int)((n_src - k0) < mb ? (n_src - k0) : mb);
         e = hipMemcpyAsync(w.src.p, src + k0, (size_t)nb * 8, hipMemcpyDeviceToDevice, st);
         if (e != hipSuccess) return hip_fail(e, "source copy");
         if ((rc = run_features(m, d, nb, st))) return rc;
