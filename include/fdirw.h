@@ -344,7 +344,9 @@ int fdirw_nn_load(void *nn, const char *path);
  * (not scaled with a far field): by linearity the sum of the point-source
  * kernels of J's cells on that shared window; with block = 1 it is the
  * point-source window of radius r.  Its state lives in HBM (batches of
- * nodes, one launch per sub-step).
+ * nodes, one launch per sub-step), in two buffers of at most 2 GB each (or the
+ * bytes in the environment variable FDIRW_NODEWIN_BYTES); where they cannot be
+ * allocated, window by window in 2 GB for both.
  * Far field (Eqs. 7, 8, 10, 14): cells of the reservoir phases are the
  * far-field boundary, Dirichlet cells holding the uniform far-field
  * concentration c_ff.  Their handle builds P from kernels in which those cells
@@ -363,7 +365,7 @@ int fdirw_nn_load(void *nn, const char *path);
  * a steady flow as in fdirw_kernels_flow; P and P_BC then include it (the
  * kernels are the flow kernels, generated in chunks of sources; r <= 8 only).  block: 1..256.  d->label is read
  * only here.  *handle
- * receives a handle owning device memory of about 4 N + (2K+1)^3 x N_nodes x
+ * receives a handle owning device memory of about 5 N + (2K+1)^3 x N_nodes x
  * element bytes (for K >= 5 N_nodes counts only the nodes of the 16-byte z
  * groups of P that hold a grouped cell; the build also holds (2K+1)^3 x
  * N_nodes x 8 bytes for its duration); seconds (host, may be NULL) receives

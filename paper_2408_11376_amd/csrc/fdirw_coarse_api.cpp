@@ -11,8 +11,10 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <vector>
 
 #include "../../include/fdirw.h"
@@ -93,15 +95,24 @@ int check_handle(const Coarse *h)
 // (60^3, 100 sub-steps): particle 0.28 12.4 / 52 (250 sub-steps), 0.84 5.7 /
 // 9.9; porous medium, block 3, r 12 1.54 91 / 108; block 2, r 9 (60) 1.57 137 /
 // 133; block 4, r 12, pores 2.16 36 / 41; block 20, r 20 2.37 8.6 / 6.8; block 6,
-// r 12 2.94 25 / 17; block 10, r 10 6.3 9.6 / 4.8.  The rows take at most ~2 GB
-// per buffer (else *done stays false).
+// r 12 2.94 25 / 17; block 10, r 10 6.3 9.6 / 4.8.  A state buffer of the rows
+// takes at most nodewin_bytes(); where a chunk needs more, or an allocation
+// fails, *done stays false (whole windows take 2 GB for both buffers together).
 constexpr double NODEWIN_LANES = 1.5;
 
-int nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> ids, const double *count, double *S,
+// 2 GB, or the environment variable FDIRW_NODEWIN_BYTES.
+size_t nodewin_bytes()
+{
+    const char *v = std::getenv("FDIRW_NODEWIN_BYTES");
+    const unsigned long long b = v ? std::strtoull(v, nullptr, 10) : 0;
+    return b ? (size_t)b : (size_t)2 << 30;
+}
+
+void nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> ids, const double *count, double *S,
                  hipStream_t st, bool *done, hipError_t *err)
 {
     *done = false;
-    if (ids.empty()) return FDIRW_OK;
+    if (ids.empty()) return;
     struct Bufs {
         void *block = nullptr, *start = nullptr, *row = nullptr, *cells = nullptr, *lanes = nullptr, *units = nullptr,
              *ga = nullptr, *gb = nullptr;
@@ -113,19 +124,19 @@ int nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> ids
         }
     } m;
     m.st = st;
-    int rc;
-    if ((rc = coarse_alloc(&m.block, (size_t)w.n_nodes * sizeof(int)))) return rc;
-    if ((rc = coarse_alloc(&m.start, (size_t)(w.n_nodes + 1) * sizeof(int)))) return rc;
-    if ((rc = coarse_alloc(&m.row, (size_t)w.n * sizeof(int)))) return rc;
+    if (coarse_alloc(&m.block, (size_t)w.n_nodes * sizeof(int)) ||
+        coarse_alloc(&m.start, (size_t)(w.n_nodes + 1) * sizeof(int)) ||
+        coarse_alloc(&m.row, (size_t)w.n * sizeof(int)))
+        return;
     std::vector<int> start((size_t)w.n_nodes + 1);
     hipError_t e = launch_nodewin_number(fp64, w, (int *)m.block, (int *)m.start, (int *)m.row, st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(start.data(), m.start, start.size() * sizeof(int), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) { *err = e; return FDIRW_OK; }
+    if (e != hipSuccess) { *err = e; return; }
     const int n_act = start[(size_t)w.n_nodes];
-    const size_t chunk_bytes = (size_t)(n_act + 1) * 64 * (fp64 ? 8 : 4), most = (size_t)2 << 30;
-    if (n_act <= 0 || chunk_bytes > most) return FDIRW_OK;
+    const size_t chunk_bytes = (size_t)(n_act + 1) * 64 * (fp64 ? 8 : 4), most = nodewin_bytes();
+    if (n_act <= 0 || chunk_bytes > most) return;
     // nodes along a Morton curve, 64 to a chunk: compact groups, and halves of them
     const int ncx = w.ncx, ncy = w.ncy, ncz = w.ncz, K = w.K;
     auto morton = [&](int J) {
@@ -161,18 +172,18 @@ int nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> ids
                         units.push_back({(int)c, r, std::min(r + per, start[I + 1]), x, y, z});
                     rows += start[I + 1] - start[I];
                 }
-        if (64.0 * rows > NODEWIN_LANES * windows) return FDIRW_OK;
+        if (64.0 * rows > NODEWIN_LANES * windows) return;
         first[(size_t)c + 1] = units.size();
     }
     int64_t at_once = std::min<int64_t>(n_chunk, (int64_t)(most / chunk_bytes));
     if (at_once > 65535) at_once = 65535;
     for (NodeWinUnit &u : units) u.chunk %= (int)at_once;      // chunks are numbered within their launch
     ids.resize((size_t)n_chunk * 64, -1);
-    if ((rc = coarse_alloc(&m.cells, (size_t)n_act * nodewin_cell_bytes(fp64)))) return rc;
-    if ((rc = coarse_alloc(&m.lanes, ids.size() * sizeof(int)))) return rc;
-    if ((rc = coarse_alloc(&m.units, units.size() * sizeof(NodeWinUnit)))) return rc;
-    if ((rc = coarse_alloc(&m.ga, (size_t)at_once * chunk_bytes))) return rc;
-    if ((rc = coarse_alloc(&m.gb, (size_t)at_once * chunk_bytes))) return rc;
+    if (coarse_alloc(&m.cells, (size_t)n_act * nodewin_cell_bytes(fp64)) ||
+        coarse_alloc(&m.lanes, ids.size() * sizeof(int)) ||
+        coarse_alloc(&m.units, units.size() * sizeof(NodeWinUnit)) ||
+        coarse_alloc(&m.ga, (size_t)at_once * chunk_bytes) || coarse_alloc(&m.gb, (size_t)at_once * chunk_bytes))
+        return;
     e = hipMemcpyAsync(m.lanes, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice, st);
     if (e == hipSuccess && !units.empty())
         e = hipMemcpyAsync(m.units, units.data(), units.size() * sizeof(NodeWinUnit), hipMemcpyHostToDevice, st);
@@ -186,7 +197,6 @@ int nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> ids
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     *err = e;
     *done = e == hipSuccess;
-    return FDIRW_OK;
 }
 
 int field_sum_h(Coarse *h, const double *c, hipStream_t st, double *out)
@@ -372,10 +382,12 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
                 w.wb = wb;
                 w.sink = h->far_field ? 1 : 0;
                 bool done = false;
-                rc = nodewin_rows(w, prec == FDIRW_FP64, d->n_sub, ids, (const double *)h->count, S, st, &done, &e);
+                try {
+                    nodewin_rows(w, prec == FDIRW_FP64, d->n_sub, ids, (const double *)h->count, S, st, &done, &e);
+                } catch (const std::bad_alloc &) {}              // of host memory: before anything is launched for S
                 int *dids = nullptr;
                 void *ga = nullptr, *gb = nullptr;
-                if (!rc && e == hipSuccess && !done) {
+                if (e == hipSuccess && !done) {
                     rc = coarse_alloc((void **)&dids, ids.size() * sizeof(int));
                     if (!rc) rc = coarse_alloc(&ga, (size_t)nbat * wb * wb * wb * esz);
                     if (!rc) rc = coarse_alloc(&gb, (size_t)nbat * wb * wb * wb * esz);
