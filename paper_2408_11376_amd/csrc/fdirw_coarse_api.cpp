@@ -96,8 +96,9 @@ int check_handle(const Coarse *h)
 // 9.9; porous medium, block 3, r 12 1.54 91 / 108; block 2, r 9 (60) 1.57 137 /
 // 133; block 4, r 12, pores 2.16 36 / 41; block 20, r 20 2.37 8.6 / 6.8; block 6,
 // r 12 2.94 25 / 17; block 10, r 10 6.3 9.6 / 4.8.  A state buffer of the rows
-// takes at most nodewin_bytes(); where a chunk needs more, or an allocation
-// fails, *done stays false (whole windows take 2 GB for both buffers together).
+// with the list of a launch's units (at most a tenth of it) takes at most
+// nodewin_bytes(); where a chunk needs more, or an allocation fails, *done stays
+// false (whole windows take 2 GB for both buffers together).
 constexpr double NODEWIN_LANES = 1.5;
 
 // 2 GB, or the environment variable FDIRW_NODEWIN_BYTES.
@@ -108,11 +109,26 @@ size_t nodewin_bytes()
     return b ? (size_t)b : (size_t)2 << 30;
 }
 
+// Rows and units of the blocks of a chunk, from prefix sums over the blocks
+// (x fastest), so that nothing is listed before the chunk runs.
+struct NodeWinBox {
+    int lo[3], hi[3];
+    template <typename F> void rows_of_blocks(int ncx, int ncy, F f) const   // f(first block, past the last) per x row
+    {
+        for (int z = lo[2]; z < hi[2]; ++z)
+            for (int y = lo[1]; y < hi[1]; ++y) {
+                const size_t I = ((size_t)z * ncy + y) * ncx;
+                f(I + lo[0], I + hi[0], y, z);
+            }
+    }
+};
+
 void nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> ids, const double *count, double *S,
                  hipStream_t st, bool *done, hipError_t *err)
 {
     *done = false;
-    if (ids.empty()) return;
+    if (ids.empty() || w.n > INT32_MAX) return;
+    std::vector<NodeWinUnit> units;                              // lives until the stream is synchronised
     struct Bufs {
         void *block = nullptr, *start = nullptr, *row = nullptr, *cells = nullptr, *lanes = nullptr, *units = nullptr,
              *ga = nullptr, *gb = nullptr;
@@ -152,47 +168,60 @@ void nodewin_rows(const NodeWinArgs &w, int fp64, int n_sub, std::vector<int> id
     // workgroup's rows; given up where the lanes are too many for the windows
     const double windows = (double)ids.size() * w.wb * (double)w.wb * w.wb;
     const int per = nodewin_unit_rows();
-    std::vector<NodeWinUnit> units;
-    std::vector<size_t> first((size_t)n_chunk + 1, 0);
+    std::vector<int> units_before((size_t)w.n_nodes + 1, 0);
+    for (size_t I = 0; I < (size_t)w.n_nodes; ++I)
+        units_before[I + 1] = units_before[I] + (start[I + 1] - start[I] + per - 1) / per;
+    std::vector<NodeWinBox> box((size_t)n_chunk);
+    std::vector<int> n_units((size_t)n_chunk, 0);                // of a chunk: at most n_act
+    int units_most = 0;
     double rows = 0.0;
     for (int64_t c = 0; c < n_chunk; ++c) {
-        int lo[3] = {ncx, ncy, ncz}, hi[3] = {0, 0, 0};
+        NodeWinBox &b = box[(size_t)c];
+        for (int x = 0; x < 3; ++x) { b.lo[x] = x == 0 ? ncx : x == 1 ? ncy : ncz; b.hi[x] = 0; }
         for (size_t k = (size_t)c * 64; k < ids.size() && k < (size_t)(c + 1) * 64; ++k) {
             const int p[3] = {ids[k] % ncx, ids[k] / ncx % ncy, ids[k] / (ncx * ncy)};
             for (int x = 0; x < 3; ++x) {
-                lo[x] = std::min(lo[x], std::max(0, p[x] - K));
-                hi[x] = std::max(hi[x], std::min((x == 0 ? ncx : x == 1 ? ncy : ncz), p[x] + K + 1));
+                b.lo[x] = std::min(b.lo[x], std::max(0, p[x] - K));
+                b.hi[x] = std::max(b.hi[x], std::min((x == 0 ? ncx : x == 1 ? ncy : ncz), p[x] + K + 1));
             }
         }
-        for (int z = lo[2]; z < hi[2]; ++z)
-            for (int y = lo[1]; y < hi[1]; ++y)
-                for (int x = lo[0]; x < hi[0]; ++x) {
-                    const size_t I = ((size_t)z * ncy + y) * ncx + x;
-                    for (int r = start[I]; r < start[I + 1]; r += per)
-                        units.push_back({(int)c, r, std::min(r + per, start[I + 1]), x, y, z});
-                    rows += start[I + 1] - start[I];
-                }
+        b.rows_of_blocks(ncx, ncy, [&](size_t I0, size_t I1, int, int) {
+            rows += start[I1] - start[I0];
+            n_units[(size_t)c] += units_before[I1] - units_before[I0];
+        });
+        units_most = std::max(units_most, n_units[(size_t)c]);
         if (64.0 * rows > NODEWIN_LANES * windows) return;
-        first[(size_t)c + 1] = units.size();
     }
-    int64_t at_once = std::min<int64_t>(n_chunk, (int64_t)(most / chunk_bytes));
-    if (at_once > 65535) at_once = 65535;
-    for (NodeWinUnit &u : units) u.chunk %= (int)at_once;      // chunks are numbered within their launch
+    // at_once chunks run in one launch, as many as their state and units allow
+    const size_t unit_bytes = (size_t)units_most * sizeof(NodeWinUnit);
+    int64_t at_once = std::min<int64_t>({n_chunk, (int64_t)(most / (chunk_bytes + unit_bytes)), 65535,
+                                         INT32_MAX / std::max(1, units_most)});
+    if (at_once < 1) at_once = 1;
     ids.resize((size_t)n_chunk * 64, -1);
     if (coarse_alloc(&m.cells, (size_t)n_act * nodewin_cell_bytes(fp64)) ||
-        coarse_alloc(&m.lanes, ids.size() * sizeof(int)) ||
-        coarse_alloc(&m.units, units.size() * sizeof(NodeWinUnit)) ||
+        coarse_alloc(&m.lanes, ids.size() * sizeof(int)) || coarse_alloc(&m.units, (size_t)at_once * unit_bytes) ||
         coarse_alloc(&m.ga, (size_t)at_once * chunk_bytes) || coarse_alloc(&m.gb, (size_t)at_once * chunk_bytes))
         return;
     e = hipMemcpyAsync(m.lanes, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice, st);
-    if (e == hipSuccess && !units.empty())
-        e = hipMemcpyAsync(m.units, units.data(), units.size() * sizeof(NodeWinUnit), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = launch_nodewin_cells(fp64, w, (const int *)m.row, n_act, m.cells, st);
-    for (int64_t c = 0; c < n_chunk && e == hipSuccess; c += at_once) {
-        const int64_t end = std::min(n_chunk, c + at_once);
-        e = launch_nodewin_rows(fp64, w, n_sub, (const int *)m.row, n_act, m.cells, (const int *)m.lanes + c * 64,
-                                (int)(end - c), (const NodeWinUnit *)m.units + first[(size_t)c],
-                                (int)(first[(size_t)end] - first[(size_t)c]), m.ga, m.gb, count, S, st);
+    units.reserve((size_t)at_once * units_most);
+    for (int64_t c0 = 0; c0 < n_chunk && e == hipSuccess; c0 += at_once) {
+        const int64_t c1 = std::min(n_chunk, c0 + at_once);
+        if (c0 > 0) e = hipStreamSynchronize(st);                // the list of the previous chunks is used
+        units.clear();
+        for (int64_t c = c0; c < c1; ++c)
+            box[(size_t)c].rows_of_blocks(ncx, ncy, [&](size_t I0, size_t I1, int y, int z) {
+                for (size_t I = I0; I < I1; ++I)
+                    for (int r = start[I]; r < start[I + 1]; r += per)
+                        units.push_back({(int)(c - c0), r, std::min(r + per, start[I + 1]),
+                                         (int)(I % (size_t)ncx), y, z});
+            });
+        if (e == hipSuccess && !units.empty())
+            e = hipMemcpyAsync(m.units, units.data(), units.size() * sizeof(NodeWinUnit), hipMemcpyHostToDevice, st);
+        if (e == hipSuccess)
+            e = launch_nodewin_rows(fp64, w, n_sub, (const int *)m.row, n_act, m.cells, (const int *)m.lanes + c0 * 64,
+                                    (int)(c1 - c0), (const NodeWinUnit *)m.units, (int)units.size(), m.ga, m.gb, count, S,
+                                    st);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     *err = e;
