@@ -294,6 +294,7 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
     const int nb = h->nb();
     const int64_t n_pad = coarse_pad(h->ncx, h->ncy, h->ncz, h->K).size;
     double *S = nullptr;
+    int64_t n_grouped = 0;
     hipError_t e = hipSuccess;
     {
         std::lock_guard<std::mutex> lk(cache_mutex());
@@ -336,7 +337,10 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
             e = hipMemcpyAsync(hc.data(), h->count, hc.size() * sizeof(double), hipMemcpyDeviceToHost, st);
             if (e == hipSuccess) e = hipStreamSynchronize(st);
             int64_t used = 0;
-            for (double v : hc) used += v > 0.0;
+            for (double v : hc) {
+                used += v > 0.0;
+                n_grouped += (int64_t)v;
+            }
             h->dense = 2 * used >= h->n_nodes;
             // the product's units of P's layout that hold a node with cells:
             // chunks (zb nodes along z), or groups of 64 / zb chunks for small K
@@ -442,6 +446,7 @@ int fdirw_coarse_create(const fdirw_domain *d, int32_t block, int32_t prec, cons
         if (e == hipSuccess) {
             CoarseGenArgs a;
             a.nx = d->nx; a.ny = d->ny; a.nz = d->nz; a.n = h->n;
+            a.n_grouped = n_grouped;
             a.n_sub = d->n_sub;
             a.lx = lam;
             a.node = (const int *)h->node;

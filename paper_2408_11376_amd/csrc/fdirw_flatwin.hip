@@ -139,8 +139,10 @@ flat_coarse_kernel(CoarseGenArgs a)
     const int B = a.block, K = a.K, KW = 2 * K + 1, nb = KW * KW * KW;
     for (int i = t; i < 2 * LPW * XLEN; i += FLAT_NT) xb[i] = 0.0f;
 
-    const int64_t b = xcd_remap((int)blockIdx.x, (int)gridDim.x);
-    for (int64_t q0 = b * LPW; q0 < a.n; q0 += (int64_t)gridDim.x * LPW) {
+    // consecutive groups on different XCDs: grouped cells may lie in clumps, and
+    // runs of them on one XCD leave the others idle (56^3 cells, r = 8, 5 % in
+    // clumps: 5.3 against 3.6 ms; everything grouped: 43.8 and 43.5)
+    for (int64_t q0 = (int64_t)blockIdx.x * LPW; q0 < a.n; q0 += (int64_t)gridDim.x * LPW) {
         // sources outside every group are skipped (when all of the
         // workgroup's are, the whole trip: uniform per block)
         bool any = false, live = false;

@@ -72,8 +72,10 @@ int field_sum_dev(const double *c, int64_t n, hipStream_t st, DevCache &dc, doub
 void line_shape(const fdirw_domain *d, int tune, int *seg_len, int *n_seg);
 // True when the fused step of this precision and radius runs the flat-layout kernel.
 bool use_flat_layout(int prec, int r, int n_sub);
-// ... and for the window kernels of n_src sources (fdirw_kernels, the bank, the coarse build)
+// ... and for the window kernels of n_src sources (fdirw_kernels, the bank, the surrogate's targets)
 bool use_flat_window(int prec, int r, int64_t n_src);
+// ... and for the coarse build's FP32 kernels of the grouped ones of n cells
+bool use_flat_coarse(int r, int64_t n, int64_t grouped);
 // Source planes per launch of the deterministic step (a function of the
 // domain's shape and radius only, or tune > 0 planes).
 int det_slab_planes(const fdirw_domain *d, int tune);

@@ -87,7 +87,7 @@ constexpr int COARSE_RESERVOIR = -2;   // far-field boundary cell
 
 struct CoarseGenArgs {
     int nx, ny, nz;
-    int64_t n;
+    int64_t n, n_grouped;     // cells, those with node[] >= 0
     int n_sub;
     const void *lx;           // coefficients as in LineArgs
     const int *node;          // [N] node (block) index of a grouped cell, else COARSE_OUTSIDE / _RESERVOIR
