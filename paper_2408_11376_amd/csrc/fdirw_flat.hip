@@ -94,6 +94,8 @@ __device__ __forceinline__ void flush_plane(const Line &a, const double *pl, int
     }
 }
 
+constexpr int FLAT_CS = 32;        // sources of a line read at a time
+
 // LDS of one workgroup at radius R: exchange floats (two buffers per line) and
 // output-plane doubles (one per line and parity); _MAX over the radii 0..8.
 template <int R> constexpr int FLAT_XB = 2 * Flat<R>::LPW * Flat<R>::XLEN;
@@ -115,15 +117,17 @@ template <int R> constexpr int flat_plane_max()
 // threads, F::SG threads per line, the lines side by side in lockstep
 // (their sub-steps share the barriers): kernels generated and superposed into
 // a.c_out (FP64 atomics).  xb: 2 LPW XLEN cells of LDS (16-byte aligned),
-// red: NT / 64 doubles, edge: EDGE doubles, plane: 2 LPW W2 doubles.  Every
-// thread of the block calls it; the first thread of line g leaves the line's smallest and largest kernel mass
-// and its number of kernels in fig[3 g .. 3 g + 2] (LDS; kept there and not in
-// registers, which the sub-step loop needs all).  A window group
+// red: NT / 64 doubles, edge: EDGE doubles, plane: 2 LPW W2 doubles, csrc: LPW
+// FLAT_CS doubles.  Every thread of the block calls it; the first thread of line
+// g leaves the line's smallest and largest kernel mass and its number of kernels
+// in fig[3 g .. 3 g + 2] (LDS; kept there and not in registers, which the
+// sub-step loop needs all).  A window group
 // past nlines runs on zero coefficients and writes nothing.  DET:
 // the deterministic form (partial slots, a.part).
 template <typename F, bool DET, typename Faces>
 __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, int nlines, int z0, int z1,
-                                          typename F::S *xb, double *red, double *edge, double *plane, double *fig)
+                                          typename F::S *xb, double *red, double *edge, double *plane, double *fig,
+                                          double *csrc)
 {
     using S = typename F::S;
     constexpr int R = F::R, FLAT_EDGE = F::EDGE;
@@ -141,9 +145,6 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     const bool live = LPW == 1 || g < nlines;
     const int ln = line0 + (live ? g : 0);
     const int sy = ln / a.nx, sx = ln - sy * a.nx;
-    int lofs[LPW];                                           // (y, x) offsets of the workgroup's lines
-#pragma unroll
-    for (int h = 0; h < LPW; ++h) lofs[h] = line0 + h;
     S *const xg = xb + g * XLEN;                         // the line's first exchange buffer
     __syncthreads();                                        // LDS of a previous line is no longer read
     for (int i = t; i < 2 * LPW * XLEN; i += F::NT) xb[i] = S(0);
@@ -161,23 +162,36 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
 #pragma unroll
     for (int k = 0; k < RUN; ++k) acc[k] = 0.0;
     int par = 0;
+    int last = z0 - W;                                       // the last source with a kernel: the ring holds planes up to last + R
 
-    for (int sz = z0; sz < z1; ++sz) {
+    // FLAT_CS sources of every line at a time, into LDS: the memory's latency is
+    // met once for all of them, which is what lines without sources wait for
+    // (61 x 57 x 60 cells, one nonzero source, ms with a load per source / so: FP64
+    // r = 7 1.14 / 0.20, r = 8 1.44 / 0.18, FP32 r = 8 1.03 / 0.11; 10 % nonzero,
+    // FP64 r = 6, 8 sub-steps 1.18 / 0.96).  Bit k of some: a line has a nonzero
+    // source at the k-th one from sz on.
+    unsigned some = 0;
+    for (int sz = z0; sz < z1; ++sz, some >>= 1) {
+        if (((sz - z0) & (FLAT_CS - 1)) == 0) {
+            const int z = sz + (t & (FLAT_CS - 1));
+            bool nz = false;
+#pragma unroll
+            for (int h = 0; h < LPW; ++h) {
+                const double c = h < nlines && z < z1 ? a.c_in[(int64_t)z * nxy + line0 + h] : 0.0;
+                nz = nz || c != 0.0;
+                if (t / FLAT_CS == h) csrc[t] = c;               // read after the next barrier, written after the last read's
+            }
+            some = (unsigned)__ballot(nz);
+        }
+        // a kernel is generated for every line when one of them has a nonzero
+        // source; past the window of the last one the ring is empty and stays
+        // so (DET stores the zeros).  Uniform per block.
+        const bool any = some & 1u;
+        if (!DET && !any && sz - last >= W) continue;
         int s0v = act ? s0 : F::NCELL;
         asm volatile("" : "+v"(s0v));
-        // the sources of the workgroup's lines: a kernel is generated for
-        // every line when one of them is nonzero (uniform per block)
-        double cs = 0.0;
-        bool any = false;
-#pragma unroll
-        for (int h = 0; h < LPW; ++h) {
-            if (h < nlines) {
-                const double c = a.c_in[(int64_t)sz * nxy + lofs[h]];
-                any = any || c != 0.0;
-                if (h == g) cs = c;
-            }
-        }
         if (any) {
+            last = sz;
             FlatSeg<F> c;
             flat_load<F>(c, a.f, a.nx, a.ny, a.nz, sx, sy, sz, s0v);
             S Gs[RUN];
@@ -194,10 +208,7 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
                 for (int k = 0; k < RUN; ++k) ms += (double)Gs[k];
             }
             const double m = flat_window_sum<F>(ms, red, g);
-            // (the source is read again, not kept across the sub-steps)
-            int gv = g;
-            asm volatile("" : "+v"(gv));
-            cs = live ? a.c_in[(int64_t)sz * nxy + line0 + gv] : 0.0;
+            const double cs = csrc[g * FLAT_CS + ((sz - z0) & (FLAT_CS - 1))];   // 0 past the last line
             if (tg == 0 && cs != 0.0) {
                 fig[3 * g] = fmin(fig[3 * g], m);
                 fig[3 * g + 1] = fmax(fig[3 * g + 1], m);
@@ -237,9 +248,11 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
         par ^= 1;
     }
     // the planes still held: after the last shift cell (col, z) holds plane
-    // z1 - R + z (z = W - 1 holds the plane no source reached yet: zeros)
+    // z1 - R + z (z = W - 1 holds the plane no source reached yet: zeros), up to
+    // plane last + R
     const int s0v = act ? s0 : F::NCELL;
-    for (int zp = 0; zp < W - 1; ++zp) {
+    const int zp_end = DET ? W - 1 : min(W - 1, last + W - z1);
+    for (int zp = 0; zp < zp_end; ++zp) {
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
             const FlatCell<F> p(s0v + k);
@@ -268,16 +281,17 @@ flat_line_kernel(LineArgs a)
     const int z1 = min(a.z_end, z0 + a.seg_len);
     if (z0 >= z1) return;                                   // uniform per block
     __shared__ double fig[3 * F::LPW];
+    __shared__ double csrc[F::LPW * FLAT_CS];
     if constexpr (LAB) {
         const FaceLabels<S> f{a.label, (const S *)a.lam_tab, a.n_phase, a.nx, a.ny, a.nz};
         const FlatLine<FaceLabels<S>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, f,
                                          a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
-        flat_line<F, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
+        flat_line<F, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig, csrc);
     } else {
         const S *lx = (const S *)a.lx;
         const FlatLine<FaceArrays<S>> fl{a.nx,   a.ny,    a.nz,   a.n,         a.n_sub, {lx, lx + a.n, lx + 2 * a.n},
                                          a.c_in, a.c_out, a.part, a.part_z0, a.part_planes};
-        flat_line<F, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig);
+        flat_line<F, DET>(fl, line0, nlines, z0, z1, xb, red, edge, plane, fig, csrc);
     }
     // per line and segment: entry line n_seg + sgi of the kernel-mass range
     const int g = (int)threadIdx.x / F::SG;
@@ -304,7 +318,8 @@ template <typename T> __device__ __forceinline__ T *uniform(T *p)
 template <int R>
 __device__ __attribute__((noinline)) void flat_line_item(const FlatLine<FaceArrays<float>> &a, int line0, int nlines,
                                                           int z0, int z1, float *xb, double *red,
-                                                          double *edge, double *plane, double *fig, double *km, int *used)
+                                                          double *edge, double *plane, double *fig, double *csrc, double *km,
+                                                          int *used)
 {
     // arguments of a function arrive in vector registers: without this the
     // sub-step loop counts per lane, and its registers are copied every trip
@@ -314,7 +329,7 @@ __device__ __attribute__((noinline)) void flat_line_item(const FlatLine<FaceArra
     const FlatLine<FaceArrays<float>> u{nx, ny, nz, n, uniform(a.n_sub), {lx, lx + n, lx + 2 * n},
                                         uniform(a.c_in), uniform(a.c_out), nullptr, 0, 0};
     nlines = uniform(nlines);
-    flat_line<Flat<R>, false>(u, uniform(line0), nlines, uniform(z0), uniform(z1), xb, red, edge, plane, fig);
+    flat_line<Flat<R>, false>(u, uniform(line0), nlines, uniform(z0), uniform(z1), xb, red, edge, plane, fig, csrc);
     const int t = threadIdx.x;
     __syncthreads();                                         // every line's figures are there
     if (t == 0) {
@@ -341,7 +356,8 @@ flat_batched_kernel(BatchArgs a)
     __shared__ double red[4];
     __shared__ double edge[Flat<8>::EDGE];
     __shared__ double plane[flat_plane_max<8>()];
-    __shared__ double fig[3 * (FLAT_NT / 32)];
+    __shared__ double fig[3 * (FLAT_NT / 64)];
+    __shared__ double csrc[FLAT_NT / 64 * FLAT_CS];
     __shared__ int s_item;
     for (;;) {
         if (threadIdx.x == 0) s_item = (int)atomicAdd(a.head, 1u);
@@ -357,15 +373,15 @@ flat_batched_kernel(BatchArgs a)
         double km[2];
         int used = 0;
         switch (d.r) {
-        case 0: flat_line_item<0>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        case 1: flat_line_item<1>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        case 2: flat_line_item<2>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        case 3: flat_line_item<3>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        case 4: flat_line_item<4>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        case 5: flat_line_item<5>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        case 6: flat_line_item<6>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        case 7: flat_line_item<7>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
-        default: flat_line_item<8>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, km, &used); break;
+        case 0: flat_line_item<0>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        case 1: flat_line_item<1>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        case 2: flat_line_item<2>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        case 3: flat_line_item<3>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        case 4: flat_line_item<4>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        case 5: flat_line_item<5>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        case 6: flat_line_item<6>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        case 7: flat_line_item<7>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
+        default: flat_line_item<8>(fl, item.line0, item.nlines, item.z0, item.z1, xb, red, edge, plane, fig, csrc, km, &used); break;
         }
         if (threadIdx.x == 0) {
             if (a.item_kmass) { a.item_kmass[2 * it] = km[0]; a.item_kmass[2 * it + 1] = km[1]; }
