@@ -286,23 +286,45 @@ static bool flat_radius(int r, int lo)
 // flat64_min_sub sub-steps on.  Measured (61 x 57 x 60 cells, ms, segments /
 // flat; 2 sub-steps, then 28 (r / 3)^2): r = 3 0.45 / 0.80, 1.68 / 1.46; r = 4
 // 1.05 / 0.93, 7.1 / 4.4; r = 5 1.23 / 2.49, 16.1 / 13.4; r = 6 3.5 / 4.9, 59.0 /
-// 32.1; r = 7 4.3 / 6.7, 97.3 / 70.8; r = 8 7.0 / 11.4, 160 / 119.
+// 32.1; r = 7 4.3 / 6.7, 97.3 / 70.8; r = 8 7.0 / 11.4, 160 / 119.  At the lines:
+// r = 3 1.44 / 1.17, r = 4 1.06 / 0.91, r = 5 6.2 / 5.4, r = 6 6.5 / 5.4, r = 8 24.1
+// / 21.6; 24^3 cells 0.17 / 0.16, 0.14 / 0.14, 0.47 / 0.45, 0.53 / 0.45, 1.76 /
+// 1.55; r = 7, 16 sub-steps 12.85 / 12.86 and, 10 % of the sources nonzero, 1.99 /
+// 2.26, 60 sub-steps 39.8 / 31.9 and 5.2 / 4.6.
 static int flat64_min_sub(int r)
 {
     switch (r) {
     case 4: return 2;
     case 5: return 28;
     case 6: return 8;
-    case 7: return 16;
+    case 7: return 28;
     default: return 24;
+    }
+}
+
+// FP32: the same, with coefficient loads that touch a cache line per lane.
+// Measured (61 x 57 x 60 cells, ms, segments / flat at two sub-step counts): r = 4
+// 10 1.04 / 1.04, 20 1.65 / 1.35; r = 5 10 1.76 / 2.39, 20 3.00 / 2.63; r = 6 1 2.66
+// / 3.81, 10 5.53 / 3.94; r = 7 20 7.05 / 9.12, 40 12.7 / 13.3 (24^3 cells 0.91 /
+// 1.01); r = 8 20 11.9 / 14.6, 40 20.2 / 16.1.
+static int flat32_min_sub(int r)
+{
+    switch (r) {
+    case 4: return 12;
+    case 5: return 15;
+    case 6: return 5;
+    case 7: return 48;
+    default: return 26;
     }
 }
 
 bool use_flat_layout(int prec, int r, int n_sub)
 {
     if (prec == FDIRW_FP64) return flat_radius(r, 3) && n_sub >= flat64_min_sub(r);
-    return prec == FDIRW_FP32 && flat_radius(r, 4);
+    return prec == FDIRW_FP32 && flat_radius(r, 4) && n_sub >= flat32_min_sub(r);
 }
+
+bool use_flat_flow(int r) { return flat_radius(r, 4); }
 
 // A segment-layout workgroup puts 10 waves on one window where a flat one has
 // 4 for one to four of them, so it is the faster one until the flat

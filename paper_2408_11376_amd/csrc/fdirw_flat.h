@@ -82,8 +82,8 @@ template <typename S_, int R_, int NT_, int SG_, int RUN_, int WPE_> struct Flat
 };
 
 // FP32: see line_threads.
-template <int R>
-using Flat = FlatGeo<float, R, FLAT_NT, line_threads(R), run_for(flat_cells(R, 4), line_threads(R)), 3>;
+template <int R, int WPE = 3>
+using Flat = FlatGeo<float, R, FLAT_NT, line_threads(R), run_for(flat_cells(R, 4), line_threads(R)), WPE>;
 
 // FP64, one window per workgroup (r = 3..8): 10 cells per thread at r = 6 and 8
 // (256 and 512 threads of two waves per SIMD: 221 and 493 busy), 6 at the others

@@ -94,6 +94,21 @@ __device__ __forceinline__ void flush_plane(const Line &a, const double *pl, int
     }
 }
 
+// Plane Z of a line whose ring is empty: nothing to add, and in the
+// deterministic form zeros in its slots.
+template <int R, int SG, bool DET, typename Line>
+__device__ __forceinline__ void flush_empty(const Line &a, int sx, int sy, int Z, int tg)
+{
+    constexpr int W = 2 * R + 1, W2 = W * W;
+    if (!DET || Z < 0 || Z >= a.nz) return;
+    const int64_t nxy = (int64_t)a.nx * a.ny;
+    for (int col = tg; col < W2; col += SG) {
+        const int X = sx - R + col % W, Y = sy - R + col / W;
+        if (X >= 0 && X < a.nx && Y >= 0 && Y < a.ny)
+            a.part[((int64_t)col * a.part_planes + (Z - a.part_z0)) * nxy + (int64_t)Y * a.nx + X] = 0.0;
+    }
+}
+
 constexpr int FLAT_CS = 32;        // sources of a line read at a time
 
 // LDS of one workgroup at radius R: exchange floats (two buffers per line) and
@@ -185,9 +200,12 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
         }
         // a kernel is generated for every line when one of them has a nonzero
         // source; past the window of the last one the ring is empty and stays
-        // so (DET stores the zeros).  Uniform per block.
+        // so.  Uniform per block.
         const bool any = some & 1u;
-        if (!DET && !any && sz - last >= W) continue;
+        if (!any && sz - last >= W) {
+            if (live) flush_empty<R, SG, DET>(a, sx, sy, sz - R, tg);
+            continue;
+        }
         int s0v = act ? s0 : F::NCELL;
         asm volatile("" : "+v"(s0v));
         if (any) {
@@ -251,7 +269,7 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
     // z1 - R + z (z = W - 1 holds the plane no source reached yet: zeros), up to
     // plane last + R
     const int s0v = act ? s0 : F::NCELL;
-    const int zp_end = DET ? W - 1 : min(W - 1, last + W - z1);
+    const int zp_end = max(0, min(W - 1, last + W - z1));
     for (int zp = 0; zp < zp_end; ++zp) {
 #pragma unroll
         for (int k = 0; k < RUN; ++k) {
@@ -262,6 +280,8 @@ __device__ __forceinline__ void flat_line(const FlatLine<Faces> &a, int line0, i
         if (live) flush_plane<R, SG, DET>(a, plane + (par * LPW + g) * W2, sx, sy, z1 - R + zp, tg);
         par ^= 1;
     }
+    for (int zp = zp_end; DET && zp < W - 1; ++zp)
+        if (live) flush_empty<R, SG, DET>(a, sx, sy, z1 - R + zp, tg);
 }
 
 template <typename F, bool LAB, bool DET>
@@ -406,22 +426,36 @@ int flat_lines_per_group(int r)
     return r >= 0 && r <= 8 ? FLAT_NT / line_threads(r) : 1;
 }
 
-template <typename F, bool LAB>
+template <typename F, bool LAB, bool DET>
 static hipError_t launch_flat_f(const LineArgs &a, hipStream_t st)
 {
     const int64_t groups = ((int64_t)a.nx * a.ny + F::LPW - 1) / F::LPW;
-    const int64_t nblk = groups * a.n_seg;
-    if (a.part)
-        hipLaunchKernelGGL((flat_line_kernel<F, LAB, true>), dim3((unsigned)nblk), dim3(F::NT), 0, st, a);
-    else
-        hipLaunchKernelGGL((flat_line_kernel<F, LAB, false>), dim3((unsigned)nblk), dim3(F::NT), 0, st, a);
+    hipLaunchKernelGGL((flat_line_kernel<F, LAB, DET>), dim3((unsigned)(groups * a.n_seg)), dim3(F::NT), 0, st, a);
     return hipGetLastError();
 }
+
+// FP32: three waves per SIMD, or two where the registers count for more than the
+// sub-steps.  r = 6: at three, part of a source's coefficients is spilled while
+// they are loaded.  Measured (two / three, ms): 61 x 57 x 60 cells, 10 sub-steps
+// 3.94 / 5.08, 40 7.32 / 7.38, 112 16.4 / 15.7; 96 x 40 x 40, 40 5.48 / 5.89, 90
+// 10.2 / 10.5, 150 15.9 / 16.2; 80^3, 56 23.0 / 23.1, 112 40.9 / 39.6.
+// Deterministic form: a launch holds a slab of planes only, and short lines meet
+// the spills around their ends more often.  40^3 cells, 100 sub-steps: r = 6
+// 5.79 / 7.41 ms, r = 7 10.3 / 10.7, r = 8 10.9 / 11.7.
+constexpr int FLAT6_THREE_WAVES = 96;
 
 template <int R, bool LAB>
 static hipError_t launch_flat_r(int mode, const LineArgs &a, hipStream_t st)
 {
-    return mode == M_FP64 ? launch_flat_f<Flat64<R>, LAB>(a, st) : launch_flat_f<Flat<R>, LAB>(a, st);
+    if (mode == M_FP64)
+        return a.part ? launch_flat_f<Flat64<R>, LAB, true>(a, st) : launch_flat_f<Flat64<R>, LAB, false>(a, st);
+    if constexpr (R >= 4) {
+        if (a.part) return launch_flat_f<Flat<R, R >= 6 ? 2 : 3>, LAB, true>(a, st);
+        if constexpr (R == 6)
+            if (a.n_sub < FLAT6_THREE_WAVES) return launch_flat_f<Flat<R, 2>, LAB, false>(a, st);
+        return launch_flat_f<Flat<R>, LAB, false>(a, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 template <bool LAB>
@@ -431,7 +465,7 @@ static hipError_t launch_flat(int mode, int r, const LineArgs &a, hipStream_t st
     // that each partial slot has one writer)
     if ((mode != M_FP32 && mode != M_FP64) || (a.part && a.n_seg != 1)) return hipErrorInvalidValue;
     switch (r) {
-    case 3: return mode == M_FP64 ? launch_flat_f<Flat64<3>, LAB>(a, st) : hipErrorInvalidValue;
+    case 3: return launch_flat_r<3, LAB>(mode, a, st);
     case 4: return launch_flat_r<4, LAB>(mode, a, st);
     case 5: return launch_flat_r<5, LAB>(mode, a, st);
     case 6: return launch_flat_r<6, LAB>(mode, a, st);

@@ -70,8 +70,10 @@ int prepare_geometry(const fdirw_domain *d, hipStream_t st, DevCache &dc, double
 int coef_buffers(const fdirw_domain *d, int prec, hipStream_t st, DevCache &dc, Geometry *g, const void **lam);
 int field_sum_dev(const double *c, int64_t n, hipStream_t st, DevCache &dc, double *out_host);
 void line_shape(const fdirw_domain *d, int tune, int *seg_len, int *n_seg);
-// True when the fused step of this precision and radius runs the flat-layout kernel.
+// True when the fused step of this precision, radius and number of sub-steps runs the flat-layout kernel.
 bool use_flat_layout(int prec, int r, int n_sub);
+// ... and for the FP32 window kernels with a flow
+bool use_flat_flow(int r);
 // ... and for the window kernels of n_src sources (fdirw_kernels, the bank, the surrogate's targets)
 bool use_flat_window(int prec, int r, int64_t n_src);
 // ... and for the coarse build's FP32 kernels of the grouped ones of n cells
