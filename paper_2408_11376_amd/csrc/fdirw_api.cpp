@@ -326,17 +326,37 @@ bool use_flat_layout(int prec, int r, int n_sub)
 
 bool use_flat_flow(int r) { return flat_radius(r, 4); }
 
+// Window kernels: with few sub-steps the flat layout's coefficient loads (a
+// cache line per lane) weigh more than its sub-steps save.  Measured (ms,
+// segments / flat; 20,000 sources of 40^3 cells for fdirw_kernels, all 64,000 for
+// a bank, which the segment layout also stores with more lanes idle):
+//   r = 4  kernels 5 0.152 / 0.165, 10 0.175 / 0.174; bank 0 0.59 / 0.41
+//   r = 5  kernels 10 0.27 / 0.37, 20 0.37 / 0.37; bank 0 0.97 / 0.98
+//   r = 6  kernels 10 0.51 / 0.69, 20 0.72 / 0.74; bank 10 1.93 / 2.09, 20 2.45 / 2.23
+//   r = 7  kernels 0 0.45 / 0.48, 2 0.52 / 0.51; bank 0 2.3 / 2.0
+//   r = 8  kernels 10 0.95 / 1.07, 20 1.40 / 1.12; bank 10 4.1 / 4.6, 20 5.2 / 4.6
+static int flat_window_min_sub(int r, bool bank)
+{
+    static const int kernels[5] = {10, 20, 22, 2, 14}, banks[5] = {0, 0, 14, 0, 14};
+    return r >= 4 && r <= 8 ? (bank ? banks : kernels)[r - 4] : 0;
+}
+
 // A segment-layout workgroup puts 10 waves on one window where a flat one has
 // 4 for one to four of them, so it is the faster one until the flat
 // workgroups fill the 256 CUs about one and a half times.  Measured (us per
 // call, segments / flat; 200, 113, 50 sub-steps): r = 8, 256 sources 192 /
 // 247, 384 304 / 261; r = 6, 512 137 / 176, 768 177 / 190, 1024 244 / 198; r =
 // 4, 1024 94 / 96, 1536 103 / 101, 4096 145 / 129.
-bool use_flat_window(int prec, int r, int64_t n_src)
+static bool flat_window_fills(int r, int64_t n_src)
+{
+    const int per = flat_lines_per_group(r);
+    return n_src > (per > 1 ? 384 * per : 256);
+}
+
+bool use_flat_window(int prec, int r, int64_t n_src, int n_sub, bool bank)
 {
     const bool mode = prec == FDIRW_FP32 || prec == FDIRW_FP16_BANK || prec == FDIRW_BF16_BANK;
-    const int per = flat_lines_per_group(r);
-    return mode && flat_radius(r, 4) && n_src > (per > 1 ? 384 * per : 256);
+    return mode && flat_radius(r, 4) && flat_window_fills(r, n_src) && n_sub >= flat_window_min_sub(r, bank);
 }
 
 // The flat coarse build runs one to four consecutive cells as one workgroup and
@@ -345,10 +365,14 @@ bool use_flat_window(int prec, int r, int64_t n_src)
 // build, segments / flat; grouped cells at random): r = 4, all 3.33 / 2.43, 70 %
 // 2.31 / 2.19, 60 % 2.02 / 2.09, 20 % 0.89 / 1.49; r = 5, all 9.05 / 5.81, 35 %
 // 3.64 / 3.55, 25 % 2.74 / 2.87; r = 6, 5 % 3.65 / 2.13; r = 7, 5 % 3.19 / 2.72; r
-// = 8, 5 % 7.20 / 3.47, 86 cells 1.57 / 0.82.
-bool use_flat_coarse(int r, int64_t n, int64_t grouped)
+// = 8, 5 % 7.20 / 3.47, 86 cells 1.57 / 0.82.  By sub-steps (40^3, two thirds
+// grouped): r = 4 40 0.74 / 0.74; r = 5 20 0.91 / 0.95, 40 1.41 / 1.25; r = 6 5 1.77
+// / 1.90, 10 2.21 / 2.03; r = 7 40 3.27 / 3.38, 80 5.77 / 5.28; r = 8 10 2.86 /
+// 2.83.
+bool use_flat_coarse(int r, int64_t n, int64_t grouped, int n_sub)
 {
-    if (!use_flat_window(FDIRW_FP32, r, n)) return false;
+    static const int min_sub[5] = {40, 22, 8, 48, 10};
+    if (!flat_radius(r, 4) || !flat_window_fills(r, n) || n_sub < min_sub[r - 4]) return false;
     return r == 4 ? 3 * grouped > 2 * n : r == 5 ? 3 * grouped > n : true;
 }
 

@@ -865,7 +865,7 @@ static hipError_t launch_cw_m(int r, const CoarseGenArgs &a, hipStream_t st)
 
 hipError_t launch_coarse_window(int fp64, int sink, int r, const CoarseGenArgs &a, hipStream_t st)
 {
-    if (!fp64 && use_flat_coarse(r, a.n, a.n_grouped)) return launch_coarse_flat(sink, r, a, st);
+    if (!fp64 && use_flat_coarse(r, a.n, a.n_grouped, a.n_sub)) return launch_coarse_flat(sink, r, a, st);
     if (sink) return fp64 ? launch_cw_m<M_FP64, true>(r, a, st) : launch_cw_m<M_FP32, true>(r, a, st);
     return fp64 ? launch_cw_m<M_FP64, false>(r, a, st) : launch_cw_m<M_FP32, false>(r, a, st);
 }

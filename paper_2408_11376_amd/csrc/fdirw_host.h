@@ -75,9 +75,10 @@ bool use_flat_layout(int prec, int r, int n_sub);
 // ... and for the FP32 window kernels with a flow
 bool use_flat_flow(int r);
 // ... and for the window kernels of n_src sources (fdirw_kernels, the bank, the surrogate's targets)
-bool use_flat_window(int prec, int r, int64_t n_src);
+// (bank: in the bank's layout)
+bool use_flat_window(int prec, int r, int64_t n_src, int n_sub, bool bank);
 // ... and for the coarse build's FP32 kernels of the grouped ones of n cells
-bool use_flat_coarse(int r, int64_t n, int64_t grouped);
+bool use_flat_coarse(int r, int64_t n, int64_t grouped, int n_sub);
 // Source planes per launch of the deterministic step (a function of the
 // domain's shape and radius only, or tune > 0 planes).
 int det_slab_planes(const fdirw_domain *d, int tune);

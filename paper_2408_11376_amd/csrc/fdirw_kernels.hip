@@ -745,7 +745,7 @@ hipError_t launch_line_labels(int mode, int r, const LineArgs &a, hipStream_t st
 
 hipError_t launch_window(int mode, int r, const WindowArgs &a, hipStream_t st)
 {
-    if (use_flat_window(mode, r, a.n_src)) return launch_window_flat(mode, r, a, st);
+    if (use_flat_window(mode, r, a.n_src, a.n_sub, a.offset_major != 0)) return launch_window_flat(mode, r, a, st);
     switch (mode) {
     case M_FP64: return launch_window_m<M_FP64>(r, a, st);
     case M_FP32: return launch_window_m<M_FP32>(r, a, st);
