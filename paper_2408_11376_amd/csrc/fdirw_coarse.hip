@@ -734,13 +734,20 @@ __global__ void coarse_remap_kernel(const double *__restrict__ c_in, const int *
 // workgroup takes REMAP_ROWS rows of x, a thread the same x of each: one division
 // by B per thread, the rows' blocks are uniform, and the rows' loads are in
 // flight together.  It pays where the fields and the indices (20 bytes per cell)
-// near or outgrow the 256 MB last-level cache.  Measured (us per coarse step
-// marching between two fields, by index / by role): 300 x 256 x 256 130 / 117,
-// 256 x 256 x 200 70.0 / 62.1, 192^3 43.6 / 43.5 (rotating over several pairs of
-// fields 59.7 / 52.9), 97 x 91 x 88 16.7 / 18.3.
+// come from memory and the rows fill the lanes of their waves.  Measured (us per
+// coarse step, B = 5, by index / by role, marching between two fields and, after
+// the comma, over four pairs of them): 110^3 18.0 / 20.0, 18.1 / 19.8; 144^3 27.3 /
+// 28.8, 27.3 / 29.1; 160^3 30.3 / 31.0, 31.2 / 31.9; 172^3 34.5 / 34.2, 36.5 / 35.9;
+// 184^3 40.2 / 38.4, 43.9 / 41.4; 216^3 56.1 / 55.2, 66.0 / 62.6; 256 x 256 x 224
+// 99.3 / 76.8, 108.6 / 87.9.  By the length of the rows, 5.6 to 8 million cells: 41
+// 50.7 / 55.9; 60 45.6 / 43.7; 90 39.3 / 42.9; 104 42.2 / 43.1; 120 41.4 / 40.1; 200
+// 48.3 / 48.7; 220 39.6 / 39.4; 300 44.8 / 44.5; 500 47.9 / 46.1.
 constexpr int REMAP_ROWS = 4;
-constexpr int REMAP_MIN_NX = 40;                // narrower rows leave the lanes idle
 constexpr int64_t REMAP_MIN_CELLS = 5 << 20;
+
+// Whether a row of nx cells uses 5 of 6 lanes of its waves (rows beyond a
+// workgroup: always).
+static bool remap_fills(int nx) { return nx >= 256 || 6 * nx >= 5 * ru(nx, 64); }
 
 __global__ void __launch_bounds__(256) coarse_remap_rows_kernel(const double *__restrict__ c_in,
                                                                 const uint8_t *__restrict__ role,
@@ -1211,7 +1218,7 @@ hipError_t launch_coarse_remap(const double *c_in, const int *node, const uint8_
 {
     const int64_t n_rows = (int64_t)ny * nz, n = n_rows * nx;
     const int64_t grid = (n_rows + REMAP_ROWS - 1) / REMAP_ROWS;
-    if (n >= REMAP_MIN_CELLS && nx >= REMAP_MIN_NX && grid <= INT32_MAX) {
+    if (n >= REMAP_MIN_CELLS && remap_fills(nx) && grid <= INT32_MAX) {
         const int nt = nx < 256 ? ru(nx, 64) : 256;
         hipLaunchKernelGGL(coarse_remap_rows_kernel, dim3((unsigned)grid), dim3(nt), 0, st, c_in, role, cnew, nx, ny,
                            n_rows, B, ncx, ncy, c_out);
