@@ -592,21 +592,28 @@ int64_t bank_elems(int nx, int ny, int nz, int r, int elem_bytes)
 
 // Parts that the source rows (offsets oy) of a tile are cut into: a wave keeps
 // W KB of bank reads in flight and waits for them (W times per row), so a small
-// grid needs more workgroups than it has tiles: up to BANK_GROUPS, about what
-// 256 CUs hold at once.  The parts are summed in order by a second launch.
-// Measured, 50 applies with the bank's generation (2 sub-steps), ms, whole /
-// split: FP16 20 x 18 x 16 r = 8 19.8 / 2.6, 24^3 r = 3 2.46 / 0.85, 56 x 48 x 52
-// r = 8 36.6 / 24.4, 70 x 64 x 64 57.7 / 54.5; FP32 56 x 48 x 52 36.7 / 35.8; a
-// target of 256 or 1024 groups: 25.7 and 25.3 for the 24.4.
-constexpr int BANK_GROUPS = 768;
+// grid needs more workgroups than it has tiles: parts of W groups / BANK_GROUPS
+// rows, summed in order by a second launch.  Only where the rounds of one
+// workgroup per CU that they save are more than a quarter: the parts are written
+// and read once more.  Measured, us per apply, whole / split (tiles): FP16 r = 8
+// 529 / 227 (60), 599 / 528 (148), 726 / 756 (200), 853 / 863 (256), 1217 / 1067
+// (300), 1408 / 1347 (380), 1521 / 1617 (448), 2374 / 2401 (680); FP32 r = 8 684 /
+// 727 (200), 1252 / 1138 (340), 1288 / 1337 (380); FP16 r = 5 241 / 209 (200), 349 /
+// 308 (300), 379 / 393 (380), 437 / 468 (448), 703 / 765 (740); FP64 r = 3 44 / 41
+// (148), 89 / 82 (300), 109 / 120 (448).  Aims of 256 or 1024 groups instead of 768
+// on 56 x 48 x 52, FP16, r = 8, 50 applies: 25.7 and 25.3 ms for 24.4.
+constexpr int BANK_GROUPS = 768, BANK_CUS = 256;
 
 int bank_split(int prec, int r, int nx, int ny, int nz)
 {
     const int zb = 16 / (int)bank_elem_bytes(prec), tz = FDIRW_GATHER_TZW * zb;
     const int64_t groups = (int64_t)((nx + 63) / 64) * ny * ((nz + tz - 1) / tz);
     const int w = 2 * r + 1;
-    const int rows = (int)std::max<int64_t>(1, w * groups / BANK_GROUPS);   // source rows per part
-    return rows >= w ? 1 : (w + rows - 1) / rows;
+    const int64_t rows = std::max<int64_t>(1, w * groups / BANK_GROUPS);   // source rows per part
+    if (rows >= w) return 1;
+    const int64_t parts = (w + rows - 1) / rows;
+    const auto rounds = [](int64_t g) { return (g + BANK_CUS - 1) / BANK_CUS; };
+    return 4 * rounds(groups * parts) < 3 * parts * rounds(groups) ? (int)parts : 1;
 }
 
 hipError_t launch_bank_apply(int prec, int r, const BankArgs &a, hipStream_t st)
