@@ -78,13 +78,28 @@ def window_cells(shape, r):
     return total
 
 
+CSRC = os.path.join(ROOT, "paper_2408_11376_amd", "csrc")
+KERNEL_SOURCES = ("fdirw_device.h", "fdirw_kernels.hip", "fdirw_flat.h", "fdirw_flat.hip")
+
+
 def kernel_source_hash():
     """Hash of the sources that define the fused line kernel."""
     h = hashlib.sha256()
-    csrc = os.path.join(ROOT, "paper_2408_11376_amd", "csrc")
-    for f in ("fdirw_device.h", "fdirw_kernels.hip", "fdirw_flat.hip"):
-        h.update(open(os.path.join(csrc, f), "rb").read())
+    for f in KERNEL_SOURCES:
+        h.update(open(os.path.join(CSRC, f), "rb").read())
     return h.hexdigest()[:16]
+
+
+# Sub-steps from which a step of this radius runs flat_line_kernel
+# (flat32_min_sub, flat64_min_sub of csrc/fdirw_api.cpp).
+FLAT_MIN_SUB = {"fp32": {4: 12, 5: 15, 6: 5, 7: 48, 8: 26}, "fp64": {3: 24, 4: 2, 5: 28, 6: 8, 7: 28, 8: 24}}
+
+
+def fused_kernel(prec, r, n_sub):
+    """Name of the fused kernel that a step runs."""
+    at = FLAT_MIN_SUB.get(prec, {}).get(r)
+    flat = at is not None and n_sub >= at and os.environ.get("FDIRW_FUSED_LAYOUT") != "segments"
+    return "flat_line_kernel" if flat else "line_kernel"
 
 
 def read_profile_values(kernel_tag, suffix, keys):
@@ -649,8 +664,7 @@ def main():
     # cell-sub-step) and FMA issue time at one FMA per lane per clock
     t_lds = cs * (4 * esize / LDS_READ_B_PER_CLK + esize / LDS_WRITE_B_PER_CLK) / CU_HZ
     t_valu = cs * FMA_PER_CELL_SUBSTEP / (64 * CU_HZ)
-    flat = args.prec == "fp32" and 4 <= d.r <= 8 and os.environ.get("FDIRW_FUSED_LAYOUT") != "segments"
-    kname = "flat_line_kernel" if flat else "line_kernel"
+    kname = fused_kernel(args.prec, d.r, d.n_sub)
     kernel_tag = f"{kname}_{args.prec}_grf{args.n}"
     traffic = read_traffic(kernel_tag)
     roofline = {"bound": "alu", "achieved": achieved, "peak": PEAK_FP32_VECTOR_TFLOPS, "unit": "TFLOP/s",
