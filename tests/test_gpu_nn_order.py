@@ -63,7 +63,14 @@ RUNS = [
     (513, 20, False, 5, [
         (0xe43c7cdf, "0x1.e8e9bdfdcf37ap+0", "0x1.1f73bc47d2320p+0"),
         (0x583caec3, "0x1.e626dc33f0a72p+0", "0x1.1efde70ccecdbp+0"),
-        (0xf98e6b44, "0x1.e1b8e7b2b7dfbp+0", "0x1.1e2e4913b2bdap+0")])
+        (0xf98e6b44, "0x1.e1b8e7b2b7dfbp+0", "0x1.1e2e4913b2bdap+0")]),
+    (293, 12, True, 6, [
+        (0xf2cb8ca1, "0x1.a87a88d1b3d16p-4", "0x1.fd690a7ad9462p-1"),
+        (0x36c35a94, "0x1.f5fccf2874376p-4", "0x1.ffd6fc11c3060p-1"),
+        (0x09fb5924, "0x1.32841494fa74bp-3", "0x1.0178ac7d56983p+0")]),
+    (512, 9, True, 7, [
+        (0x08b1cd79, "-0x1.10f9162756f2bp-5", "0x1.f33ad0b72b1e7p-1"),
+        (0x43230dac, "-0x1.23cbf3426a4b4p-6", "0x1.f61425ad19093p-1")])
 ]
 
 
