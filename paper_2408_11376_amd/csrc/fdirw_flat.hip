@@ -439,23 +439,37 @@ static hipError_t launch_flat_f(const LineArgs &a, hipStream_t st)
 // they are loaded.  Measured (two / three, ms): 61 x 57 x 60 cells, 10 sub-steps
 // 3.94 / 5.08, 40 7.32 / 7.38, 112 16.4 / 15.7; 96 x 40 x 40, 40 5.48 / 5.89, 90
 // 10.2 / 10.5, 150 15.9 / 16.2; 80^3, 56 23.0 / 23.1, 112 40.9 / 39.6.
-// Deterministic form: a launch holds a slab of planes only, and short lines meet
-// the spills around their ends more often.  40^3 cells, 100 sub-steps: r = 6
-// 5.79 / 7.41 ms, r = 7 10.3 / 10.7, r = 8 10.9 / 11.7.
-constexpr int FLAT6_THREE_WAVES = 96;
+// Deterministic form: a launch holds a slab of planes only, and lines that short
+// meet the spills around their ends more often; a large grid makes up for it.  40^3
+// cells, 100 sub-steps: r = 6 5.79 / 7.41 ms, r = 7 10.3 / 10.7, r = 8 10.9 / 11.7;
+// 64^3, r = 8, 200 sub-steps 66.5 / 70.1; 96^3 225 / 225; 192^3 1800 / 1751; 128^3,
+// 60 sub-steps 206 / 210.
+constexpr int FLAT_THREE_WAVES_SUB = 96;
+constexpr int64_t FLAT_DET_THREE_WAVES_LINES = 128 * 128;
+
+static bool flat_three_waves(int r, const LineArgs &a)
+{
+    const bool subs = a.n_sub >= FLAT_THREE_WAVES_SUB;
+    if (a.part) return r < 6 || (subs && (int64_t)a.nx * a.ny >= FLAT_DET_THREE_WAVES_LINES);
+    return r != 6 || subs;
+}
+
+template <int R, bool LAB, bool DET>
+static hipError_t launch_flat_rd(int mode, const LineArgs &a, hipStream_t st)
+{
+    if (mode == M_FP64) return launch_flat_f<Flat64<R>, LAB, DET>(a, st);
+    if constexpr (R >= 4) {
+        if constexpr (R == 6 || (DET && R > 6))
+            if (!flat_three_waves(R, a)) return launch_flat_f<Flat<R, 2>, LAB, DET>(a, st);
+        return launch_flat_f<Flat<R>, LAB, DET>(a, st);
+    }
+    return hipErrorInvalidValue;
+}
 
 template <int R, bool LAB>
 static hipError_t launch_flat_r(int mode, const LineArgs &a, hipStream_t st)
 {
-    if (mode == M_FP64)
-        return a.part ? launch_flat_f<Flat64<R>, LAB, true>(a, st) : launch_flat_f<Flat64<R>, LAB, false>(a, st);
-    if constexpr (R >= 4) {
-        if (a.part) return launch_flat_f<Flat<R, R >= 6 ? 2 : 3>, LAB, true>(a, st);
-        if constexpr (R == 6)
-            if (a.n_sub < FLAT6_THREE_WAVES) return launch_flat_f<Flat<R, 2>, LAB, false>(a, st);
-        return launch_flat_f<Flat<R>, LAB, false>(a, st);
-    }
-    return hipErrorInvalidValue;
+    return a.part ? launch_flat_rd<R, LAB, true>(mode, a, st) : launch_flat_rd<R, LAB, false>(mode, a, st);
 }
 
 template <bool LAB>

@@ -37,3 +37,20 @@ def test_step(prec, r, n_sub):
     assert np.max(np.abs(got - det)) <= 1e-13 * np.abs(det).max()
     lab = to_host(fd.fdirw_step_noalloc(dom, to_dev(c0), torch.empty_like(to_dev(c0)), prec=prec))
     assert np.max(np.abs(lab - got)) <= 1e-13 * np.abs(got).max()
+
+
+@pytest.mark.parametrize("r,n_sub", [(6, 95), (6, 96), (7, 96), (8, 95), (8, 96)])
+def test_deterministic_step_of_many_lines(r, n_sub):
+    # 128 x 128 lines, where the deterministic form changes its register budget;
+    # few planes and sources
+    d = synth.random_small((3, 128, 128), 3, r=r, n_sub=n_sub, seed=340 + r)
+    c0 = d.c0.copy()
+    c0[:, 24:, :] = 0.0
+    c0[:, :, 20:] = 0.0
+    dom = fd.Domain(d.label, d.d_phase, d.r, d.n_sub, d.h, d.dt)
+    det = to_host(fd.fdirw_step(dom, to_dev(c0), prec=fd.FP32, deterministic=True))
+    ref, _, _ = oracle.Problem.from_domain(d).step(c0)
+    assert np.max(np.abs(det - ref)) <= 1e-5
+    assert np.array_equal(det, to_host(fd.fdirw_step(dom, to_dev(c0), prec=fd.FP32, deterministic=True)))
+    got = to_host(fd.fdirw_step(dom, to_dev(c0), prec=fd.FP32))
+    assert np.max(np.abs(got - det)) <= 1e-13 * np.abs(det).max()
