@@ -14,7 +14,8 @@ namespace fdirw {
 // Bound by the LDS exchange like the fused step: 645 clocks per CU, window and
 // sub-step at r = 8 (4.6 T cell-sub-steps/s; the segment layout 1,340), 89 at
 // r = 4.  The bank of a 56 x 48 x 52 grid (r = 8, 200 sub-steps, FP16) is built
-// in 35.6 ms, 57.9 ms in the segment layout.
+// in 35.5 ms, 57.9 ms in the segment layout; with few sub-steps the coefficient
+// loads bound it and the segment layout is the faster one (flat_window_min_sub).
 template <int M, int R>
 __global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(3)))
 flat_window_kernel(WindowArgs a)
@@ -114,8 +115,8 @@ flat_window_kernel(WindowArgs a)
 // (SINK) the far-field cells absorb and the kernel keeps the mass that is
 // left.  The bins of a window live in its exchange buffers, which are free
 // after the sub-steps; consecutive cells of a run mostly fall in one bin and
-// are added up in a register first.  An 80 x 64 x 72 build (r = 8, 200
-// sub-steps) takes 81.4 ms, 118.4 ms in the segment layout.
+// are added up in a register first.  An 80 x 64 x 72 build (porous medium, r = 8,
+// 200 sub-steps) takes 64 ms, 117 ms in the segment layout.
 template <int R, bool SINK>
 __global__ void __launch_bounds__(FLAT_NT) __attribute__((amdgpu_waves_per_eu(3)))
 flat_coarse_kernel(CoarseGenArgs a)
@@ -164,8 +165,9 @@ flat_coarse_kernel(CoarseGenArgs a)
             const int at = (ax == 0 ? sx : ax == 1 ? sy : sz) - R + j;
             dest[g][ax][j] = (at < 0 ? 0 : at / B) - (ax == 0 ? jx : ax == 1 ? jy : jz) + K;
         }
-        // which cells of the run are grouped / far-field cells, through LDS
-        // like the coefficients: 1 grouped, 2 far field, 0 else
+        // which cells of the run are grouped / far-field cells, read in grid
+        // order and changed to the run order in LDS: 1 grouped, 2 far field, 0
+        // else (the coefficients come straight from memory, see flat_load)
         int at = tg;
         asm volatile("" : "+v"(at));
 #pragma unroll
