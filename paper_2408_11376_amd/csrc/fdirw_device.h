@@ -99,6 +99,15 @@ __device__ __forceinline__ int xcd_remap(int b, int g)
     return (b % 8) * (g / 8) + b / 8;
 }
 
+// The same with runs of `run` consecutive indices per XCD, the runs in turn (the
+// last ones, fewer than 8 runs, as they come).
+__device__ __forceinline__ int xcd_runs(int b, int g, int run)
+{
+    if (b >= g / (8 * run) * (8 * run)) return b;
+    const int q = b / 8;
+    return (q / run * 8 + b % 8) * run + q % run;
+}
+
 #ifndef FDIRW_SEG_CELLS
 #define FDIRW_SEG_CELLS 9          // most cells of a z-column one thread owns
 #endif

@@ -140,10 +140,14 @@ flat_coarse_kernel(CoarseGenArgs a)
     const int B = a.block, K = a.K, KW = 2 * K + 1, nb = KW * KW * KW;
     for (int i = t; i < 2 * LPW * XLEN; i += FLAT_NT) xb[i] = 0.0f;
 
-    // consecutive groups on different XCDs: grouped cells may lie in clumps, and
-    // runs of them on one XCD leave the others idle (56^3 cells, r = 8, 5 % in
-    // clumps: 5.3 against 3.6 ms; everything grouped: 43.8 and 43.5)
-    for (int64_t q0 = (int64_t)blockIdx.x * LPW; q0 < a.n; q0 += (int64_t)gridDim.x * LPW) {
+    // runs of 128 groups of cells per XCD, the runs in turn: neighbours share
+    // their coefficients in one L2, and clumps of grouped cells are spread over the
+    // XCDs.  One range per XCD / groups one by one / runs of 32, 128, 512 (ms):
+    // particle of radius 50 in 192^3 cells 112.6 / 137.9 / 108.8, 106.4, 111.9; 56^3
+    // cells, r = 8, 5 % grouped in clumps 5.3 / 3.5 / 3.3, 3.5, 3.4, all grouped 44
+    // each; 80 x 64 x 72 72.3 / 65.7 / 62.3, 63.4, 63.1
+    const int b = xcd_runs((int)blockIdx.x, (int)gridDim.x, 128);
+    for (int64_t q0 = (int64_t)b * LPW; q0 < a.n; q0 += (int64_t)gridDim.x * LPW) {
         // sources outside every group are skipped (when all of the
         // workgroup's are, the whole trip: uniform per block)
         bool any = false, live = false;
