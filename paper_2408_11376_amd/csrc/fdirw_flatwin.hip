@@ -386,6 +386,10 @@ flat_flow_kernel(FlowArgs a)
             // the kernel in (z, y, x) window order into the run region of
             // the second buffer (rewritten by every sub-step before a read)
             float *stage = xg + LPW * XLEN + PAD;
+            // positions recomputed, not kept across the sub-steps: at 20 cells per
+            // thread they were spilled (16,000 sources, ms: r = 6, 113 sub-steps
+            // 2.60 -> 2.12, r = 7, 153 5.64 -> 4.86, r = 8, 200 6.60 -> 5.96)
+            asm volatile("" : "+v"(s0v));
 #pragma unroll
             for (int k = 0; k < RUN; ++k) {
                 const FlatCell<F> p(s0v + k);
